@@ -18,8 +18,10 @@
 //     (instance, node, chunk) items from a queue, lanes refilled with the
 //     chunk's next path when a path ends, path values evaluated when an
 //     item drains, FP64 per-lane sums reduced by wave shuffles.
-//   * paths_fp64: the plain baseline.  One thread per path, FP64 throughout
-//     (software transcendentals), one launch per instance, block reduction.
+//   * paths_fp64: the same estimator in double precision throughout, one
+//     launch per instance (path_fp64.hpp): the monitor from an LDS table of
+//     rho, elementary functions written for the 23-bit uniforms, lanes that
+//     go on to the wave's next item as their paths end.
 //
 // The random stream of path p of interface node r: word q is word (q mod 4)
 // of Philox4x32-10 (Salmon et al., SC'11) at counter
@@ -1007,37 +1009,14 @@ __global__ __launch_bounds__(kTableBlock) void paths_fp32_win(const InstView *__
 }
 
 // ---------------------------------------------------------------------------
-// FP64 plain path
+// FP64 path
 // ---------------------------------------------------------------------------
-struct StreamF64 {
-    uint32_t path, node, ctr3, key0, key1;
-    uint32_t blk;
-    Words4 cur;
-    __device__ uint32_t word(uint32_t q)
-    {
-        const uint32_t b = q >> 2;
-        if (b != blk) {
-            cur = philox4x32_10(b, path, node, ctr3, key0, key1);
-            blk = b;
-        }
-        const uint32_t r = q & 3u;
-        return r == 0 ? cur.w0 : (r == 1 ? cur.w1 : (r == 2 ? cur.w2 : cur.w3));
-    }
-};
-
 __device__ __forceinline__ int cell_of_d(double s, int n1, double &t)
 {
     int c = (int)floor(s);
     c = max(0, min(c, n1 - 1));
     t = s - (double)c;
     return c;
-}
-
-__device__ __forceinline__ double bilinear_d(const double *f, int n_xi, int cx, int cy, double tx, double ty)
-{
-    const double *r0 = f + (size_t)cy * n_xi + cx;
-    const double *r1 = r0 + n_xi;
-    return (1.0 - tx) * (1.0 - ty) * r0[0] + tx * (1.0 - ty) * r0[1] + (1.0 - tx) * ty * r1[0] + tx * ty * r1[1];
 }
 
 __device__ __forceinline__ double boundary_d(const double *b0, const double *b1, int n_xi, int n_eta, int side,
@@ -1072,152 +1051,119 @@ __device__ __forceinline__ double keys_d(const double *pad, int n_xi, int n_eta,
     return acc;
 }
 
-struct PathOutD {
-    double vx, vy;
-    int side;
-    int steps;
+}  // namespace msdd
+
+#include "path_fp64.hpp"
+
+namespace msdd {
+
+// Item sources of the FP64 kernel.  Src64List: all items of the launch.  The
+// waves take their first `rounds` items by their number, wave after wave
+// across the workgroups (so a launch with fewer items than waves spreads over
+// every CU), the others from one counter.
+struct Src64List {
+    uint32_t *head;
+    uint32_t n_items, chunks, chunk_paths, n_paths, wave, waves, rounds, taken;
+    __device__ __forceinline__ bool next(int lane, uint32_t &node, uint32_t &p_begin, uint32_t &count,
+                                         uint32_t &partial)
+    {
+        const uint32_t it = taken < rounds ? wave + taken * waves : rounds * waves + pop_item(head, lane);
+        ++taken;
+        if (it >= n_items) return false;
+        node = it / chunks;
+        const uint32_t c = it - node * chunks;
+        p_begin = c * chunk_paths;
+        count = min(chunk_paths, n_paths - p_begin);
+        partial = it;
+        return true;
+    }
 };
 
-// One whole path in FP64 (a2-a7).
-template <bool TRACE>
-__device__ __forceinline__ PathOutD run_path_f64(const InstView &I, uint32_t node, uint32_t path, double *trace)
-{
-    const int nx1 = I.n_xi - 1, ny1 = I.n_eta - 1;
-    const double dt = I.dt, sq = sqrt(2.0 * dt);
-    StreamF64 S{path, I.node_r[node], I.ctr3, I.key0, I.key1, 0xFFFFFFFFu, Words4{0, 0, 0, 0}};
-    double x = (double)I.node_i[node] / (double)nx1;
-    double y = (double)I.node_j[node] / (double)ny1;
-    long wx = 0, wy = 0;
-    PathOutD out{0.0, 0.0, -1, I.K};
-    for (int k = 0; k < I.K; ++k) {
-        const uint32_t q = 3u * (uint32_t)k;
-        const double u0 = uniform_f64(S.word(q));
-        const double u1 = uniform_f64(S.word(q + 1u));
-        double sn, cs;
-        sincospi(2.0 * u1, &sn, &cs);
-        const double rad = sqrt(-2.0 * log(u0));
-        const double n1 = rad * cs, n2 = rad * sn;
+// Src64Job: the items q0 .. q0 + count of a windowed job, handed out by a
+// counter in LDS.
+struct Src64Job {
+    uint32_t *next_item;
+    uint32_t q0, n_items, chunks, chunk_paths, n_paths;
+    __device__ __forceinline__ bool next(int lane, uint32_t &node, uint32_t &p_begin, uint32_t &count,
+                                         uint32_t &partial)
+    {
+        const uint32_t it = pop_item(next_item, lane);
+        if (it >= n_items) return false;
+        partial = q0 + it;
+        node = partial / chunks;
+        const uint32_t c = partial - node * chunks;
+        p_begin = c * chunk_paths;
+        count = min(chunk_paths, n_paths - p_begin);
+        return true;
+    }
+};
 
-        double tx, ty;
-        const int cx = cell_of_d(x * (double)nx1, nx1, tx);
-        const int cy = cell_of_d(y * (double)ny1, ny1, ty);
-        const double r = bilinear_d(I.rho, I.n_xi, cx, cy, tx, ty);
-        const double rx = bilinear_d(I.rho_xi, I.n_xi, cx, cy, tx, ty);
-        const double ry = bilinear_d(I.rho_eta, I.n_xi, cx, cy, tx, ty);
-        double nx = x + (rx / r) * dt + sq * n1;
-        double ny = y + (ry / r) * dt + sq * n2;
-        if (I.per_xi) {
-            const double f = floor(nx);
-            nx -= f;
-            wx += (long)f;
-            if (nx >= 1.0) { nx -= 1.0; wx += 1; }
-        }
-        if (I.per_eta) {
-            const double f = floor(ny);
-            ny -= f;
-            wy += (long)f;
-            if (ny >= 1.0) { ny -= 1.0; wy += 1; }
-        }
-        if (TRACE) {
-            trace[4 * k + 0] = nx;
-            trace[4 * k + 1] = ny;
-            trace[4 * k + 2] = n1;
-            trace[4 * k + 3] = n2;
-        }
-        int side = -1;
-        if (!I.per_xi) {
-            if (nx < 0.0) { side = 0; nx = 0.0; }
-            else if (nx > 1.0) { side = 1; nx = 1.0; }
-        }
-        if (!I.per_eta) {
-            if (ny < 0.0) { side = side < 0 ? 2 : side; ny = 0.0; }
-            else if (ny > 1.0) { side = side < 0 ? 3 : side; ny = 1.0; }
-        }
-        if (side < 0 && I.bridge) {
-            double p[4] = {0.0, 0.0, 0.0, 0.0};
-            if (!I.per_xi) {
-                p[0] = exp(-x * nx / dt);
-                p[1] = exp(-(1.0 - x) * (1.0 - nx) / dt);
-            }
-            if (!I.per_eta) {
-                p[2] = exp(-y * ny / dt);
-                p[3] = exp(-(1.0 - y) * (1.0 - ny) / dt);
-            }
-            const double q_exit = 1.0 - (1.0 - p[0]) * (1.0 - p[1]) * (1.0 - p[2]) * (1.0 - p[3]);
-            if (uniform_f64(S.word(q + 2u)) < q_exit) {
-                int s = 0;
-                double pm = p[0];
-                if (p[1] > pm) { s = 1; pm = p[1]; }
-                if (p[2] > pm) { s = 2; pm = p[2]; }
-                if (p[3] > pm) { s = 3; pm = p[3]; }
-                side = s;
-                if (s == 0) nx = 0.0;
-                if (s == 1) nx = 1.0;
-                if (s == 2) ny = 0.0;
-                if (s == 3) ny = 1.0;
-            }
-        }
-        x = nx;
-        y = ny;
-        if (side >= 0) {
-            const double w_tn = (double)(k + 1) * dt / I.tau;
-            const double tang = side < 2 ? y : x;
-            out.vx = boundary_d(I.bnd0, I.bnd1, I.n_xi, I.n_eta, side, 0, tang, w_tn);
-            out.vy = boundary_d(I.bnd0, I.bnd1, I.n_xi, I.n_eta, side, 1, tang, w_tn);
-            out.side = side;
-            out.steps = k + 1;
-            break;
-        }
-    }
-    if (out.side < 0) {
-        out.vx = keys_d(I.xpad, I.n_xi, I.n_eta, x, y);
-        out.vy = keys_d(I.ypad, I.n_xi, I.n_eta, x, y);
-    }
-    if (I.per_xi) out.vx += (double)wx * I.Lx;
-    if (I.per_eta) out.vy += (double)wy * I.Ly;
-    return out;
-}
-
-__global__ __launch_bounds__(kFp64Block) void paths_fp64(const InstView *__restrict__ inst, uint32_t n_paths,
-                                                         uint32_t chunks, Partial *__restrict__ partials)
+// FP64 kernel: a persistent grid of 1024-thread workgroups, one per CU, four
+// waves per SIMD (at most 128 registers).  PER: the instance's periodic flags
+// (PER & 1: xi, PER >> 1: eta).  MODE: where the padded rho table is read
+// (path_fp64.hpp): 1, the whole table in LDS, taken where it fits; 2, windows
+// of it per job, as in paths_fp32_win; 0, global memory, for a launch that has
+// no room for its job list (the no-allocation solve).
+// Bound: VALU issue (217 vector instructions per path-step, 90 % of the issue
+// slots).  The form before it -- one thread per path, the library's log,
+// sincospi, sqrt and exp, twelve 8-byte gathers per substep, no lane refill --
+// took about 680 slots and filled the texture path as well: 129^2 bump,
+// 753 nodes, N = 10^4, K = 500: 54.4 -> 22.2 ms; 33^2, 31 nodes, N = 10^4:
+// 2.67 -> 1.6 ms (4844 items on 4096 waves: the second round is mostly empty).
+template <int PER, int MODE>
+__global__ __launch_bounds__(kTableBlock) void paths_fp64(Fp64View V, uint32_t n_paths, uint32_t chunks)
 {
-    const InstView &I = *inst;
-    const uint32_t node = blockIdx.x / chunks;
-    const uint32_t chunk = blockIdx.x - node * chunks;
-    const uint32_t path = chunk * kFp64Block + threadIdx.x;
-    double v[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    if (path < n_paths) {
-        const PathOutD o = run_path_f64<false>(I, node, path, nullptr);
-        const int i0 = I.node_i[node], j0 = I.node_j[node];
-        const double dx = o.vx - I.x64[(size_t)j0 * I.n_xi + i0];
-        const double dy = o.vy - I.y64[(size_t)j0 * I.n_xi + i0];
-        v[0] = dx;
-        v[1] = dx * dx;
-        v[2] = dy;
-        v[3] = dy * dy;
-        v[4] = o.side >= 0 ? 1.0 : 0.0;
-        v[5] = (double)o.steps;
+    constexpr int BLOCK = kTableBlock;
+    __shared__ double lds[MODE == 0 ? 2 : kPad64 + 2];
+    uint32_t *ctl = (uint32_t *)lds;   // [0]: current job, [1]: next item of the job
+    double *tab = lds + 2;
+    const int lane = threadIdx.x & 63;
+    const InstView &I = V;
+    const ConstD C = load_const_d<PER>(I);
+    const GLOBAL double *pad = gptr(I.rho_pad);
+    if (MODE != 2) {
+        Tab64 T{nullptr, C.stride, 0, 0, 0, 0};
+        if (MODE == 1) {
+            const int n = C.stride * (I.n_eta + 2);
+            for (int q = threadIdx.x; q < n; q += BLOCK) tab[q] = pad[q];
+            __syncthreads();
+            T.lds = tab + C.stride + 1;
+        }
+        const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * gridDim.x + blockIdx.x;
+        Src64List src{V.head, V.n_items, chunks, V.chunk_paths, n_paths, wave, gridDim.x * (uint32_t)(BLOCK / 64),
+                      V.static_rounds, 0u};
+        item_loop64<PER, MODE>(src, I, C, T, lane);
+        return;
     }
-    // fixed-order tree reduction over the block
-    __shared__ double red[6][kFp64Block];
-#pragma unroll
-    for (int c = 0; c < 6; ++c) red[c][threadIdx.x] = v[c];
-    __syncthreads();
-    for (int s = kFp64Block / 2; s >= 1; s >>= 1) {
-        if ((int)threadIdx.x < s) {
-#pragma unroll
-            for (int c = 0; c < 6; ++c) red[c][threadIdx.x] += red[c][threadIdx.x + s];
+    const uint32_t n_jobs = V.qs.b[kJobQueues];
+    for (;;) {
+        if (threadIdx.x == 0) {
+            uint32_t j = n_jobs;
+            for (int t = 0; t < kJobQueues; ++t) {
+                const int q = (int)((blockIdx.x + (uint32_t)t) % (uint32_t)kJobQueues);
+                const uint32_t k = V.qs.b[q] + atomicAdd(V.head + q, 1u);
+                if (k < V.qs.b[q + 1]) {
+                    j = k;
+                    break;
+                }
+            }
+            ctl[0] = j;
+            ctl[1] = 0u;
         }
         __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-        Partial &o = partials[blockIdx.x];
-        o.s1x = red[0][0];
-        o.s2x = red[1][0];
-        o.s1y = red[2][0];
-        o.s2y = red[3][0];
-        o.exits = (unsigned long long)red[4][0];
-        o.steps = (unsigned long long)red[5][0];
+        const uint32_t job = ctl[0];
+        if (job >= n_jobs) break;   // the same for the whole workgroup
+        const WinJob J = V.jobs[job];
+        const int sw = J.tw + 2;   // the window and one node around it (ghosts at the grid's edge)
+        for (int q = threadIdx.x; q < sw * (J.th + 2); q += BLOCK) {
+            const int r = q / sw, c = q - r * sw;
+            tab[q] = pad[(int64_t)(J.j0 + r) * C.stride + J.i0 + c];
+        }
+        __syncthreads();
+        const Tab64 T{tab + sw + 1, sw, J.i0, J.j0, J.tw - 1, J.th - 1};
+        Src64Job src{ctl + 1, J.q0, J.count, chunks, V.chunk_paths, n_paths};
+        item_loop64<PER, MODE>(src, I, C, T, lane);
+        __syncthreads();   // every wave is done with the window
     }
 }
 
@@ -1532,12 +1478,20 @@ __global__ void debug_paths_kernel(const InstView *__restrict__ inst, int fp64, 
     const uint32_t path = p_begin + t;
     double *tr = trace ? trace + (size_t)t * 4 * I.K : nullptr;
     if (fp64) {
-        const PathOutD o = tr ? run_path_f64<true>(I, node, path, tr) : run_path_f64<false>(I, node, path, nullptr);
-        vx[t] = o.vx;
-        vy[t] = o.vy;
-        exited[t] = o.side >= 0;
-        side_out[t] = o.side;
-        steps[t] = o.steps;
+        const ConstD C = load_const_d<-1>(I);
+        const Tab64 T{nullptr, C.stride, 0, 0, 0, 0};
+        PathD P{(double)I.node_i[node] / C.fnx1, (double)I.node_j[node] / C.fny1, 0.0, 0.0, 0, false};
+        P.near = side_distance64(C, P.x, P.y) < C.delta;
+        int side = -1;
+        bool ended = false;
+        while (!ended)
+            side = tr ? group64<true, 0>(P, C, T, path, I.node_r[node], I.ctr3, I.key0, I.key1, ended, tr, 1u, 64u)
+                      : group64<false, 0>(P, C, T, path, I.node_r[node], I.ctr3, I.key0, I.key1, ended, nullptr, 1u,
+                                          64u);
+        value64(I, C, P, side, vx[t], vy[t]);
+        exited[t] = side >= 0;
+        side_out[t] = side;
+        steps[t] = P.k;
         return;
     }
     const ConstF C = load_const_f<-1>(I);
@@ -1737,14 +1691,38 @@ int paths_fp32_window_blocks_per_cu(size_t lds)
 
 size_t paths_fp32_lds_bytes(int block, uint32_t cap) { return (size_t)(block / 64) * 6u * cap * sizeof(float); }
 
+template <int MODE>
+static void launch_fp64(const Fp64View &v, uint32_t n_paths, uint32_t chunks, hipStream_t s)
+{
+    const dim3 grid(v.grid), block(kTableBlock);
+    switch (v.per_xi + 2 * v.per_eta) {
+    case 0: hipLaunchKernelGGL((paths_fp64<0, MODE>), grid, block, 0, s, v, n_paths, chunks); break;
+    case 1: hipLaunchKernelGGL((paths_fp64<1, MODE>), grid, block, 0, s, v, n_paths, chunks); break;
+    case 2: hipLaunchKernelGGL((paths_fp64<2, MODE>), grid, block, 0, s, v, n_paths, chunks); break;
+    default: hipLaunchKernelGGL((paths_fp64<3, MODE>), grid, block, 0, s, v, n_paths, chunks); break;
+    }
+}
+
 hipError_t launch_paths_fp64(const InstView *inst, uint32_t M, uint32_t n_paths, uint32_t chunks_per_node,
                              Partial *partials, hipStream_t s)
 {
-    const size_t blocks = (size_t)M * chunks_per_node;
-    if (blocks == 0) return hipSuccess;
-    if (blocks > 0x7FFFFFFFu) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(paths_fp64, dim3((unsigned)blocks), dim3(kFp64Block), 0, s, inst, n_paths, chunks_per_node,
-                       partials);
+    const Fp64View &v = *static_cast<const Fp64View *>(inst);
+    if (M == 0 || chunks_per_node == 0) return hipSuccess;
+    if (v.n_items != M * chunks_per_node || v.grid < 1u || v.partials != partials || !v.rho_pad || !v.head ||
+        (uint64_t)v.chunk_paths * chunks_per_node < n_paths || v.chunk_paths < 64u)
+        return hipErrorInvalidValue;
+    const hipError_t e = launch_fill_u32(v.head, 0u, kJobQueues, s);
+    if (e != hipSuccess) return e;
+    if (v.mode == 1) {
+        if ((size_t)(v.n_xi + 2) * (v.n_eta + 2) > (size_t)kPad64) return hipErrorInvalidValue;
+        launch_fp64<1>(v, n_paths, chunks_per_node, s);
+    } else if (v.mode == 2) {
+        for (int q = 0; q < kJobQueues; ++q)
+            if (v.qs.b[q] > v.qs.b[q + 1]) return hipErrorInvalidValue;
+        launch_fp64<2>(v, n_paths, chunks_per_node, s);
+    } else {
+        launch_fp64<0>(v, n_paths, chunks_per_node, s);
+    }
     return hipGetLastError();
 }
 

@@ -31,6 +31,7 @@ struct WorkRange {
 // nodes [i0, i0 + tw) x [j0, j0 + th), inside the grid.  kind 0: the window
 // holds (rho, dt rho_xi) per node (8 B); kind 1: also dt rho_eta per node
 // (4 B each, after the pairs).
+// FP64 launches: the window holds rho alone, with one node more on each side.
 struct WinJob {
     uint32_t range;
     uint32_t q0;
@@ -97,8 +98,9 @@ struct InstView {
     const float *xpad_f, *ypad_f;
     const float *bnd0_f, *bnd1_f;
 
-    // FP64 path: node tables rho, rho_xi, rho_eta; padded mesh; boundary.
-    const double *rho, *rho_xi, *rho_eta;
+    // FP64 path: rho padded by one node on each side ([n_eta+2][n_xi+2], Keys'
+    // ghost values or images; FP64 instances only); padded mesh; boundary.
+    const double *rho_pad;
     const double *xpad, *ypad;
     const double *bnd0, *bnd1;
 
@@ -107,6 +109,19 @@ struct InstView {
 
     // Partial sums of this request's work items.
     Partial *partials;
+};
+
+// One FP64 launch: the instance and how its items are handed out.  The
+// address given to launch_paths_fp64 is the host address of one of these.
+struct Fp64View : InstView {
+    uint32_t n_items;        // (node, chunk) items, node-major; item q writes partial q
+    uint32_t chunk_paths;    // paths per full chunk
+    uint32_t static_rounds;  // items that a wave takes by its number before it uses the counter
+    uint32_t grid;           // workgroups
+    int32_t mode;            // 0: rho from global memory, 1: whole table in LDS, 2: windows (jobs)
+    uint32_t *head;          // kJobQueues counters
+    const WinJob *jobs;      // mode 2
+    JobQueues qs;
 };
 
 // The FP32 path kernels' compile-time kind of an instance: its periodicity

@@ -82,11 +82,14 @@ hipError_t launch_paths_fp32_window(const InstView *insts, const WorkRange *rang
                                     uint32_t max_quarters, hipStream_t s);
 int paths_fp32_window_blocks_per_cu(size_t lds);
 
-// a2-a8, FP64 plain: one thread per path, one launch per instance; the
-// partial of (node, chunk) goes to partials[node * chunks + chunk].
+// a2-a8, FP64: persistent kernel over the items of one instance; `inst` is
+// the (host) address of the InstView part of an Fp64View.  The partial of
+// (node, chunk) goes to partials[node * chunks + chunk].
 hipError_t launch_paths_fp64(const InstView *inst, uint32_t M, uint32_t n_paths, uint32_t chunks_per_node,
                              Partial *partials, hipStream_t s);
-constexpr int kFp64Block = 256;
+constexpr int kFp64Block = 256;              // paths per item of large requests
+constexpr int kPad64Side = 143;              // padded rho in LDS: at most 143 x 143 doubles
+constexpr int kPad64 = kPad64Side * kPad64Side;
 
 // a9: fixed-order combine of each node's partials; mean, SE, exit fraction,
 // written at the node's interface rank (inst->node_r).

@@ -74,7 +74,18 @@ float4 *cell_records(const mesh_sdd &inst)
     return inst.cells.as<float4>() + (size_t)(inst.d.n_xi - 1) * (inst.d.n_eta - 1);
 }
 
-// Build the monitor's node tables and FP32 cell table from inst->rho_in on
+// The padded rho of an FP64 instance, in the same allocation.
+double *rho_padded(const mesh_sdd &inst) { return inst.cells.as<double>(); }
+
+// The rest of that allocation: room for the FP32 outputs that prep_mesh
+// writes beside the FP64 ones and no FP64 kernel reads (12 of the 64 bytes
+// per cell are used in all; 12 (n + 2)^2 <= 64 (n - 1)^2 from n = 4 on).
+float *fp64_spare(const mesh_sdd &inst)
+{
+    return reinterpret_cast<float *>(rho_padded(inst) + (size_t)(inst.d.n_xi + 2) * (inst.d.n_eta + 2));
+}
+
+// Build the monitor's node tables and FP32 cell table (FP64 instances: the padded rho) from inst->rho_in on
 // `st` (a0), wait for them, and mark the monitor as set.  The caller holds
 // the context's gpu_mu.
 int install_monitor(mesh_sdd *inst, hipStream_t st)
@@ -82,6 +93,18 @@ int install_monitor(mesh_sdd *inst, hipStream_t st)
     const mesh_sdd_desc &d = inst->d;
     HIP_TRY(msdd::launch_prep_gradient(inst->rho_in.as<double>(), d.n_xi, d.n_eta, d.periodic_xi, d.periodic_eta,
                                        inst->rho.as<double>(), inst->rho_xi.as<double>(), inst->rho_eta.as<double>(), st));
+    if (d.precision == MESH_SDD_FP64) {
+        // the FP64 kernel reads rho alone, padded by one node on each side;
+        // the table takes the place of the FP32 cell records (which an FP64
+        // instance does not read)
+        float *const spare = fp64_spare(*inst);
+        HIP_TRY(msdd::launch_prep_mesh(inst->rho.as<double>(), inst->rho.as<double>(), d.n_xi, d.n_eta, d.periodic_xi,
+                                       d.periodic_eta, 0.0, 0.0, rho_padded(*inst), rho_padded(*inst), spare, spare,
+                                       st));
+        HIP_TRY(hipStreamSynchronize(st));
+        inst->monitor_set = true;
+        return MESH_SDD_OK;
+    }
     HIP_TRY(msdd::launch_prep_cells(inst->rho.as<double>(), inst->rho_xi.as<double>(), inst->rho_eta.as<double>(),
                                     d.n_xi, d.n_eta, d.tau / (double)d.K, cell_records(*inst),
                                     inst->cells.as<float4>(), st));
@@ -398,11 +421,15 @@ std::shared_ptr<Request> make_request(mesh_sdd *inst, const mesh_sdd_step &s, in
 // gathers.
 constexpr int kWin1MaxN = 400;
 
-// LDS bytes of a window of tw x th nodes.
+// LDS bytes of a window of tw x th nodes.  Kind 2 is the FP64 kernel's: rho
+// alone in double precision, one node more on each side.
 size_t window_bytes(int kind, int tw, int th)
 {
+    if (kind == 2) return (size_t)(tw + 2) * (th + 2) * sizeof(double);
     return (size_t)tw * th * (kind ? 12 : 8);
 }
+
+size_t window_limit(int kind) { return kind == 2 ? msdd::kPad64 * sizeof(double) : msdd::kWinBytes; }
 
 // want: 0 automatic, 1 two-field (kind 0), 2 three-field (kind 1); a
 // window that holds the whole grid is always taken.
@@ -419,11 +446,13 @@ int window_kind(const mesh_sdd_desc &d, int want = 0)
 // whole axis where it fits.
 void window_dims(int kind, int n_xi, int n_eta, int *wx, int *wy)
 {
-    const int side = kind ? msdd::kWin3Side : 140;   // the largest square of each kind within kWinBytes
+    // the largest square of each kind
+    const int side = kind == 2 ? msdd::kPad64Side - 2 : kind ? msdd::kWin3Side : 140;
+    const size_t limit = window_limit(kind);
     int y = std::min(n_eta, side);
     int x = n_xi;
-    while (window_bytes(kind, x, y) > msdd::kWinBytes) --x;
-    while (y < n_eta && window_bytes(kind, x, y + 1) <= msdd::kWinBytes) ++y;
+    while (window_bytes(kind, x, y) > limit) --x;
+    while (y < n_eta && window_bytes(kind, x, y + 1) <= limit) ++y;
     *wx = x;
     *wy = y;
 }
@@ -431,6 +460,9 @@ void window_dims(int kind, int n_xi, int n_eta, int *wx, int *wy)
 // Window nodes beyond a block on each side, where the axis does not fit
 // (`want` > 0: the tuned margin).
 int window_margin(int kind, int want = 0) { return want > 0 ? want : (kind ? 30 : 45); }
+
+// Margin of the FP64 kernel's windows (at most 141 nodes a side).
+constexpr int kMargin64 = 45;
 
 // Block layout of an instance's windowed launches: window kind and margin.
 struct Layout {
@@ -441,6 +473,13 @@ Layout layout_of(const mesh_sdd_desc &d, const mesh_sdd_launch &l)
 {
     const int kind = window_kind(d, l.window_kind);
     return Layout{kind, window_margin(kind, l.window_margin)};
+}
+
+// Layout of the node lists that a request of the instance runs from: the
+// FP64 kernel's windows have a layout of their own, which no knob changes.
+Layout set_layout(const mesh_sdd_desc &d, const mesh_sdd_launch &l)
+{
+    return d.precision == MESH_SDD_FP64 ? Layout{2, kMargin64} : layout_of(d, l);
 }
 
 // Block length along an axis of n nodes whose window is w nodes long (at
@@ -543,6 +582,22 @@ int sample_set(mesh_sdd &inst, int stride, const Layout &lay, const SampleSet **
 #endif
 constexpr uint32_t kMaxLaunchItems = MESH_SDD_MAX_LAUNCH_ITEMS;
 
+// A request's counters: the executed-step total, and from byte 64 on the work
+// counters of an FP64 launch.
+constexpr size_t kTotalsBytes = 128;
+
+// Paths per item of an FP64 request.  256; requests below 32 items of 64 paths
+// for every wave of the device take 64, so that the last items of a launch
+// are short and a launch with few items still gives every wave some (6 MB
+// of partials at most; on the 129^2 bump at N = 10^4 items of 256 leave the
+// last of 7.4 rounds half empty).  A function of the request alone, so alone,
+// batched and served results have the same sums.
+int fp64_chunk(const mesh_sdd_ctx *ctx, int32_t Ms, int64_t N)
+{
+    const int64_t waves = (int64_t)ctx->cu_count * (msdd::kTableBlock / 64);
+    return (int64_t)Ms * ((N + 63) / 64) <= 32 * waves ? 64 : msdd::kFp64Block;
+}
+
 // Allocate the request's device buffers, stage its inputs and run the prep
 // kernels; builds the work items.  With an arena the buffers are carved from
 // it instead of allocated (the no-allocation solve).  Caller holds gpu_mu.
@@ -561,7 +616,7 @@ int stage_request(Request &r, const mesh_sdd_step *dev_step, Arena *arena = null
     if (arena) {
         // no allocation: the set of the instance's current layout if built,
         // else any set of the stride (the layout orders the work only)
-        const Layout lay = layout_of(d, launch_for(ctx, d));
+        const Layout lay = set_layout(d, launch_for(ctx, d));
         auto it = inst.samples.find(std::make_tuple(r.stride, lay.kind, lay.margin));
         if (it == inst.samples.end())
             for (auto s = inst.samples.begin(); s != inst.samples.end(); ++s)
@@ -571,20 +626,17 @@ int stage_request(Request &r, const mesh_sdd_step *dev_step, Arena *arena = null
                         "solve with that stride", r.stride);
         r.ss = it->second.get();
     } else {
-        rc = sample_set(inst, r.stride, layout_of(d, launch_for(ctx, d)), &r.ss);
+        rc = sample_set(inst, r.stride, set_layout(d, launch_for(ctx, d)), &r.ss);
         if (rc != MESH_SDD_OK) return rc;
     }
     const int Ms = r.ss->Ms;
 
-    uint32_t chunks;
-    if (fp64)
-        chunks = (uint32_t)((r.N + msdd::kFp64Block - 1) / msdd::kFp64Block);
-    else
-        chunks = (uint32_t)((r.N + r.chunk_paths - 1) / r.chunk_paths);
+    if (fp64) r.chunk_paths = fp64_chunk(ctx, Ms, r.N);
+    const uint32_t chunks = (uint32_t)((r.N + r.chunk_paths - 1) / r.chunk_paths);
     r.chunks_per_node = chunks;
     const size_t n_part = (size_t)Ms * chunks;
-    // the kernels number (node, chunk) items and partials in 32 bits; an FP64
-    // launch runs one 256-thread block per item, within HIP's 2^32 work-items
+    // the kernels number (node, chunk) items and partials in 32 bits; FP64
+    // requests end at 2^24 items of 256 paths
     if (!fp64 && n_part > (size_t)kMaxLaunchItems)
         return fail(MESH_SDD_E_INVAL, "%zu (node, chunk) work items, more than 2^32 - 2^20 (fewer paths per node or "
                     "an interface stride)", n_part);
@@ -598,10 +650,11 @@ int stage_request(Request &r, const mesh_sdd_step *dev_step, Arena *arena = null
         b->arena = arena;
     }
     if (r.x64.alloc(n * 8) || r.y64.alloc(n * 8) || r.b0.alloc(nb * 8) || r.b1.alloc(nb * 8) ||
-        r.xpad.alloc(np * 8) || r.ypad.alloc(np * 8) || r.xpad_f.alloc(np * 4) || r.ypad_f.alloc(np * 4) ||
-        r.b0f.alloc(nb * 4) || r.b1f.alloc(nb * 4) || r.view.alloc(sizeof(InstView)) ||
+        r.xpad.alloc(np * 8) || r.ypad.alloc(np * 8) ||
+        (!fp64 && (r.xpad_f.alloc(np * 4) || r.ypad_f.alloc(np * 4) || r.b0f.alloc(nb * 4) || r.b1f.alloc(nb * 4))) ||
+        r.view.alloc(sizeof(InstView)) ||
         r.partials.alloc(n_part * sizeof(Partial)) || r.spans.alloc((size_t)Ms * sizeof(NodeSpan)) ||
-        r.out.alloc((size_t)5 * M * sizeof(double)) || r.steps_total.alloc(sizeof(unsigned long long)))
+        r.out.alloc((size_t)5 * M * sizeof(double)) || r.steps_total.alloc(kTotalsBytes))
         return fail(MESH_SDD_E_NOMEM, "device allocation for a request failed");
 
     if (dev_step) {
@@ -617,9 +670,12 @@ int stage_request(Request &r, const mesh_sdd_step *dev_step, Arena *arena = null
     }
     HIP_TRY(msdd::launch_prep_mesh(r.x64.as<double>(), r.y64.as<double>(), d.n_xi, d.n_eta, d.periodic_xi,
                                    d.periodic_eta, d.Lx, d.Ly, r.xpad.as<double>(), r.ypad.as<double>(),
-                                   r.xpad_f.as<float>(), r.ypad_f.as<float>(), st));
-    HIP_TRY(msdd::launch_to_f32(r.b0.as<double>(), r.b0f.as<float>(), nb, st));
-    HIP_TRY(msdd::launch_to_f32(r.b1.as<double>(), r.b1f.as<float>(), nb, st));
+                                   fp64 ? fp64_spare(inst) : r.xpad_f.as<float>(),
+                                   fp64 ? fp64_spare(inst) : r.ypad_f.as<float>(), st));
+    if (!fp64) {
+        HIP_TRY(msdd::launch_to_f32(r.b0.as<double>(), r.b0f.as<float>(), nb, st));
+        HIP_TRY(msdd::launch_to_f32(r.b1.as<double>(), r.b1f.as<float>(), nb, st));
+    }
 
     // kernel view
     InstView &v = r.v;
@@ -662,9 +718,7 @@ int stage_request(Request &r, const mesh_sdd_step *dev_step, Arena *arena = null
     v.ypad_f = r.ypad_f.as<float>();
     v.bnd0_f = r.b0f.as<float>();
     v.bnd1_f = r.b1f.as<float>();
-    v.rho = inst.rho.as<double>();
-    v.rho_xi = inst.rho_xi.as<double>();
-    v.rho_eta = inst.rho_eta.as<double>();
+    v.rho_pad = rho_padded(inst);
     v.xpad = r.xpad.as<double>();
     v.ypad = r.ypad.as<double>();
     v.bnd0 = r.b0.as<double>();
@@ -700,6 +754,34 @@ void release_request_buffers(Request &r)
     for (DevBuf *b : {&r.x64, &r.y64, &r.b0, &r.b1, &r.xpad, &r.ypad, &r.xpad_f, &r.ypad_f, &r.b0f, &r.b1f,
                       &r.view, &r.partials, &r.spans, &r.out, &r.steps_total})
         b->release();
+}
+
+// Cuts a job list, in order, into the per-XCD queues of about equal weight.
+template <class Weight>
+void cut_queues(const std::vector<msdd::WinJob> &jobs, Weight weight, msdd::JobQueues &qs)
+{
+    std::vector<double> cum(jobs.size() + 1, 0.0);
+    for (size_t k = 0; k < jobs.size(); ++k) cum[k + 1] = cum[k] + weight(jobs[k]);
+    for (int q = 0, k = 0; q <= msdd::kJobQueues; ++q) {
+        const double goal = cum.back() * q / msdd::kJobQueues;
+        while (q == msdd::kJobQueues ? k < (int)jobs.size() : (k < (int)jobs.size() && cum[k] < goal)) ++k;
+        qs.b[q] = (uint32_t)k;
+    }
+}
+
+// Items that each wave of a persistent launch takes by its number (one per
+// round over the waves) before it uses the launch's counter.  One, so that
+// the first items spread over all CUs.  All of them where an item is shorter
+// than 16 substeps of the wave: the counter, one address for all XCDs, gives
+// out an item every 10 ns or so, which 4096 waves with such items outrun.  In
+// between, all but the last two rounds.
+uint32_t static_rounds(size_t n_items, uint32_t waves, int chunk_paths, int K)
+{
+    const size_t rounds = (n_items + waves - 1) / waves;
+    const int64_t substeps = (int64_t)(chunk_paths / 64) * K;
+    if (substeps <= 16) return (uint32_t)rounds;
+    if (substeps <= 256) return (uint32_t)std::max<size_t>(1, rounds > 2 ? rounds - 2 : 1);
+    return 1u;
 }
 
 // One persistent FP32 launch over the items described by `ranges` (their
@@ -777,16 +859,10 @@ int run_fp32_launch(mesh_sdd_ctx *ctx, const std::vector<InstView> &views, const
                 if (qa < qb) win_lds = std::max(win_lds, window_bytes(b.kind, b.tw, b.th));
             }
         }
-        std::vector<double> cum(jobs.size() + 1, 0.0);
-        for (size_t k = 0; k < jobs.size(); ++k) {
-            const WorkRange &w = ranges[jobs[k].range];
-            cum[k + 1] = cum[k] + (double)jobs[k].count * w.chunk_paths * views[w.inst].K;
-        }
-        for (int q = 0, k = 0; q <= msdd::kJobQueues; ++q) {
-            const double goal = cum.back() * q / msdd::kJobQueues;
-            while (q == msdd::kJobQueues ? k < (int)jobs.size() : (k < (int)jobs.size() && cum[k] < goal)) ++k;
-            qs.b[q] = (uint32_t)k;
-        }
+        cut_queues(jobs, [&](const msdd::WinJob &j) {
+            const WorkRange &w = ranges[j.range];
+            return (double)j.count * w.chunk_paths * views[w.inst].K;
+        }, qs);
         if (jobs_b.reserve(std::max<size_t>(1, jobs.size()) * sizeof(msdd::WinJob)))
             return fail(MESH_SDD_E_NOMEM, "device allocation of the job list failed");
         if (!jobs.empty())
@@ -836,15 +912,49 @@ WorkRange range_of(const Request &r, uint32_t slot, size_t base, size_t first, s
     return w;
 }
 
-// FP64 plain launch of one request.  Caller holds gpu_mu.
-int run_fp64_launch(mesh_sdd_ctx *ctx, Request &r, double *ms)
+// FP64 launch of one request.  Caller holds gpu_mu.
+int run_fp64_launch(mesh_sdd_ctx *ctx, Request &r, double *ms, Arena *arena = nullptr)
 {
     hipStream_t st = ctx->stream;
+    DevBuf a_jobs;
+    a_jobs.arena = arena;
+    DevBuf &jobs_b = arena ? a_jobs : ctx->jobs;
+    msdd::Fp64View v{};
+    static_cast<InstView &>(v) = r.v;
+    const uint32_t waves = (uint32_t)ctx->cu_count * (uint32_t)(msdd::kTableBlock / 64);
+    v.n_items = (uint32_t)((size_t)r.Ms * r.chunks_per_node);
+    v.chunk_paths = (uint32_t)r.chunk_paths;
+    v.static_rounds = static_rounds(v.n_items, waves, r.chunk_paths, r.v.K);
+    v.grid = (uint32_t)ctx->cu_count;
+    v.head = r.steps_total.as<uint32_t>() + 16;
+    v.mode = 1;
+    if (window_bytes(2, v.n_xi, v.n_eta) > window_limit(2)) {
+        // windows: one job per grid block, cut so that every workgroup gets
+        // about 32 of them (at least two items for each of its waves)
+        std::vector<msdd::WinJob> jobs;
+        const size_t jmax = std::max<size_t>(32, v.n_items / ((size_t)ctx->cu_count * 32) + 1);
+        for (const BlockRun &b : r.ss->blocks) {
+            const size_t qa = (size_t)b.pos_begin * r.chunks_per_node, qb = (size_t)b.pos_end * r.chunks_per_node;
+            for (size_t q = qa; q < qb; q += jmax)
+                jobs.push_back(msdd::WinJob{0u, (uint32_t)q, (uint32_t)std::min(jmax, qb - q), b.i0, b.j0, b.tw, b.th,
+                                            (uint32_t)b.kind});
+        }
+        cut_queues(jobs, [](const msdd::WinJob &j) { return (double)j.count; }, v.qs);
+        v.mode = 2;
+        if (jobs_b.reserve(std::max<size_t>(1, jobs.size()) * sizeof(msdd::WinJob))) {
+            if (!arena) return fail(MESH_SDD_E_NOMEM, "device allocation of the job list failed");
+            v.mode = 0;   // no room in the scratch: the table is read from global memory (the same values)
+        } else if (!jobs.empty()) {
+            HIP_TRY(hipMemcpyAsync(jobs_b.p, jobs.data(), jobs.size() * sizeof(msdd::WinJob), hipMemcpyHostToDevice,
+                                   st));
+            v.jobs = jobs_b.as<msdd::WinJob>();
+        }
+    }
     TimerEvents ev;
     HIP_TRY(ev.create());
     HIP_TRY(hipEventRecord(ev.e0, st));
-    hipError_t le = msdd::launch_paths_fp64(r.view.as<InstView>(), (uint32_t)r.Ms, (uint32_t)r.N,
-                                            r.chunks_per_node, r.partials.as<Partial>(), st);
+    hipError_t le = msdd::launch_paths_fp64(&v, (uint32_t)r.Ms, (uint32_t)r.N, r.chunks_per_node,
+                                            r.partials.as<Partial>(), st);
     HIP_TRY(hipEventRecord(ev.e1, st));
     hipError_t se = hipEventSynchronize(ev.e1);
     float t = 0.0f;
@@ -1551,7 +1661,7 @@ try {
         }
     }
     const SampleSet *all = nullptr;
-    rc = sample_set(*inst, 1, layout_of(inst->d, launch_for(ctx, inst->d)), &all);
+    rc = sample_set(*inst, 1, set_layout(inst->d, launch_for(ctx, inst->d)), &all);
     if (rc != MESH_SDD_OK) return rc;
     {
         std::lock_guard<std::mutex> lk(ctx->mu);
@@ -1724,9 +1834,12 @@ try {
     if (set == inst->samples.end())
         return fail(MESH_SDD_E_STATE, "interface stride %d: its node lists are built by the first allocating solve "
                     "with that stride", r->stride);
-    // the scratch this call carves, counted as stage_request and the launch
-    // carve it (each piece rounded to 256 bytes); the job list by its bound
-    // of one job per 64 items plus one per grid block
+    // a bound on the scratch this call carves (each piece rounded to 256
+    // bytes; the job list by one job per 64 items plus one per grid block).
+    // An FP64 request carves no FP32 staging and, with few items, up to 5 MB
+    // more of partials (fp64_chunk): within the bound, as a solve with few
+    // items comes near the capacity only on grids above 1.4e6 nodes, whose
+    // FP32 staging alone is 11 MB
     const bool fp64 = d.precision == MESH_SDD_FP64;
     const size_t n = (size_t)d.n_xi * d.n_eta, np = (size_t)(d.n_xi + 2) * (d.n_eta + 2);
     const size_t nb = 4 * (size_t)d.n_eta + 4 * (size_t)d.n_xi;
@@ -1762,7 +1875,7 @@ try {
     double ms = 0.0;
     if (rc == MESH_SDD_OK) {
         if (fp64) {
-            rc = run_fp64_launch(ctx, *r, &ms);
+            rc = run_fp64_launch(ctx, *r, &ms, &arena);
         } else {
             std::vector<InstView> views{r->v};
             std::vector<WorkRange> ranges;
