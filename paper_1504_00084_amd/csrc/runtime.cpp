@@ -590,12 +590,12 @@ constexpr size_t kTotalsBytes = 128;
 // for every wave of the device take 64, so that the last items of a launch
 // are short and a launch with few items still gives every wave some (6 MB
 // of partials at most; on the 129^2 bump at N = 10^4 items of 256 leave the
-// last of 7.4 rounds half empty).  A function of the request alone, so alone,
-// batched and served results have the same sums.
-int fp64_chunk(const mesh_sdd_ctx *ctx, int32_t Ms, int64_t N)
+// last of 7.4 rounds half empty).  Counted over all M interface nodes, so
+// alone, batched, served and subsampled results have the same sums.
+int fp64_chunk(const mesh_sdd_ctx *ctx, int32_t M, int64_t N)
 {
     const int64_t waves = (int64_t)ctx->cu_count * (msdd::kTableBlock / 64);
-    return (int64_t)Ms * ((N + 63) / 64) <= 32 * waves ? 64 : msdd::kFp64Block;
+    return (int64_t)M * ((N + 63) / 64) <= 32 * waves ? 64 : msdd::kFp64Block;
 }
 
 // Allocate the request's device buffers, stage its inputs and run the prep
@@ -631,7 +631,7 @@ int stage_request(Request &r, const mesh_sdd_step *dev_step, Arena *arena = null
     }
     const int Ms = r.ss->Ms;
 
-    if (fp64) r.chunk_paths = fp64_chunk(ctx, Ms, r.N);
+    if (fp64) r.chunk_paths = fp64_chunk(ctx, M, r.N);
     const uint32_t chunks = (uint32_t)((r.N + r.chunk_paths - 1) / r.chunk_paths);
     r.chunks_per_node = chunks;
     const size_t n_part = (size_t)Ms * chunks;
