@@ -206,8 +206,9 @@ typedef struct {
                                         paths inside, at more window refills         */
     int32_t job_split;               /* windowed kernel: a job holds at most 1/job_split
                                         of a workgroup's share of the launch's items
-                                        (1..4096; default 32, and 256 on grids cut
-                                        into several two-field windows)              */
+                                        (1..4096; default 6, and 256 on grids cut
+                                        into several two-field windows); the last
+                                        jobs of a launch are smaller                 */
 } mesh_sdd_launch;
 
 /* ---- context ------------------------------------------------------------ */

@@ -274,6 +274,14 @@ int validate_step(const mesh_sdd &inst, const mesh_sdd_step *s, int64_t *N_out)
 // ---------------------------------------------------------------------------
 // Launch shape
 // ---------------------------------------------------------------------------
+// Default job_split.  Every job ends with its waves waiting for the last of
+// them and starts with a window refill, so jobs are large, and JobSizer makes
+// the last ones small: 1/6 of a workgroup's share (257^2 front, N = 10^5:
+// 403.5 ms; 1/16 404.9, 1/32 409.8; before the last jobs were cut, 1/32 was
+// the best, 411.2).  In a block of a grid cut into two-field windows 1/256:
+// smaller jobs keep the blocks an XCD runs at one time within its L2.
+constexpr int kJobSplit = 6, kJobSplit0 = 256;
+
 mesh_sdd_launch default_launch()
 {
     mesh_sdd_launch l{};
@@ -292,7 +300,7 @@ mesh_sdd_launch default_launch()
     l.max_quarters = 16;
     l.window_kind = 0;     // automatic: see window_kind()
     l.window_margin = 0;   // the kind's default margin
-    l.job_split = 0;       // 32, and 256 in grids cut into several two-field windows
+    l.job_split = 0;       // kJobSplit, and kJobSplit0 in grids cut into several two-field windows
     return l;
 }
 
@@ -774,6 +782,36 @@ void cut_queues(const std::vector<msdd::WinJob> &jobs, Weight weight, msdd::JobQ
 // the first items spread over all CUs.  All of them where an item is shorter
 // than 16 substeps of the wave: the counter, one address for all XCDs, gives
 // out an item every 10 ns or so, which 4096 waves with such items outrun.  In
+// Sizes the jobs of a windowed launch towards the end of each queue: a job
+// takes at most a third of an equal share of what is left in its queue (32
+// items at least, two for each wave of the workgroup), so that the workgroups
+// of an XCD end together.  513^2 bump, N = 10^4: 204.5 -> 194.0 ms (its jobs of
+// 1/8 of a workgroup's share are 580 items, 17 ms); half or a sixth of the
+// share: 199.6, 196; 16 items at least: the batched mix at small path counts
+// 1 to 2 % slower.  The no-allocation solve, whose scratch holds jobs of 64
+// items, takes every job at its full size.
+struct JobSizer {
+    double queue, done = 0.0;   // work of one queue; work of the jobs so far
+    double groups;              // workgroups per queue
+    bool full;
+    JobSizer(double total, size_t share, bool full_size)
+        : queue(total / msdd::kJobQueues), groups((double)share / msdd::kJobQueues), full(full_size)
+    {
+    }
+    // items of the next job: at most jmax and `left`, each of `item` work
+    size_t next(size_t jmax, size_t left, double item)
+    {
+        size_t n = std::min(jmax, left);
+        if (!full && queue > 0.0) {
+            const double at = done / queue;
+            const double rest = (1.0 - (at - std::floor(at))) * queue / (3.0 * groups * item);
+            if ((double)n > rest) n = std::min(left, std::max<size_t>(32, (size_t)rest));
+        }
+        done += (double)n * item;
+        return n;
+    }
+};
+
 // between, all but the last two rounds.
 uint32_t static_rounds(size_t n_items, uint32_t waves, int chunk_paths, int K)
 {
@@ -826,20 +864,18 @@ int run_fp32_launch(mesh_sdd_ctx *ctx, const std::vector<InstView> &views, const
     if (level > 0 && ends_b.reserve((size_t)end_waves * 6u * cap * sizeof(float)))
         return fail(MESH_SDD_E_NOMEM, "device allocation of the end-state buffer failed");
     // windowed launch: one job per (range, grid block), split so that no job
-    // holds more than 1/job_split of a workgroup's share of the items (by
-    // default 1/32, and 1/256 in a block of a grid cut into two-field
-    // windows: measured on the batched mix, whose 513^2 grids then run 5 %
-    // faster; whole-grid windows are refilled for every job, and three-field
-    // windows lose with smaller jobs), in block order, cut into per-XCD
-    // queues of equal nominal work
+    // holds more than 1/job_split of a workgroup's share of the items, in
+    // block order, cut into per-XCD queues of equal nominal work
     std::vector<msdd::WinJob> jobs;
     msdd::JobQueues qs{};
     size_t win_lds = 32;
     int kind = -2;
     if (level == 3) {
         const size_t share = ((size_t)ctx->cu_count * (size_t)per_cu);
-        const size_t split = l.job_split > 0 ? (size_t)l.job_split : 32u;
-        const size_t split0 = l.job_split > 0 ? (size_t)l.job_split : 256u;
+        const size_t split = l.job_split > 0 ? (size_t)l.job_split : kJobSplit;
+        const size_t split0 = l.job_split > 0 ? (size_t)l.job_split : kJobSplit0;
+        // (at least 64 items, four for each wave, as a workgroup's waves wait
+        // for the last of them at the end of a job)
         const size_t jmax = std::max<size_t>(64, (n_items + share * split - 1) / (share * split));
         const size_t jmax0 = std::max<size_t>(64, (n_items + share * split0 - 1) / (share * split0));
         for (size_t ri = 0; ri < ranges.size(); ++ri) {
@@ -852,10 +888,11 @@ int run_fp32_launch(mesh_sdd_ctx *ctx, const std::vector<InstView> &views, const
                 const size_t qa = std::max(lo, (size_t)b.pos_begin * w.chunks);
                 const size_t qb = std::min(hi, (size_t)b.pos_end * w.chunks);
                 const bool blocked0 = b.kind == 0 && (b.tw < v.n_xi || b.th < v.n_eta);
-                const size_t jm = blocked0 ? jmax0 : jmax;
-                for (size_t q = qa; q < qb; q += jm)
-                    jobs.push_back(msdd::WinJob{(uint32_t)ri, (uint32_t)q, (uint32_t)std::min(jm, qb - q), b.i0,
-                                                b.j0, b.tw, b.th, (uint32_t)b.kind});
+                for (size_t q = qa, n; q < qb; q += n) {
+                    n = sizer.next(blocked0 ? jmax0 : jmax, qb - q, item);
+                    jobs.push_back(msdd::WinJob{(uint32_t)ri, (uint32_t)q, (uint32_t)n, b.i0, b.j0, b.tw, b.th,
+                                                (uint32_t)b.kind});
+                }
                 if (qa < qb) win_lds = std::max(win_lds, window_bytes(b.kind, b.tw, b.th));
             }
         }
@@ -863,12 +900,16 @@ int run_fp32_launch(mesh_sdd_ctx *ctx, const std::vector<InstView> &views, const
             const WorkRange &w = ranges[j.range];
             return (double)j.count * w.chunk_paths * views[w.inst].K;
         }, qs);
+        double total = 0.0;
+        for (const WorkRange &w : ranges) total += (double)w.count * w.chunk_paths * views[w.inst].K;
+        JobSizer sizer(total, share, arena != nullptr);
         if (jobs_b.reserve(std::max<size_t>(1, jobs.size()) * sizeof(msdd::WinJob)))
             return fail(MESH_SDD_E_NOMEM, "device allocation of the job list failed");
         if (!jobs.empty())
             HIP_TRY(hipMemcpyAsync(jobs_b.p, jobs.data(), jobs.size() * sizeof(msdd::WinJob),
                                    hipMemcpyHostToDevice, st));
     }
+            const double item = (double)w.chunk_paths * v.K;
     TimerEvents ev;
     HIP_TRY(ev.create());
     HIP_TRY(hipEventRecord(ev.e0, st));
@@ -932,12 +973,14 @@ int run_fp64_launch(mesh_sdd_ctx *ctx, Request &r, double *ms, Arena *arena = nu
         // windows: one job per grid block, cut so that every workgroup gets
         // about 32 of them (at least two items for each of its waves)
         std::vector<msdd::WinJob> jobs;
-        const size_t jmax = std::max<size_t>(32, v.n_items / ((size_t)ctx->cu_count * 32) + 1);
+        const size_t jmax = std::max<size_t>(64, v.n_items / ((size_t)ctx->cu_count * 32) + 1);
+        JobSizer sizer((double)v.n_items, (size_t)ctx->cu_count, false);
         for (const BlockRun &b : r.ss->blocks) {
             const size_t qa = (size_t)b.pos_begin * r.chunks_per_node, qb = (size_t)b.pos_end * r.chunks_per_node;
-            for (size_t q = qa; q < qb; q += jmax)
-                jobs.push_back(msdd::WinJob{0u, (uint32_t)q, (uint32_t)std::min(jmax, qb - q), b.i0, b.j0, b.tw, b.th,
-                                            (uint32_t)b.kind});
+            for (size_t q = qa, n; q < qb; q += n) {
+                n = sizer.next(jmax, qb - q, 1.0);
+                jobs.push_back(msdd::WinJob{0u, (uint32_t)q, (uint32_t)n, b.i0, b.j0, b.tw, b.th, (uint32_t)b.kind});
+            }
         }
         cut_queues(jobs, [](const msdd::WinJob &j) { return (double)j.count; }, v.qs);
         v.mode = 2;
@@ -1565,7 +1608,7 @@ try {
     if (out->job_split == 0) {
         int wx = 0, wy = 0;
         window_dims(lay.kind, inst->d.n_xi, inst->d.n_eta, &wx, &wy);
-        out->job_split = lay.kind == 0 && (wx < inst->d.n_xi || wy < inst->d.n_eta) ? 256 : 32;
+        out->job_split = lay.kind == 0 && (wx < inst->d.n_xi || wy < inst->d.n_eta) ? kJobSplit0 : kJobSplit;
     }
     return MESH_SDD_OK;
 } catch (...) {
