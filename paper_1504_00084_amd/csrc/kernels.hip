@@ -672,12 +672,20 @@ __device__ __forceinline__ void finish_item(const float *buf, uint32_t cap, uint
 }
 
 // Item sources of the persistent kernels.  QueueSrc: the launch-wide queue,
-// one atomic per item, decoded through the launch's range table.
+// decoded through the launch's range table.  A wave's first `rounds` items
+// are those of its number (wave, wave + waves, ...; numbered across the
+// workgroups, so that a launch with fewer items than waves spreads over all
+// CUs), the later ones come from the counter, one atomic per item.
 struct QueueSrc {
     uint32_t *head;
     const GLOBAL WorkRange *rg;
     uint32_t n_ranges;
-    __device__ __forceinline__ uint32_t pop(int lane) { return pop_item(head, lane); }
+    uint32_t wave, waves, rounds, taken;
+    __device__ __forceinline__ uint32_t pop(int lane)
+    {
+        if (taken < rounds) return wave + waves * taken++;
+        return rounds * waves + pop_item(head, lane);
+    }
     __device__ __forceinline__ ItemF decode(uint32_t it) const { return decode_item(rg, n_ranges, it); }
 };
 
@@ -898,7 +906,8 @@ __global__ __launch_bounds__(BLOCK) void paths_fp32(const InstView *__restrict__
         __syncthreads();
     }
 
-    QueueSrc src{head, gptr(ranges), n_ranges};
+    QueueSrc src{head, gptr(ranges), n_ranges, __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * gridDim.x + blockIdx.x,
+                 gridDim.x * (uint32_t)(BLOCK / 64), insts[0].static_rounds, 0u};
     const Win none{0, 0, 0, 0, 0, 0};
     item_loop<TAB, PER>(src, n_items, insts, buf, cap, tab, none, lane, rf);
 }

@@ -65,7 +65,8 @@ struct InstView {
     int32_t K;                    // substeps
     int32_t bridge;               // Brownian-bridge test: 0 off, 1 on, 2 on with substeps up to 4e-3
     int32_t M;                    // nodes that run paths (entries of node_i / node_j / node_r)
-    int32_t pad0;
+    uint32_t static_rounds;       // instance 0 of a launch without jobs: items that a wave takes by its
+                                  // number before it uses the launch's counter
     uint32_t key0, key1;          // Philox key (seed low / high word)
     uint32_t ctr3;                // instance_id << 16 | mesh_step & 0xffff
     uint32_t rec0;                // byte offset of `cells` from `coef_y` (one allocation)
@@ -116,7 +117,6 @@ struct InstView {
 struct Fp64View : InstView {
     uint32_t n_items;        // (node, chunk) items, node-major; item q writes partial q
     uint32_t chunk_paths;    // paths per full chunk
-    uint32_t static_rounds;  // items that a wave takes by its number before it uses the counter
     uint32_t grid;           // workgroups
     int32_t mode;            // 0: rho from global memory, 1: whole table in LDS, 2: windows (jobs)
     uint32_t *head;          // kJobQueues counters

@@ -394,6 +394,22 @@ size_t request_bytes(const mesh_sdd &inst, int64_t N, int chunk, int32_t Ms)
            (size_t)inst.M * 5 * sizeof(double) + sizeof(InstView) + 64;
 }
 
+// Paths per item of an FP32 request: the launch shape's chunk, halved (down to
+// 64, one path per lane) while the request has fewer than 8 items for every
+// wave of the device, so that its paths spread over all waves and the last
+// items are short: 33^2 bump, N = 10^4 (1240 items of 256 on 4096 waves) 1.22 ->
+// 0.54 ms; above 8 items per wave the larger chunk is as fast.  Counted over
+// all M interface nodes, whatever the sampling stride: a function of the
+// instance, its bucket's shape and N, so alone, batched, served and subsampled
+// results have the same sums.  The partials grow by 3 MB at most (the end
+// states of a launch shrink by more).
+int small_chunk(const mesh_sdd_ctx *ctx, int32_t M, int64_t N, int chunk)
+{
+    const int64_t waves = (int64_t)ctx->cu_count * (msdd::kTableBlock / 64);
+    while (chunk > 64 && (int64_t)M * ((N + chunk - 1) / chunk) < 8 * waves) chunk = std::max(64, chunk / 128 * 64);
+    return chunk;
+}
+
 // Snapshot host inputs (the caller may free them once submit returns).
 std::shared_ptr<Request> make_request(mesh_sdd *inst, const mesh_sdd_step &s, int64_t N)
 {
@@ -404,8 +420,9 @@ std::shared_ptr<Request> make_request(mesh_sdd *inst, const mesh_sdd_step &s, in
     r->Ms = r->stride > 1 ? (int32_t)sampled_ranks(*inst, r->stride).size() : inst->M;
     r->N = N;
     r->mesh_step = s.mesh_step;
-    r->chunk_paths = std::max(64, launch_for(inst->ctx, inst->d).chunk_paths / 64 * 64);
-    r->cost_bytes = request_bytes(*inst, N, r->chunk_paths, r->Ms);
+    r->tuned_chunk = std::max(64, launch_for(inst->ctx, inst->d).chunk_paths / 64 * 64);
+    r->chunk_paths = small_chunk(inst->ctx, inst->M, N, r->tuned_chunk);
+    r->cost_bytes = request_bytes(*inst, N, r->tuned_chunk, r->Ms);
     const size_t n = (size_t)inst->d.n_xi * inst->d.n_eta;
     const size_t nb = 4 * (size_t)inst->d.n_eta + 4 * (size_t)inst->d.n_xi;
     if (!s.inputs_on_device) {
@@ -643,11 +660,12 @@ int stage_request(Request &r, const mesh_sdd_step *dev_step, Arena *arena = null
     const uint32_t chunks = (uint32_t)((r.N + r.chunk_paths - 1) / r.chunk_paths);
     r.chunks_per_node = chunks;
     const size_t n_part = (size_t)Ms * chunks;
+    r.limit_items = (size_t)Ms * (size_t)((r.N + r.tuned_chunk - 1) / r.tuned_chunk);
     // the kernels number (node, chunk) items and partials in 32 bits; FP64
     // requests end at 2^24 items of 256 paths
-    if (!fp64 && n_part > (size_t)kMaxLaunchItems)
+    if (!fp64 && r.limit_items > (size_t)kMaxLaunchItems)
         return fail(MESH_SDD_E_INVAL, "%zu (node, chunk) work items, more than 2^32 - 2^20 (fewer paths per node or "
-                    "an interface stride)", n_part);
+                    "an interface stride)", r.limit_items);
     if (fp64 && n_part >= ((size_t)1 << 32) / msdd::kFp64Block)
         return fail(MESH_SDD_E_INVAL, "FP64: %zu (node, block) pairs, at least 2^24 (fewer paths per node or an "
                     "interface stride)", n_part);
@@ -764,24 +782,6 @@ void release_request_buffers(Request &r)
         b->release();
 }
 
-// Cuts a job list, in order, into the per-XCD queues of about equal weight.
-template <class Weight>
-void cut_queues(const std::vector<msdd::WinJob> &jobs, Weight weight, msdd::JobQueues &qs)
-{
-    std::vector<double> cum(jobs.size() + 1, 0.0);
-    for (size_t k = 0; k < jobs.size(); ++k) cum[k + 1] = cum[k] + weight(jobs[k]);
-    for (int q = 0, k = 0; q <= msdd::kJobQueues; ++q) {
-        const double goal = cum.back() * q / msdd::kJobQueues;
-        while (q == msdd::kJobQueues ? k < (int)jobs.size() : (k < (int)jobs.size() && cum[k] < goal)) ++k;
-        qs.b[q] = (uint32_t)k;
-    }
-}
-
-// Items that each wave of a persistent launch takes by its number (one per
-// round over the waves) before it uses the launch's counter.  One, so that
-// the first items spread over all CUs.  All of them where an item is shorter
-// than 16 substeps of the wave: the counter, one address for all XCDs, gives
-// out an item every 10 ns or so, which 4096 waves with such items outrun.  In
 // Sizes the jobs of a windowed launch towards the end of each queue: a job
 // takes at most a third of an equal share of what is left in its queue (32
 // items at least, two for each wave of the workgroup), so that the workgroups
@@ -812,7 +812,26 @@ struct JobSizer {
     }
 };
 
-// between, all but the last two rounds.
+// Cuts a job list, in order, into the per-XCD queues of about equal weight.
+template <class Weight>
+void cut_queues(const std::vector<msdd::WinJob> &jobs, Weight weight, msdd::JobQueues &qs)
+{
+    std::vector<double> cum(jobs.size() + 1, 0.0);
+    for (size_t k = 0; k < jobs.size(); ++k) cum[k + 1] = cum[k] + weight(jobs[k]);
+    for (int q = 0, k = 0; q <= msdd::kJobQueues; ++q) {
+        const double goal = cum.back() * q / msdd::kJobQueues;
+        while (q == msdd::kJobQueues ? k < (int)jobs.size() : (k < (int)jobs.size() && cum[k] < goal)) ++k;
+        qs.b[q] = (uint32_t)k;
+    }
+}
+
+// Items that each wave of a persistent launch takes by its number (one per
+// round over the waves) before it uses the launch's counter.  One, so that
+// the first items spread over all CUs.  All of them where an item is shorter
+// than 16 substeps of the wave: the counter, one address for all XCDs, gives
+// out an item every 10 ns or so, which 4096 waves with such items outrun (five
+// rings, 41^2, one substep, N = 10^4: 200 us from the counter, 80 by number).
+// In between, all but the last two rounds.
 uint32_t static_rounds(size_t n_items, uint32_t waves, int chunk_paths, int K)
 {
     const size_t rounds = (n_items + waves - 1) / waves;
@@ -825,7 +844,7 @@ uint32_t static_rounds(size_t n_items, uint32_t waves, int chunk_paths, int K)
 // One persistent FP32 launch over the items described by `ranges` (their
 // inst fields index `views`).  Caller holds gpu_mu.  Returns the device time
 // in ms via *ms.
-int run_fp32_launch(mesh_sdd_ctx *ctx, const std::vector<InstView> &views, const std::vector<WorkRange> &ranges,
+int run_fp32_launch(mesh_sdd_ctx *ctx, std::vector<InstView> &views, const std::vector<WorkRange> &ranges,
                     const std::vector<const SampleSet *> &sets, const mesh_sdd_launch &l, double *ms,
                     Arena *arena = nullptr)
 {
@@ -849,8 +868,6 @@ int run_fp32_launch(mesh_sdd_ctx *ctx, const std::vector<InstView> &views, const
     if (views_b.reserve(views.size() * sizeof(InstView)) ||
         ranges_b.reserve(ranges.size() * sizeof(WorkRange)) || head_b.reserve(64))
         return fail(MESH_SDD_E_NOMEM, "device allocation for the work queue failed");
-    HIP_TRY(hipMemcpyAsync(views_b.p, views.data(), views.size() * sizeof(InstView), hipMemcpyHostToDevice, st));
-    HIP_TRY(hipMemcpyAsync(ranges_b.p, ranges.data(), ranges.size() * sizeof(WorkRange), hipMemcpyHostToDevice, st));
     // A launch that holds one instance whose node tables of rho and dt rho_xi
     // fit the LDS stages them whole (1024-thread workgroups); any other
     // launch stages windows of them, job by job; the waves then keep their
@@ -863,6 +880,10 @@ int run_fp32_launch(mesh_sdd_ctx *ctx, const std::vector<InstView> &views, const
     const uint32_t end_waves = (uint32_t)table_grid * (uint32_t)(msdd::kTableBlock / 64);
     if (level > 0 && ends_b.reserve((size_t)end_waves * 6u * cap * sizeof(float)))
         return fail(MESH_SDD_E_NOMEM, "device allocation of the end-state buffer failed");
+    if (level == 2)
+        views[0].static_rounds = static_rounds(n_items, end_waves, (int)ranges[0].chunk_paths, views[0].K);
+    HIP_TRY(hipMemcpyAsync(views_b.p, views.data(), views.size() * sizeof(InstView), hipMemcpyHostToDevice, st));
+    HIP_TRY(hipMemcpyAsync(ranges_b.p, ranges.data(), ranges.size() * sizeof(WorkRange), hipMemcpyHostToDevice, st));
     // windowed launch: one job per (range, grid block), split so that no job
     // holds more than 1/job_split of a workgroup's share of the items, in
     // block order, cut into per-XCD queues of equal nominal work
@@ -878,12 +899,16 @@ int run_fp32_launch(mesh_sdd_ctx *ctx, const std::vector<InstView> &views, const
         // for the last of them at the end of a job)
         const size_t jmax = std::max<size_t>(64, (n_items + share * split - 1) / (share * split));
         const size_t jmax0 = std::max<size_t>(64, (n_items + share * split0 - 1) / (share * split0));
+        double total = 0.0;
+        for (const WorkRange &w : ranges) total += (double)w.count * w.chunk_paths * views[w.inst].K;
+        JobSizer sizer(total, share, arena != nullptr);
         for (size_t ri = 0; ri < ranges.size(); ++ri) {
             const WorkRange &w = ranges[ri];
             const InstView &v = views[w.inst];
             const int p = msdd::path_kind(v);
             kind = kind == -2 || kind == p ? p : -1;
             const size_t lo = w.first, hi = (size_t)w.first + w.count;
+            const double item = (double)w.chunk_paths * v.K;
             for (const BlockRun &b : sets[w.inst]->blocks) {
                 const size_t qa = std::max(lo, (size_t)b.pos_begin * w.chunks);
                 const size_t qb = std::min(hi, (size_t)b.pos_end * w.chunks);
@@ -900,16 +925,12 @@ int run_fp32_launch(mesh_sdd_ctx *ctx, const std::vector<InstView> &views, const
             const WorkRange &w = ranges[j.range];
             return (double)j.count * w.chunk_paths * views[w.inst].K;
         }, qs);
-        double total = 0.0;
-        for (const WorkRange &w : ranges) total += (double)w.count * w.chunk_paths * views[w.inst].K;
-        JobSizer sizer(total, share, arena != nullptr);
         if (jobs_b.reserve(std::max<size_t>(1, jobs.size()) * sizeof(msdd::WinJob)))
             return fail(MESH_SDD_E_NOMEM, "device allocation of the job list failed");
         if (!jobs.empty())
             HIP_TRY(hipMemcpyAsync(jobs_b.p, jobs.data(), jobs.size() * sizeof(msdd::WinJob),
                                    hipMemcpyHostToDevice, st));
     }
-            const double item = (double)w.chunk_paths * v.K;
     TimerEvents ev;
     HIP_TRY(ev.create());
     HIP_TRY(hipEventRecord(ev.e0, st));
@@ -1093,7 +1114,7 @@ int run_blocking(mesh_sdd_ctx *ctx, std::vector<std::shared_ptr<Request>> &reqs,
     std::vector<WorkRange> ranges;
     std::vector<const SampleSet *> sets;
     std::vector<size_t> fp32_reqs;
-    size_t base = 0;
+    size_t base = 0, limit = 0;   // items gathered, and in chunks of the tuned size
     // one persistent launch over the FP32 requests gathered so far: the
     // bucket's shape for a launch of one instance, the multi-instance shape
     // otherwise
@@ -1114,7 +1135,7 @@ int run_blocking(mesh_sdd_ctx *ctx, std::vector<std::shared_ptr<Request>> &reqs,
         ranges.clear();
         sets.clear();
         fp32_reqs.clear();
-        base = 0;
+        base = limit = 0;
     };
     for (size_t q = 0; q < reqs.size(); ++q) {
         Request &r = *reqs[q];
@@ -1135,7 +1156,8 @@ int run_blocking(mesh_sdd_ctx *ctx, std::vector<std::shared_ptr<Request>> &reqs,
             // a launch numbers its items in 32 bits: start another one first
             // where this request's items would not fit (every request fits
             // alone, stage_request checks it)
-            if (base + r.n_items > (size_t)kMaxLaunchItems) launch_group();
+            if (limit + r.limit_items > (size_t)kMaxLaunchItems || base + r.n_items > 0xFFF00000u) launch_group();
+            limit += r.limit_items;
             const uint32_t slot = (uint32_t)views.size();
             views.push_back(r.v);
             sets.push_back(r.ss);
@@ -1887,7 +1909,7 @@ try {
     const size_t n = (size_t)d.n_xi * d.n_eta, np = (size_t)(d.n_xi + 2) * (d.n_eta + 2);
     const size_t nb = 4 * (size_t)d.n_eta + 4 * (size_t)d.n_xi;
     const size_t chunks = fp64 ? (size_t)((N + msdd::kFp64Block - 1) / msdd::kFp64Block)
-                               : (size_t)((N + r->chunk_paths - 1) / r->chunk_paths);
+                               : (size_t)((N + r->tuned_chunk - 1) / r->tuned_chunk);
     const size_t n_items = (size_t)r->Ms * chunks;
     auto piece = [](size_t b) { return b == 0 ? (size_t)256 : round_up(b, 256); };
     size_t need = 2 * piece(n * 8) + 2 * piece(nb * 8) + 2 * piece(np * 8) + 2 * piece(np * 4) + 2 * piece(nb * 4) +
@@ -1897,7 +1919,7 @@ try {
         const mesh_sdd_launch l = launch_for(ctx, d);
         int per_cu = 0;
         const int level = table_level((int)n, l.monitor_table, &per_cu);
-        const size_t cap = (size_t)(r->chunk_paths + 63) / 64 * 64;
+        const size_t cap = (size_t)(r->tuned_chunk + 63) / 64 * 64;
         need += piece(sizeof(InstView)) + piece(sizeof(WorkRange)) + piece(64);
         if (level > 0) need += piece((size_t)ctx->cu_count * per_cu * (msdd::kTableBlock / 64) * 6 * cap * 4);
         size_t nb_max = 0;   // the most blocks of any layout of the stride

@@ -276,7 +276,8 @@ struct Request {
     const SampleSet *ss = nullptr; // set by stage_request
     int64_t N = 0;
     uint32_t mesh_step = 0;
-    int chunk_paths = 0;
+    int chunk_paths = 0;           // paths per item
+    int tuned_chunk = 0;           // the launch shape's; chunk_paths is smaller in small requests
     // host snapshots of host inputs
     std::vector<double> hx, hy, hb0, hb1;
     // device buffers owned by the request
@@ -284,6 +285,7 @@ struct Request {
     DevBuf view, partials, spans, out, steps_total;
     InstView v{};
     size_t n_items = 0;            // FP32 work items (node-major, see WorkRange)
+    size_t limit_items = 0;        // the same in chunks of the tuned size (what the launch limits count)
     size_t next_item = 0;          // first item not yet handed to a tick
     size_t done_items = 0;
     uint32_t chunks_per_node = 0;
