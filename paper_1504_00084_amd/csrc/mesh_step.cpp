@@ -191,26 +191,34 @@ int solve_dev(mesh_sdd *inst, const MpOpts &o, const double *x0, const double *y
     const bool fits = msdd::subdomain_fits_lds(a.P_xi, a.P_eta);
     if (with_interfaces && o.solver == 1 && !fits)
         return fail(MESH_SDD_E_INVAL, "a %dx%d subdomain does not fit in LDS", a.P_xi + 1, a.P_eta + 1);
-    if (with_interfaces && o.solver != 2 && fits) {
+    if (with_interfaces && o.solver != 2 && fits && msdd::subdomain_shape(a.P_xi, a.P_eta).block) {
         HIP_TRY(msdd::launch_subdomain_lds(a, x_new, y_new, st));
         return MESH_SDD_OK;
     }
-    // whole-grid sweeps: x0 -> A -> B -> A ..., the last level copied out
+    // tiles of the grid, kTileRim substeps per launch: x0 -> A -> B -> A ...,
+    // the last launch into x_new.  With a periodic axis the first substep is
+    // a plain sweep: it alone reads the image nodes as the caller gave them
+    // (from then on they are node 0 plus the period).
     if (ax.alloc(n * 8) || ay.alloc(n * 8) || bx.alloc(n * 8) || by.alloc(n * 8))
         return fail(MESH_SDD_E_NOMEM, "device allocation for the mesh step failed");
     const double *cx = x0, *cy = y0;
     double *nx = ax.as<double>(), *ny = ay.as<double>();
     double *ox = bx.as<double>(), *oy = by.as<double>();
-    for (int l = 0; l < L; ++l) {
-        const double th1 = (double)(l + 1) / (double)L;
-        HIP_TRY(msdd::launch_fe_sweep(a, cx, cy, nx, ny, th1, st));
+    const bool wraps = !with_interfaces && (d.periodic_xi || d.periodic_eta);
+    for (int l = 0; l < L;) {
+        a.l0 = l;
+        a.steps = wraps && l == 0 ? 0 : std::min(msdd::kTileRim, L - l);
+        l += std::max(a.steps, 1);
+        if (l == L) {
+            nx = x_new;
+            ny = y_new;
+        }
+        HIP_TRY(msdd::launch_fe_sweep(a, cx, cy, nx, ny, (double)(a.l0 + 1) / (double)L, st));
         cx = nx;
         cy = ny;
         std::swap(nx, ox);
         std::swap(ny, oy);
     }
-    HIP_TRY(hipMemcpyAsync(x_new, cx, n * 8, hipMemcpyDeviceToDevice, st));
-    HIP_TRY(hipMemcpyAsync(y_new, cy, n * 8, hipMemcpyDeviceToDevice, st));
     return MESH_SDD_OK;
 }
 

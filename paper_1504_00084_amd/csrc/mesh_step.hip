@@ -7,9 +7,11 @@
 //   * subdomain_lds_kernel: the subdomain solves of section 3.5 (centred
 //     differences, forward Euler), one workgroup per subdomain with the
 //     subdomain's mesh resident in LDS for all substeps;
-//   * fe_sweep_kernel: one forward-Euler substep over the whole grid in
-//     global memory; used when a subdomain does not fit in LDS and for the
-//     single-domain reference (periodic axes wrap there);
+//   * fe_tile_kernel: several forward-Euler substeps over the whole grid in
+//     one launch, tile by tile in LDS; used when a subdomain does not fit one
+//     workgroup and for the single-domain reference (periodic axes wrap);
+//   * fe_sweep_kernel: one substep over the whole grid in global memory, the
+//     first of a periodic single domain (it reads the image nodes as given);
 //   * arclength kernels: the monitor rho = sqrt(1 + a |grad u|^2) from nodal u
 //     on the new mesh (section 3.6), the physical gradient through the
 //     inverse mesh Jacobian;
@@ -20,6 +22,8 @@
 // sequence of IEEE operations written below, in that order.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+
+#include <algorithm>
 
 #include "msdd_mesh_step.hpp"
 
@@ -40,6 +44,13 @@ __device__ __forceinline__ int side_offset(int side, int comp, int n_xi, int n_e
 // Workgroup k advances one side: sides 0, 1 (xi = 0, 1; y runs along eta)
 // when xi is a Dirichlet axis, sides 2, 3 (eta = 0, 1; x runs along xi)
 // when eta is.  LDS holds the two time levels and the drift coefficients.
+// P2: n - 1 is a power of two on every side, so the divisors h are, and the
+// divisions go into the coefficients exactly (as in fe_update).  Bound: the
+// chain of one substep (LDS read, update, LDS write, barrier), so one node
+// per thread up to 1024: 129 nodes, 1457 substeps 104 -> 51 us; 257 nodes,
+// periodic, 728 substeps 380 -> 175 us (256 threads took the last node in a
+// second round).
+template <bool P2>
 __global__ __launch_bounds__(kEdgeBlock) void edge_gen_kernel(const double *__restrict__ rho,
                                                              const double *__restrict__ rho_xi,
                                                              const double *__restrict__ rho_eta, int n_xi,
@@ -56,37 +67,55 @@ __global__ __launch_bounds__(kEdgeBlock) void edge_gen_kernel(const double *__re
     const double period = along_eta ? Ly : Lx;
     const int off = side_offset(side, along_eta ? 1 : 0, n_xi, n_eta);
     double *cur = sm, *nxt = sm + n, *bb = sm + 2 * n;
+    const double h = 1.0 / (double)(n - 1);
+    const double two_h = 2.0 * h, hh = h * h;
+    const double scale = P2 ? hh / two_h : 1.0;
+    const double dt = P2 ? tau / (double)L / hh : tau / (double)L;
     for (int s = threadIdx.x; s < n; s += blockDim.x) {
         const int g = along_eta ? s * n_xi + (side == 0 ? 0 : n_xi - 1) : (side == 2 ? 0 : n_eta - 1) * n_xi + s;
         cur[s] = bnd[off + s];
-        bb[s] = (along_eta ? rho_eta[g] : rho_xi[g]) / rho[g];
+        bb[s] = (along_eta ? rho_eta[g] : rho_xi[g]) / rho[g] * scale;
     }
     __syncthreads();
-    const double h = 1.0 / (double)(n - 1);
-    const double two_h = 2.0 * h, hh = h * h;
-    const double dt = tau / (double)L;
-    for (int l = 0; l < L; ++l) {
-        for (int s = threadIdx.x; s < n; s += blockDim.x) {
-            double v;
-            if (periodic) {
-                // node n-1 is the image of node 0: its update is node 0's plus the period
-                const int q = s == n - 1 ? 0 : s;
-                const double left = q > 0 ? cur[q - 1] : cur[n - 2] - period;
-                const double right = cur[q + 1];
-                v = cur[q] + dt * (bb[q] * (right - left) / two_h + (right - 2.0 * cur[q] + left) / hh);
-                if (s == n - 1) v = v + period;
-            } else if (s == 0 || s == n - 1) {
-                v = cur[s];
-            } else {
-                v = cur[s] + dt * (bb[s] * (cur[s + 1] - cur[s - 1]) / two_h +
-                                   (cur[s + 1] - 2.0 * cur[s] + cur[s - 1]) / hh);
-            }
-            nxt[s] = v;
+    auto update = [&](double b, double c, double left, double right) {
+        if (P2) return c + dt * (b * (right - left) + (__builtin_fma(-2.0, c, right) + left));
+        return c + dt * (b * (right - left) / two_h + (right - 2.0 * c + left) / hh);
+    };
+    // the value of node s one substep on; node n-1 of a periodic side is the
+    // image of node 0: its update is node 0's plus the period
+    auto next = [&](int s, double b, double c) {
+        if (periodic) {
+            const bool image = s == n - 1;
+            const int q = image ? 0 : s;
+            const double left = q > 0 ? cur[q - 1] : cur[n - 2] - period;
+            const double v = update(b, image ? cur[0] : c, left, cur[q + 1]);
+            return image ? v + period : v;
         }
-        __syncthreads();
-        double *t = cur;
-        cur = nxt;
-        nxt = t;
+        return s == 0 || s == n - 1 ? c : update(b, c, cur[s - 1], cur[s + 1]);
+    };
+    if (n <= (int)blockDim.x) {   // one node per thread, its value and coefficient in registers
+        const int s = threadIdx.x;
+        double c = s < n ? cur[s] : 0.0;
+        const double b = s < n ? bb[periodic && s == n - 1 ? 0 : s] : 0.0;
+        for (int l = 0; l < L; ++l) {
+            if (s < n) {
+                c = next(s, b, c);
+                nxt[s] = c;
+            }
+            __syncthreads();
+            double *t = cur;
+            cur = nxt;
+            nxt = t;
+        }
+    } else {
+        for (int l = 0; l < L; ++l) {
+            for (int s = threadIdx.x; s < n; s += blockDim.x)
+                nxt[s] = next(s, bb[periodic && s == n - 1 ? 0 : s], cur[s]);
+            __syncthreads();
+            double *t = cur;
+            cur = nxt;
+            nxt = t;
+        }
     }
     for (int s = threadIdx.x; s < n; s += blockDim.x) bnd[off + s] = cur[s];
 }
@@ -140,8 +169,10 @@ __global__ void targets_kernel(MeshStepArgs a, double *__restrict__ x_new, doubl
     const int i = g % a.n_xi, j = g / a.n_xi;
     const Target t = target_of(i, j, a);
     a.mask[g] = t.dirichlet ? 1 : 0;
-    a.tx1[g] = t.x;
-    a.ty1[g] = t.y;
+    // the drift coefficients of a node that is advanced take the place of its
+    // Dirichlet values, so no launch of the solve divides again
+    a.tx1[g] = t.dirichlet ? t.x : a.rho_xi[g] / a.rho[g];
+    a.ty1[g] = t.dirichlet ? t.y : a.rho_eta[g] / a.rho[g];
     if (t.dirichlet) {
         x_new[g] = t.x;
         y_new[g] = t.y;
@@ -149,113 +180,343 @@ __global__ void targets_kernel(MeshStepArgs a, double *__restrict__ x_new, doubl
 }
 
 // ---------------------------------------------------------------------------
+// The forward-Euler update
+// ---------------------------------------------------------------------------
+// One substep of a node, with the roundings of the plain expression
+//   c + dt (bx (e - w) / 2hx + by (n - s) / 2hy + (e - 2c + w) / hx^2 + (n - 2c + s) / hy^2).
+// P2: the cell counts of both axes are powers of two.  Every divisor is then a
+// power of two, which scales exactly, so the whole sum is taken in units of
+// 1 / hx^2 and the divisions go into bx, by and dt (13 operations and one for
+// hy != hx instead of 17 and four divisions); e - 2c is one rounding either
+// way.  Otherwise the divisions stay: bx, by are the plain coefficients.
+struct FeCoef {
+    double two_hx, two_hy, hxx, hyy, dt;   // P2: dt / hx^2 in dt, hx^2 / hy^2 in hyy
+    double sx, sy;                         // P2: scales of bx and by
+};
+
+template <bool P2>
+__device__ __forceinline__ FeCoef fe_coef(const MeshStepArgs &a)
+{
+    const double hx = 1.0 / (double)(a.n_xi - 1), hy = 1.0 / (double)(a.n_eta - 1);
+    FeCoef k;
+    k.two_hx = 2.0 * hx;
+    k.two_hy = 2.0 * hy;
+    k.hxx = hx * hx;
+    k.hyy = hy * hy;
+    k.dt = a.tau / (double)a.L;
+    k.sx = k.sy = 1.0;
+    if (P2) {
+        k.sx = k.hxx / k.two_hx;
+        k.sy = k.hxx / k.two_hy;
+        k.hyy = k.hxx / k.hyy;
+        k.dt = k.dt / k.hxx;
+    }
+    return k;
+}
+
+template <bool P2>
+__device__ __forceinline__ double fe_update(const FeCoef &k, double bx, double by, double c, double e, double w,
+                                            double n, double s)
+{
+    if (P2)
+        return c + k.dt * (bx * (e - w) + by * (n - s) + (__builtin_fma(-2.0, c, e) + w) +
+                           (__builtin_fma(-2.0, c, n) + s) * k.hyy);
+    return c + k.dt * (bx * (e - w) / k.two_hx + by * (n - s) / k.two_hy + (e - 2.0 * c + w) / k.hxx +
+                       (n - 2.0 * c + s) / k.hyy);
+}
+
+// ---------------------------------------------------------------------------
 // Subdomain solves with the subdomain resident in LDS
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(kSubBlock) void subdomain_lds_kernel(MeshStepArgs a, double *__restrict__ x_new,
+// One workgroup per subdomain, all substeps in one launch, two time levels in
+// LDS, one barrier per substep.  A thread owns R nodes of a column (its north
+// and south neighbours then are its own registers but for two), the last
+// segment of a column overlapping the one before it; the threads from
+// `first_bnd` on own a boundary node each.  Bound: LDS reads and FP64 issue of
+// one CU (33x33 box: 5 + 2 LDS values and 28 operations per node and
+// substep, about 420 clocks of each), then the barrier.  16 boxes of 33x33,
+// 729 substeps: 1.10 ms with a node per thread, four divisions per update and
+// two barriers, 0.43 ms now.
+template <bool P2, int R>
+__global__ __launch_bounds__(kSubBlock) void subdomain_lds_kernel(MeshStepArgs a, int first_bnd,
+                                                                  double *__restrict__ x_new,
                                                                   double *__restrict__ y_new)
 {
     extern __shared__ double sm[];
     const int bi = (int)blockIdx.x % a.sub_xi, bj = (int)blockIdx.x / a.sub_xi;
     const int Px = a.P_xi, Py = a.P_eta;
-    const int Bx = Px + 1, By = Py + 1;
+    const int Bx = Px + 1, By = Py + 1, n = Bx * By;
     const int i0 = bi * Px, j0 = bj * Py;
-    double *sx = sm, *sy = sm + Bx * By;
+    double *cur = sm, *nxt = sm + 2 * n;   // x, then y, of each level
     const int tid = threadIdx.x;
-    for (int q = tid; q < Bx * By; q += kSubBlock) {
+    for (int q = tid; q < n; q += blockDim.x) {
         const int g = (j0 + q / Bx) * a.n_xi + i0 + q % Bx;
-        sx[q] = a.x0[g];
-        sy[q] = a.y0[g];
+        cur[q] = a.x0[g];
+        cur[n + q] = a.y0[g];
     }
-    // interior nodes owned by this thread: q = tid + r * kSubBlock
-    const int nin = (Px - 1) * (Py - 1);
-    double bxr[kSubPerThread], byr[kSubPerThread];
-    int lq[kSubPerThread];
+    const FeCoef k = fe_coef<P2>(a);
+    const int segs = (Px - 1) * ((Py - 1 + R - 1) / R);
+    const bool inner = tid < segs;
+    int q0 = 0;   // first node of the segment, or the boundary node
+    double bx[R], by[R], x[R], y[R];
+    if (inner) {
+        const int ca = 1 + tid % (Px - 1), grp = tid / (Px - 1);
+        const int cc = min(1 + grp * R, Py - R);
+        q0 = cc * Bx + ca;
 #pragma unroll
-    for (int r = 0; r < kSubPerThread; ++r) {
-        const int q = tid + r * kSubBlock;
-        lq[r] = -1;
-        bxr[r] = 0.0;
-        byr[r] = 0.0;
-        if (q < nin) {
-            const int ca = 1 + q % (Px - 1), cc = 1 + q / (Px - 1);
-            const int g = (j0 + cc) * a.n_xi + i0 + ca;
-            lq[r] = cc * Bx + ca;
-            bxr[r] = a.rho_xi[g] / a.rho[g];
-            byr[r] = a.rho_eta[g] / a.rho[g];
+        for (int r = 0; r < R; ++r) {
+            const int g = (j0 + cc + r) * a.n_xi + i0 + ca;
+            bx[r] = a.tx1[g] * k.sx;
+            by[r] = a.ty1[g] * k.sy;
+            x[r] = a.x0[g];
+            y[r] = a.y0[g];
         }
     }
-    // boundary node of the box owned by this thread (at most one)
     const int nb = 2 * Bx + 2 * (By - 2);
-    int bq = -1;
+    const int tb = tid - first_bnd;
+    const bool edge = tb >= 0 && tb < nb;
     double bx0 = 0.0, by0 = 0.0, bx1 = 0.0, by1 = 0.0;
-    if (tid < nb) {
+    if (edge) {
         int ca, cc;
-        if (tid < Bx) {
-            ca = tid;
+        if (tb < Bx) {
+            ca = tb;
             cc = 0;
-        } else if (tid < 2 * Bx) {
-            ca = tid - Bx;
+        } else if (tb < 2 * Bx) {
+            ca = tb - Bx;
             cc = By - 1;
-        } else if (tid < 2 * Bx + By - 2) {
+        } else if (tb < 2 * Bx + By - 2) {
             ca = 0;
-            cc = 1 + tid - 2 * Bx;
+            cc = 1 + tb - 2 * Bx;
         } else {
             ca = Bx - 1;
-            cc = 1 + tid - 2 * Bx - (By - 2);
+            cc = 1 + tb - 2 * Bx - (By - 2);
         }
         const int g = (j0 + cc) * a.n_xi + i0 + ca;
-        bq = cc * Bx + ca;
+        q0 = cc * Bx + ca;
         bx0 = a.x0[g];
         by0 = a.y0[g];
         bx1 = a.tx1[g];
         by1 = a.ty1[g];
     }
-    const double hx = 1.0 / (double)(a.n_xi - 1), hy = 1.0 / (double)(a.n_eta - 1);
-    const double two_hx = 2.0 * hx, two_hy = 2.0 * hy, hxx = hx * hx, hyy = hy * hy;
-    const double dt = a.tau / (double)a.L;
     __syncthreads();
-    double nxr[kSubPerThread], nyr[kSubPerThread];
     for (int l = 0; l < a.L; ++l) {
-        const double th1 = (double)(l + 1) / (double)a.L;
+        if (inner) {
+            const double *px = cur + q0, *py = px + n;
+            double e[R], w[R];
 #pragma unroll
-        for (int r = 0; r < kSubPerThread; ++r) {
-            nxr[r] = 0.0;
-            nyr[r] = 0.0;
-            if (lq[r] >= 0) {
-                const int q = lq[r];
-                {
-                    const double c = sx[q], e = sx[q + 1], w = sx[q - 1], n = sx[q + Bx], s = sx[q - Bx];
-                    nxr[r] = c + dt * (bxr[r] * (e - w) / two_hx + byr[r] * (n - s) / two_hy +
-                                       (e - 2.0 * c + w) / hxx + (n - 2.0 * c + s) / hyy);
-                }
-                {
-                    const double c = sy[q], e = sy[q + 1], w = sy[q - 1], n = sy[q + Bx], s = sy[q - Bx];
-                    nyr[r] = c + dt * (bxr[r] * (e - w) / two_hx + byr[r] * (n - s) / two_hy +
-                                       (e - 2.0 * c + w) / hxx + (n - 2.0 * c + s) / hyy);
-                }
+            for (int r = 0; r < R; ++r) {
+                e[r] = px[r * Bx + 1];
+                w[r] = px[r * Bx - 1];
             }
+            double below = px[-Bx];
+            const double above = px[R * Bx];
+            double e2[R], w2[R];
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                e2[r] = py[r * Bx + 1];
+                w2[r] = py[r * Bx - 1];
+            }
+            double below2 = py[-Bx];
+            const double above2 = py[R * Bx];
+            double *ox = nxt + q0, *oy = ox + n;
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const double v = fe_update<P2>(k, bx[r], by[r], x[r], e[r], w[r], r + 1 < R ? x[r + 1] : above, below);
+                below = x[r];
+                x[r] = v;
+                ox[r * Bx] = v;
+            }
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const double v =
+                    fe_update<P2>(k, bx[r], by[r], y[r], e2[r], w2[r], r + 1 < R ? y[r + 1] : above2, below2);
+                below2 = y[r];
+                y[r] = v;
+                oy[r * Bx] = v;
+            }
+        }
+        if (edge) {
+            const double th1 = (double)(l + 1) / (double)a.L;
+            nxt[q0] = (1.0 - th1) * bx0 + th1 * bx1;
+            nxt[n + q0] = (1.0 - th1) * by0 + th1 * by1;
         }
         __syncthreads();
+        double *t = cur;
+        cur = nxt;
+        nxt = t;
+    }
+    if (inner) {
 #pragma unroll
-        for (int r = 0; r < kSubPerThread; ++r) {
-            if (lq[r] >= 0) {
-                sx[lq[r]] = nxr[r];
-                sy[lq[r]] = nyr[r];
+        for (int r = 0; r < R; ++r) {
+            const int q = q0 + r * Bx;
+            const int g = (j0 + q / Bx) * a.n_xi + i0 + q % Bx;
+            x_new[g] = x[r];
+            y_new[g] = y[r];
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Several substeps of the whole grid in one launch
+// ---------------------------------------------------------------------------
+// For boxes (subdomains, or the single domain) that one workgroup does not
+// hold.  A workgroup advances a tile of kTileCore^2 nodes by a.steps substeps
+// in LDS, with a rim of kTileRim nodes on each side, of which each substep
+// uses up one: the nodes of the rim are computed again by the neighbours,
+// and no workgroup waits for another.  Beyond a Dirichlet side of the box
+// there is nothing to compute, so the rim ends there; Dirichlet nodes follow
+// their line in time by themselves.  On a periodic axis (PER; the single
+// domain) the rim goes round: nodes are held by their index 0 .. n-2, and a
+// neighbour across the seam is the node there plus or minus the period, the
+// rounding of which is that of the stored image.
+// A thread owns kTileRows nodes of a column.  Bound: the launch and the loads
+// of a tile (about 5 us) and the FP64 issue of its 32 x 32 nodes (0.4 us a
+// substep).  Cores of 16 with a rim of 8 and two rows per thread, on 257^2:
+// rims of 6, 12, 16 and cores of 24 are 15 to 40 % slower, four rows 8 %.  257^2,
+// 1457 substeps: 1457 sweeps 5.1 ms, 182 tile launches 1.6 ms.
+template <bool P2, bool PER>
+__global__ __launch_bounds__(kTileSide *kTileSide / kTileRows) void fe_tile_kernel(
+    MeshStepArgs a, const double *__restrict__ cx, const double *__restrict__ cy, double *__restrict__ nx,
+    double *__restrict__ ny)
+{
+    constexpr int S = kTileSide, R = kTileRows;
+    // one row and one node more on each side, read by the outermost threads
+    // only and never part of a result
+    __shared__ double sm[2][2][(S + 2) * S + 2];
+    const bool pxi = PER && a.per_xi, peta = PER && a.per_eta;
+    // nodes of a box that are advanced: the inner ones, all distinct ones along a periodic axis
+    const int nix = pxi ? a.n_xi - 1 : a.P_xi - 1, niy = peta ? a.n_eta - 1 : a.P_eta - 1;
+    const int tiles_x = (nix + kTileCore - 1) / kTileCore, tiles_y = (niy + kTileCore - 1) / kTileCore;
+    const int box = (int)blockIdx.x / (tiles_x * tiles_y), tile = (int)blockIdx.x % (tiles_x * tiles_y);
+    const int bi = box % a.sub_xi, bj = box / a.sub_xi;
+    const int ox = bi * a.P_xi + (pxi ? 0 : 1) + tile % tiles_x * kTileCore;   // first node of the core
+    const int oy = bj * a.P_eta + (peta ? 0 : 1) + tile / tiles_x * kTileCore;
+    const int lo_x = bi * a.P_xi, hi_x = lo_x + a.P_xi, lo_y = bj * a.P_eta, hi_y = lo_y + a.P_eta;
+    const int col = threadIdx.x % S, row0 = (int)threadIdx.x / S * R;
+    const FeCoef k = fe_coef<P2>(a);
+
+    // own nodes: 0 outside the box, 1 Dirichlet, 2 advanced
+    int kind[R], gi[R];
+    double p0[R], p1[R], p2[R], p3[R], x[R], y[R], eo = 0.0, wo = 0.0, no[R], so[R];
+    int i = ox - kTileRim + col;
+    bool in_x = pxi || (i >= lo_x && i <= hi_x), edge_x = !pxi && (i == lo_x || i == hi_x);
+    if (pxi) {
+        const int m = a.n_xi - 1;
+        i = ((i % m) + m) % m;
+        eo = i == m - 1 ? a.Lx : 0.0;
+        wo = i == 0 ? 0.0 - a.Lx : 0.0;
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        int j = oy - kTileRim + row0 + r;
+        const bool in_y = peta || (j >= lo_y && j <= hi_y), edge_y = !peta && (j == lo_y || j == hi_y);
+        no[r] = so[r] = 0.0;
+        if (peta) {
+            const int m = a.n_eta - 1;
+            j = ((j % m) + m) % m;
+            no[r] = j == m - 1 ? a.Ly : 0.0;
+            so[r] = j == 0 ? 0.0 - a.Ly : 0.0;
+        }
+        kind[r] = !(in_x && in_y) ? 0 : (edge_x || edge_y) ? 1 : 2;
+        const int g = kind[r] ? j * a.n_xi + i : 0;
+        gi[r] = g;
+        x[r] = y[r] = p0[r] = p1[r] = p2[r] = p3[r] = 0.0;
+        if (kind[r] == 2) {
+            x[r] = cx[g];
+            y[r] = cy[g];
+            p0[r] = a.tx1[g] * k.sx;
+            p1[r] = a.ty1[g] * k.sy;
+        } else if (kind[r] == 1) {
+            p0[r] = a.x0[g];
+            p1[r] = a.tx1[g];
+            p2[r] = a.y0[g];
+            p3[r] = a.ty1[g];
+            const double th = (double)a.l0 / (double)a.L;
+            x[r] = a.l0 == 0 ? p0[r] : (1.0 - th) * p0[r] + th * p1[r];
+            y[r] = a.l0 == 0 ? p2[r] : (1.0 - th) * p2[r] + th * p3[r];
+        }
+    }
+    const int q0 = (row0 + 1) * S + col + 1;
+    bool edge = false, seam = false;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        sm[0][0][q0 + r * S] = x[r];
+        sm[0][1][q0 + r * S] = y[r];
+        edge = edge || kind[r] == 1;
+        if (PER) seam = seam || no[r] != 0.0 || so[r] != 0.0;
+    }
+    if (PER) seam = seam || eo != 0.0 || wo != 0.0;
+    // most waves hold no Dirichlet node and no node beside a seam
+    const bool any_edge = __ballot(edge) != 0, any_seam = PER && __ballot(seam) != 0;
+    __syncthreads();
+    for (int l = 0; l < a.steps; ++l) {
+        const double *px = &sm[l & 1][0][q0], *py = &sm[l & 1][1][q0];
+        double *qx = &sm[(l & 1) ^ 1][0][q0], *qy = &sm[(l & 1) ^ 1][1][q0];
+        double bel = px[-S], bel2 = py[-S];
+        const double abv = px[R * S], abv2 = py[R * S];
+        double e[R], w[R], e2[R], w2[R], n2[R], s2[R], u[R], v[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            e[r] = px[r * S + 1];
+            w[r] = px[r * S - 1];
+            e2[r] = py[r * S + 1];
+            w2[r] = py[r * S - 1];
+            n2[r] = r + 1 < R ? y[r + 1] : abv2;
+            s2[r] = r > 0 ? y[r - 1] : bel2;
+        }
+        if (any_seam) {
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                e[r] = e[r] + eo;
+                w[r] = w[r] + wo;
+                n2[r] = n2[r] + no[r];
+                s2[r] = s2[r] + so[r];
             }
         }
-        if (bq >= 0) {
-            sx[bq] = (1.0 - th1) * bx0 + th1 * bx1;
-            sy[bq] = (1.0 - th1) * by0 + th1 * by1;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            u[r] = fe_update<P2>(k, p0[r], p1[r], x[r], e[r], w[r], r + 1 < R ? x[r + 1] : abv, r > 0 ? x[r - 1] : bel);
+            v[r] = fe_update<P2>(k, p0[r], p1[r], y[r], e2[r], w2[r], n2[r], s2[r]);
+        }
+        if (any_edge) {
+            const double th1 = (double)(a.l0 + l + 1) / (double)a.L;
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+                if (kind[r] == 1) {
+                    u[r] = (1.0 - th1) * p0[r] + th1 * p1[r];
+                    v[r] = (1.0 - th1) * p2[r] + th1 * p3[r];
+                }
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            x[r] = u[r];
+            y[r] = v[r];
+            qx[r * S] = u[r];
+            qy[r * S] = v[r];
         }
         __syncthreads();
     }
+    // the core's advanced nodes, and the images of node 0 on a periodic axis
+    const int c = col - kTileRim;
 #pragma unroll
-    for (int r = 0; r < kSubPerThread; ++r) {
-        if (lq[r] >= 0) {
-            const int q = lq[r];
-            const int g = (j0 + q / Bx) * a.n_xi + i0 + q % Bx;
-            x_new[g] = sx[q];
-            y_new[g] = sy[q];
+    for (int r = 0; r < R; ++r) {
+        const int d = row0 + r - kTileRim;
+        if (kind[r] != 2 || c < 0 || c >= kTileCore || d < 0 || d >= kTileCore) continue;
+        if (PER && ((pxi && ox + c > a.n_xi - 2) || (peta && oy + d > a.n_eta - 2))) continue;   // gone round
+        const int g = gi[r];
+        nx[g] = x[r];
+        ny[g] = y[r];
+        if (PER) {
+            const int ii = g % a.n_xi, jj = g / a.n_xi;
+            const bool ix = pxi && ii == 0, iy = peta && jj == 0;
+            const int gx = jj * a.n_xi + a.n_xi - 1, gy = (a.n_eta - 1) * a.n_xi + ii;
+            if (ix) nx[gx] = x[r] + a.Lx, ny[gx] = y[r];
+            if (iy) nx[gy] = x[r], ny[gy] = y[r] + a.Ly;
+            if (ix && iy) {
+                const int gc = a.n_eta * a.n_xi - 1;
+                nx[gc] = x[r] + a.Lx;
+                ny[gc] = y[r] + a.Ly;
+            }
         }
     }
 }
@@ -578,6 +839,8 @@ __global__ void transfer_p1_kernel(TransferArgs a)
 // ---------------------------------------------------------------------------
 // Launchers
 // ---------------------------------------------------------------------------
+static bool power_of_two(int n) { return n > 0 && (n & (n - 1)) == 0; }
+
 size_t edge_gen_lds_bytes(int n_max) { return (size_t)3 * (size_t)n_max * sizeof(double); }
 
 hipError_t launch_edge_gen(const double *rho, const double *rho_xi, const double *rho_eta, int n_xi, int n_eta,
@@ -587,8 +850,14 @@ hipError_t launch_edge_gen(const double *rho, const double *rho_xi, const double
     const int sides = (per_xi ? 0 : 2) + (per_eta ? 0 : 2);
     if (sides == 0) return hipSuccess;
     const int n_max = per_xi ? n_xi : (per_eta ? n_eta : (n_xi > n_eta ? n_xi : n_eta));
-    hipLaunchKernelGGL(edge_gen_kernel, dim3(sides), dim3(kEdgeBlock), edge_gen_lds_bytes(n_max), s, rho, rho_xi,
-                       rho_eta, n_xi, n_eta, per_xi, per_eta, Lx, Ly, tau, L_eta, L_xi, bnd);
+    const int block = std::min(kEdgeBlock, (n_max + 63) / 64 * 64);
+    const bool p2 = (per_xi || power_of_two(n_eta - 1)) && (per_eta || power_of_two(n_xi - 1));
+    if (p2)
+        hipLaunchKernelGGL(edge_gen_kernel<true>, dim3(sides), dim3(block), edge_gen_lds_bytes(n_max), s, rho, rho_xi,
+                           rho_eta, n_xi, n_eta, per_xi, per_eta, Lx, Ly, tau, L_eta, L_xi, bnd);
+    else
+        hipLaunchKernelGGL(edge_gen_kernel<false>, dim3(sides), dim3(block), edge_gen_lds_bytes(n_max), s, rho, rho_xi,
+                           rho_eta, n_xi, n_eta, per_xi, per_eta, Lx, Ly, tau, L_eta, L_xi, bnd);
     return hipGetLastError();
 }
 
@@ -609,18 +878,55 @@ bool subdomain_fits_lds(int P_xi, int P_eta)
            subdomain_lds_bytes(P_xi, P_eta) <= kSubLdsMax;
 }
 
+template <bool P2>
+static void launch_sub(const MeshStepArgs &a, const SubShape &h, double *x_new, double *y_new, hipStream_t s)
+{
+    const dim3 grid(a.sub_xi * a.sub_eta), block(h.block);
+    const size_t lds = 2 * subdomain_lds_bytes(a.P_xi, a.P_eta);
+    if (h.rows == 8)
+        hipLaunchKernelGGL((subdomain_lds_kernel<P2, 8>), grid, block, lds, s, a, h.first_bnd, x_new, y_new);
+    else if (h.rows == 4)
+        hipLaunchKernelGGL((subdomain_lds_kernel<P2, 4>), grid, block, lds, s, a, h.first_bnd, x_new, y_new);
+    else
+        hipLaunchKernelGGL((subdomain_lds_kernel<P2, 1>), grid, block, lds, s, a, h.first_bnd, x_new, y_new);
+}
+
 hipError_t launch_subdomain_lds(const MeshStepArgs &a, double *x_new, double *y_new, hipStream_t s)
 {
-    hipLaunchKernelGGL(subdomain_lds_kernel, dim3(a.sub_xi * a.sub_eta), dim3(kSubBlock),
-                       subdomain_lds_bytes(a.P_xi, a.P_eta), s, a, x_new, y_new);
+    const SubShape h = subdomain_shape(a.P_xi, a.P_eta);
+    if (!h.block) return hipErrorInvalidValue;
+    if (power_of_two(a.n_xi - 1) && power_of_two(a.n_eta - 1))
+        launch_sub<true>(a, h, x_new, y_new, s);
+    else
+        launch_sub<false>(a, h, x_new, y_new, s);
     return hipGetLastError();
 }
 
 hipError_t launch_fe_sweep(const MeshStepArgs &a, const double *cx, const double *cy, double *nx, double *ny,
                            double th1, hipStream_t s)
 {
-    const size_t n = (size_t)a.n_xi * a.n_eta;
-    hipLaunchKernelGGL(fe_sweep_kernel, dim3(blocks_of(n, 256)), dim3(256), 0, s, a, cx, cy, nx, ny, th1);
+    if (a.steps == 0) {
+        const size_t n = (size_t)a.n_xi * a.n_eta;
+        hipLaunchKernelGGL(fe_sweep_kernel, dim3(blocks_of(n, 256)), dim3(256), 0, s, a, cx, cy, nx, ny, th1);
+        return hipGetLastError();
+    }
+    const bool per = !a.with_interfaces && (a.per_xi || a.per_eta);
+    if (a.steps < 1 || a.steps > kTileRim || a.l0 < 0 || a.l0 + a.steps > a.L) return hipErrorInvalidValue;
+    const int nix = per && a.per_xi ? a.n_xi - 1 : a.P_xi - 1, niy = per && a.per_eta ? a.n_eta - 1 : a.P_eta - 1;
+    const size_t tiles = (size_t)blocks_of((size_t)std::max(nix, 0), kTileCore) *
+                         blocks_of((size_t)std::max(niy, 0), kTileCore) * a.sub_xi * a.sub_eta;
+    if (tiles == 0) return hipSuccess;   // boxes of one cell: every node is Dirichlet
+    if (tiles > 0x7FFFFFFFu) return hipErrorInvalidValue;
+    const bool p2 = power_of_two(a.n_xi - 1) && power_of_two(a.n_eta - 1);
+    const dim3 grid((unsigned)tiles), block(kTileSide * kTileSide / kTileRows);
+    if (p2 && per)
+        hipLaunchKernelGGL((fe_tile_kernel<true, true>), grid, block, 0, s, a, cx, cy, nx, ny);
+    else if (p2)
+        hipLaunchKernelGGL((fe_tile_kernel<true, false>), grid, block, 0, s, a, cx, cy, nx, ny);
+    else if (per)
+        hipLaunchKernelGGL((fe_tile_kernel<false, true>), grid, block, 0, s, a, cx, cy, nx, ny);
+    else
+        hipLaunchKernelGGL((fe_tile_kernel<false, false>), grid, block, 0, s, a, cx, cy, nx, ny);
     return hipGetLastError();
 }
 

@@ -11,11 +11,36 @@
 
 namespace msdd {
 
-constexpr int kEdgeBlock = 256;
+constexpr int kEdgeBlock = 1024;
 constexpr int kSubBlock = 1024;                 // one workgroup per subdomain
-constexpr int kSubPerThread = 4;                // interior nodes per thread (registers; up to 65x65 subdomains)
+constexpr int kSubPerThread = 4;                // interior nodes per thread of the LDS solve's size limit
 constexpr size_t kSubLdsMax = 160u * 1024u;     // LDS of one CU on gfx950
 constexpr int kQualityBlock = 256;
+constexpr int kTileCore = 16;                   // the sweeps' tiles: nodes a workgroup advances per axis,
+constexpr int kTileRim = 8;                     // the rim around them = substeps per launch,
+constexpr int kTileSide = kTileCore + 2 * kTileRim;
+constexpr int kTileRows = 2;                    // and nodes per thread
+
+// Workgroup of the LDS solve of one (P_xi + 1) x (P_eta + 1) subdomain: rows
+// of a column per thread, the first thread that owns a boundary node, the
+// block.  block = 0 where two time levels do not fit the LDS or the threads do
+// not suffice: the tiles take such subdomains.
+struct SubShape {
+    int rows, first_bnd, block;
+};
+inline SubShape subdomain_shape(int P_xi, int P_eta)
+{
+    const long nb = 2L * (P_xi + 1) + 2L * (P_eta - 1);
+    if (P_xi < 2 || P_eta < 2 || (size_t)4 * (P_xi + 1) * (P_eta + 1) * sizeof(double) > kSubLdsMax)
+        return SubShape{0, 0, 0};
+    for (int rows : {4, 8, 1}) {
+        if (P_eta - 1 < rows) continue;
+        const long segs = (long)(P_xi - 1) * ((P_eta - 1 + rows - 1) / rows);
+        const long first = (segs + 63) / 64 * 64, block = first + (nb + 63) / 64 * 64;
+        if (block <= kSubBlock) return SubShape{rows, (int)first, (int)block};
+    }
+    return SubShape{0, 0, 0};
+}
 
 // Everything the targets / subdomain / sweep kernels read; device pointers.
 struct MeshStepArgs {
@@ -27,8 +52,11 @@ struct MeshStepArgs {
     const double *iface_x, *iface_y;       // interface estimate at t^{n+1}, by rank
     const int32_t *node_rank;              // [n_eta][n_xi]: interface rank or -1
     const double *rho, *rho_xi, *rho_eta;  // FP64 node tables of the frozen monitor
-    double *tx1, *ty1;                     // Dirichlet values at t^{n+1} (written by the targets kernel)
+    double *tx1, *ty1;                     // Dirichlet values at t^{n+1}, the drift coefficients rho_xi / rho and
+                                           // rho_eta / rho of the other nodes (written by the targets kernel)
     uint8_t *mask;                         // 1 on Dirichlet nodes
+    int l0, steps;                         // launch_fe_sweep: substeps done, substeps of this launch (0: the
+                                           // plain sweep of one substep)
 };
 
 size_t edge_gen_lds_bytes(int n_max);
