@@ -774,8 +774,8 @@ __device__ __forceinline__ void item_loop(Src &src, uint32_t n_items, const Inst
                 const float x0 = (float)((double)i0 / (double)C.nx1);
                 const float y0 = (float)((double)j0 / (double)C.ny1);
                 const float m0 = side_distance(C, x0, y0);
-                const double rx = gptr(Ip->x64)[(uint32_t)(j0 * C.n_xi + i0)];
-                const double ry = gptr(Ip->y64)[(uint32_t)(j0 * C.n_xi + i0)];
+                const double rx = gptr(Ip->x64)[(uint32_t)(j0 * (C.n_xi + 2) + i0)];
+                const double ry = gptr(Ip->y64)[(uint32_t)(j0 * (C.n_xi + 2) + i0)];
                 if (tgt == 0u) {
                     act0 = 1u; cnt0 = f.count; rem0 = f.count; node0 = rk; pb0 = f.p_begin;
                     part0 = f.partial; x00 = x0; y00 = y0; m00 = m0; rx0 = rx; ry0 = ry;
@@ -1188,21 +1188,18 @@ __global__ __launch_bounds__(kTableBlock) void paths_fp64(Fp64View V, uint32_t n
 // address.
 constexpr int kFinalWaves = 4, kFinalBlocks = 512;
 __global__ __launch_bounds__(64 * kFinalWaves) void finalize_kernel(
-    const Partial *__restrict__ partials, const NodeSpan *__restrict__ spans, const InstView *__restrict__ inst,
-    uint32_t M, uint64_t n_paths, double *mean_x, double *mean_y, double *se_x, double *se_y, double *exit_frac,
-    unsigned long long *steps_total)
+    const Partial *__restrict__ partials, uint32_t chunks, InstView I, uint32_t M, uint64_t n_paths, double *mean_x,
+    double *mean_y, double *se_x, double *se_y, double *exit_frac, unsigned long long *steps_total)
 {
     __shared__ unsigned long long wave_steps[kFinalWaves];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const InstView &I = *inst;
     const double N = (double)n_paths;
     unsigned long long my_steps = 0;
     for (uint32_t node = blockIdx.x * kFinalWaves + w; node < M; node += gridDim.x * kFinalWaves) {
-        const NodeSpan sp = spans[node];
         double s1x = 0.0, s2x = 0.0, s1y = 0.0, s2y = 0.0;
         unsigned long long ex = 0;
-        for (uint32_t c = (uint32_t)lane; c < sp.count; c += 64u) {
-            const Partial &p = partials[sp.first + c];
+        for (uint32_t c = (uint32_t)lane; c < chunks; c += 64u) {
+            const Partial &p = partials[(size_t)node * chunks + c];
             s1x += p.s1x;
             s2x += p.s2x;
             s1y += p.s1y;
@@ -1218,8 +1215,9 @@ __global__ __launch_bounds__(64 * kFinalWaves) void finalize_kernel(
         if (lane == 0) {
             const int i0 = I.node_i[node], j0 = I.node_j[node];
             const uint32_t r = I.node_r[node];
-            mean_x[r] = I.x64[(size_t)j0 * I.n_xi + i0] + s1x / N;
-            mean_y[r] = I.y64[(size_t)j0 * I.n_xi + i0] + s1y / N;
+            const size_t g = (size_t)j0 * (I.n_xi + 2) + i0;
+            mean_x[r] = I.x64[g] + s1x / N;
+            mean_y[r] = I.y64[g] + s1y / N;
             if (n_paths > 1) {
                 const double vx = (s2x - s1x * s1x / N) / (N - 1.0);
                 const double vy = (s2y - s1y * s1y / N) / (N - 1.0);
@@ -1761,7 +1759,7 @@ hipError_t launch_finalize(const Partial *partials, const NodeSpan *spans, const
 {
     if (M == 0) return hipSuccess;
     const unsigned blocks = blocks_for(M, kFinalWaves);
-    hipLaunchKernelGGL(finalize_kernel, dim3(blocks < kFinalBlocks ? blocks : kFinalBlocks), dim3(64 * kFinalWaves), 0, s, partials, spans, inst, M, n_paths,
+    hipLaunchKernelGGL(finalize_kernel, dim3(blocks < kFinalBlocks ? blocks : kFinalBlocks), dim3(64 * kFinalWaves), 0, s, partials, spans->count, *inst, M, n_paths,
                        mean_x, mean_y, se_x, se_y, exit_frac, steps_total);
     return hipGetLastError();
 }

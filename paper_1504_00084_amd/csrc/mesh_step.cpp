@@ -360,9 +360,9 @@ try {
             HIP_TRY(hipMemcpyAsync(bo.p, step->bnd_t1, nb * 8, in_dev ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice,
                                    st));
         }
-        HIP_TRY(hipStreamSynchronize(st));
     }
-    // interface estimate on device arrays (takes the context lock itself)
+    // interface estimate on device arrays, behind the above on the stream (takes
+    // the context lock itself)
     mesh_sdd_step s2 = *step;
     s2.inputs_on_device = 1;
     s2.x_cur = x0.p;

@@ -105,7 +105,8 @@ struct InstView {
     const double *xpad, *ypad;
     const double *bnd0, *bnd1;
 
-    // FP64 mesh at t^n (for the reference values of the shifted sums).
+    // FP64 mesh at t^n (for the reference values of the shifted sums): node
+    // (0, 0) of the padded mesh, row stride n_xi + 2; read at interface nodes.
     const double *x64, *y64;
 
     // Partial sums of this request's work items.
@@ -134,8 +135,8 @@ __host__ __device__ inline int path_kind(int per_xi, int per_eta, int bridge)
 }
 __host__ __device__ inline int path_kind(const InstView &v) { return path_kind(v.per_xi, v.per_eta, v.bridge); }
 
-// Per-node finalize descriptor: the partials of one node are
-// partials[first .. first + count) in chunk order.
+// Finalize descriptor: the partials of node m are partials[first + m count ..
+// first + (m + 1) count) in chunk order.
 struct NodeSpan {
     uint32_t first;
     uint32_t count;

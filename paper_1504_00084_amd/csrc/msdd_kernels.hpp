@@ -92,7 +92,8 @@ constexpr int kPad64Side = 143;              // padded rho in LDS: at most 143 x
 constexpr int kPad64 = kPad64Side * kPad64Side;
 
 // a9: fixed-order combine of each node's partials; mean, SE, exit fraction,
-// written at the node's interface rank (inst->node_r).
+// written at the node's interface rank (inst->node_r).  `spans` (one entry,
+// first = 0) and `inst` are host addresses, read before the call returns.
 hipError_t launch_finalize(const Partial *partials, const NodeSpan *spans, const InstView *inst, uint32_t M,
                            uint64_t n_paths, double *mean_x, double *mean_y, double *se_x, double *se_y,
                            double *exit_frac, unsigned long long *steps_total, hipStream_t s);

@@ -458,7 +458,7 @@ __device__ __forceinline__ void item_loop64(Src &src, const InstView &I, const C
                 double vx, vy;
                 value64(I, C, P, side, vx, vy);
                 const uint32_t node = (ls & 1u) ? it1.node : it0.node;
-                const size_t g = (size_t)gptr(I.node_j)[node] * I.n_xi + gptr(I.node_i)[node];
+                const size_t g = (size_t)gptr(I.node_j)[node] * (I.n_xi + 2) + gptr(I.node_i)[node];
                 const double dx = vx - gptr(I.x64)[g], dy = vy - gptr(I.y64)[g];
                 c1x += dx;
                 c2x = fma(dx, dx, c2x);

@@ -623,8 +623,19 @@ int fp64_chunk(const mesh_sdd_ctx *ctx, int32_t M, int64_t N)
     return (int64_t)M * ((N + 63) / 64) <= 32 * waves ? 64 : msdd::kFp64Block;
 }
 
+// Waits for the stream when it goes out of scope armed.
+struct SyncOnFail {
+    hipStream_t s;
+    bool armed = true;
+    ~SyncOnFail()
+    {
+        if (armed) (void)hipStreamSynchronize(s);
+    }
+};
+
 // Allocate the request's device buffers, stage its inputs and run the prep
-// kernels; builds the work items.  With an arena the buffers are carved from
+// kernels; builds the work items.  Nothing is waited for: the host snapshots
+// stay until the launch that follows has been.  With an arena the buffers are carved from
 // it instead of allocated (the no-allocation solve).  Caller holds gpu_mu.
 int stage_request(Request &r, const mesh_sdd_step *dev_step, Arena *arena = nullptr)
 {
@@ -638,6 +649,7 @@ int stage_request(Request &r, const mesh_sdd_step *dev_step, Arena *arena = null
     const int M = inst.M;
     const bool fp64 = d.precision == MESH_SDD_FP64;
     int rc = MESH_SDD_OK;
+    SyncOnFail guard{st};   // copies from the host snapshots may be under way when a later step fails
     if (arena) {
         // no allocation: the set of the instance's current layout if built,
         // else any set of the stride (the layout orders the work only)
@@ -671,36 +683,42 @@ int stage_request(Request &r, const mesh_sdd_step *dev_step, Arena *arena = null
                     "interface stride)", n_part);
 
     for (DevBuf *b : {&r.x64, &r.y64, &r.b0, &r.b1, &r.xpad, &r.ypad, &r.xpad_f, &r.ypad_f, &r.b0f, &r.b1f,
-                      &r.view, &r.partials, &r.spans, &r.out, &r.steps_total}) {
+                      &r.partials, &r.out, &r.steps_total}) {
         b->pool = &ctx->pool;
         b->arena = arena;
     }
-    if (r.x64.alloc(n * 8) || r.y64.alloc(n * 8) || r.b0.alloc(nb * 8) || r.b1.alloc(nb * 8) ||
+    if ((!dev_step && (r.x64.alloc(n * 8) || r.y64.alloc(n * 8) || r.b0.alloc(nb * 8) || r.b1.alloc(nb * 8))) ||
         r.xpad.alloc(np * 8) || r.ypad.alloc(np * 8) ||
         (!fp64 && (r.xpad_f.alloc(np * 4) || r.ypad_f.alloc(np * 4) || r.b0f.alloc(nb * 4) || r.b1f.alloc(nb * 4))) ||
-        r.view.alloc(sizeof(InstView)) ||
-        r.partials.alloc(n_part * sizeof(Partial)) || r.spans.alloc((size_t)Ms * sizeof(NodeSpan)) ||
-        r.out.alloc((size_t)5 * M * sizeof(double)) || r.steps_total.alloc(kTotalsBytes))
+        r.partials.alloc(n_part * sizeof(Partial)) || r.out.alloc((size_t)5 * M * sizeof(double)) ||
+        r.steps_total.alloc(kTotalsBytes))
         return fail(MESH_SDD_E_NOMEM, "device allocation for a request failed");
 
+    const double *x = nullptr, *y = nullptr, *b0 = nullptr, *b1 = nullptr;   // device inputs
     if (dev_step) {
-        HIP_TRY(hipMemcpyAsync(r.x64.p, dev_step->x_cur, n * 8, hipMemcpyDeviceToDevice, st));
-        HIP_TRY(hipMemcpyAsync(r.y64.p, dev_step->y_cur, n * 8, hipMemcpyDeviceToDevice, st));
-        HIP_TRY(hipMemcpyAsync(r.b0.p, dev_step->bnd_t0, nb * 8, hipMemcpyDeviceToDevice, st));
-        HIP_TRY(hipMemcpyAsync(r.b1.p, dev_step->bnd_t1, nb * 8, hipMemcpyDeviceToDevice, st));
+        // a blocking call: its kernels read the caller's arrays, which no
+        // result array of the call overlaps when results are written directly
+        x = dev_step->x_cur;
+        y = dev_step->y_cur;
+        b0 = dev_step->bnd_t0;
+        b1 = dev_step->bnd_t1;
     } else {
         HIP_TRY(hipMemcpyAsync(r.x64.p, r.hx.data(), n * 8, hipMemcpyHostToDevice, st));
         HIP_TRY(hipMemcpyAsync(r.y64.p, r.hy.data(), n * 8, hipMemcpyHostToDevice, st));
         HIP_TRY(hipMemcpyAsync(r.b0.p, r.hb0.data(), nb * 8, hipMemcpyHostToDevice, st));
         HIP_TRY(hipMemcpyAsync(r.b1.p, r.hb1.data(), nb * 8, hipMemcpyHostToDevice, st));
+        x = r.x64.as<double>();
+        y = r.y64.as<double>();
+        b0 = r.b0.as<double>();
+        b1 = r.b1.as<double>();
     }
-    HIP_TRY(msdd::launch_prep_mesh(r.x64.as<double>(), r.y64.as<double>(), d.n_xi, d.n_eta, d.periodic_xi,
-                                   d.periodic_eta, d.Lx, d.Ly, r.xpad.as<double>(), r.ypad.as<double>(),
+    HIP_TRY(msdd::launch_prep_mesh(x, y, d.n_xi, d.n_eta, d.periodic_xi, d.periodic_eta, d.Lx, d.Ly,
+                                   r.xpad.as<double>(), r.ypad.as<double>(),
                                    fp64 ? fp64_spare(inst) : r.xpad_f.as<float>(),
                                    fp64 ? fp64_spare(inst) : r.ypad_f.as<float>(), st));
     if (!fp64) {
-        HIP_TRY(msdd::launch_to_f32(r.b0.as<double>(), r.b0f.as<float>(), nb, st));
-        HIP_TRY(msdd::launch_to_f32(r.b1.as<double>(), r.b1f.as<float>(), nb, st));
+        HIP_TRY(msdd::launch_to_f32(b0, r.b0f.as<float>(), nb, st));
+        HIP_TRY(msdd::launch_to_f32(b1, r.b1f.as<float>(), nb, st));
     }
 
     // kernel view
@@ -747,17 +765,11 @@ int stage_request(Request &r, const mesh_sdd_step *dev_step, Arena *arena = null
     v.rho_pad = rho_padded(inst);
     v.xpad = r.xpad.as<double>();
     v.ypad = r.ypad.as<double>();
-    v.bnd0 = r.b0.as<double>();
-    v.bnd1 = r.b1.as<double>();
-    v.x64 = r.x64.as<double>();
-    v.y64 = r.y64.as<double>();
+    v.bnd0 = b0;
+    v.bnd1 = b1;
+    v.x64 = r.xpad.as<double>() + (d.n_xi + 2) + 1;
+    v.y64 = r.ypad.as<double>() + (d.n_xi + 2) + 1;
     v.partials = r.partials.as<Partial>();
-    HIP_TRY(hipMemcpyAsync(r.view.p, &v, sizeof v, hipMemcpyHostToDevice, st));
-
-    // node spans: node-major chunk slots
-    std::vector<NodeSpan> spans((size_t)Ms);
-    for (int m = 0; m < Ms; ++m) spans[m] = NodeSpan{(uint32_t)((size_t)m * chunks), chunks};
-    if (Ms) HIP_TRY(hipMemcpyAsync(r.spans.p, spans.data(), spans.size() * sizeof(NodeSpan), hipMemcpyHostToDevice, st));
     HIP_TRY(msdd::launch_fill_u32(r.steps_total.as<uint32_t>(), 0u, 2, st));
 
     // FP32 work: every (node, chunk), numbered node-major, so that the waves
@@ -766,20 +778,25 @@ int stage_request(Request &r, const mesh_sdd_step *dev_step, Arena *arena = null
     r.n_items = fp64 ? 0 : n_part;
     r.next_item = 0;
     r.done_items = 0;
-    // the host snapshots are no longer needed once the copies are done
-    HIP_TRY(hipStreamSynchronize(st));
+    guard.armed = false;
+    return MESH_SDD_OK;
+}
+
+// The host snapshots, once the stream has been waited for.
+void drop_snapshots(Request &r)
+{
     std::vector<double>().swap(r.hx);
     std::vector<double>().swap(r.hy);
     std::vector<double>().swap(r.hb0);
     std::vector<double>().swap(r.hb1);
-    return MESH_SDD_OK;
 }
 
 void release_request_buffers(Request &r)
 {
     for (DevBuf *b : {&r.x64, &r.y64, &r.b0, &r.b1, &r.xpad, &r.ypad, &r.xpad_f, &r.ypad_f, &r.b0f, &r.b1f,
-                      &r.view, &r.partials, &r.spans, &r.out, &r.steps_total})
+                      &r.partials, &r.out, &r.steps_total})
         b->release();
+    drop_snapshots(r);
 }
 
 // Sizes the jobs of a windowed launch towards the end of each queue: a job
@@ -842,32 +859,26 @@ uint32_t static_rounds(size_t n_items, uint32_t waves, int chunk_paths, int K)
 }
 
 // One persistent FP32 launch over the items described by `ranges` (their
-// inst fields index `views`).  Caller holds gpu_mu.  Returns the device time
-// in ms via *ms.
+// inst fields index `views`), enqueued only: wait_launch waits for it.
+// Caller holds gpu_mu.
 int run_fp32_launch(mesh_sdd_ctx *ctx, std::vector<InstView> &views, const std::vector<WorkRange> &ranges,
-                    const std::vector<const SampleSet *> &sets, const mesh_sdd_launch &l, double *ms,
-                    Arena *arena = nullptr)
+                    const std::vector<const SampleSet *> &sets, const mesh_sdd_launch &l, Arena *arena = nullptr)
 {
     hipStream_t st = ctx->stream;
+    ctx->launched = false;
     // launch scratch: the context's grow-only buffers, or pieces of the arena
-    DevBuf a_views, a_ranges, a_head, a_jobs, a_ends;
-    for (DevBuf *b : {&a_views, &a_ranges, &a_head, &a_jobs, &a_ends}) b->arena = arena;
-    DevBuf &views_b = arena ? a_views : ctx->views, &ranges_b = arena ? a_ranges : ctx->ranges;
-    DevBuf &head_b = arena ? a_head : ctx->head, &jobs_b = arena ? a_jobs : ctx->jobs;
+    DevBuf a_plan, a_head, a_ends;
+    for (DevBuf *b : {&a_plan, &a_head, &a_ends}) b->arena = arena;
+    DevBuf &plan_b = arena ? a_plan : ctx->plan, &head_b = arena ? a_head : ctx->head;
     DevBuf &ends_b = arena ? a_ends : ctx->ends;
     size_t n_items = 0;
     for (const WorkRange &w : ranges) n_items += w.count;
-    if (n_items == 0) {
-        *ms = 0.0;
-        return MESH_SDD_OK;
-    }
+    if (n_items == 0) return MESH_SDD_OK;
     if (n_items > 0xFFFFFFF0u) return fail(MESH_SDD_E_INVAL, "too many work items in one launch");
     uint32_t cap = 64;   // LDS slots per item: the largest chunk of the launch
     for (const WorkRange &w : ranges) cap = std::max(cap, w.chunk_paths);
     cap = (cap + 63u) / 64u * 64u;
-    if (views_b.reserve(views.size() * sizeof(InstView)) ||
-        ranges_b.reserve(ranges.size() * sizeof(WorkRange)) || head_b.reserve(64))
-        return fail(MESH_SDD_E_NOMEM, "device allocation for the work queue failed");
+    if (head_b.reserve(64)) return fail(MESH_SDD_E_NOMEM, "device allocation for the work queue failed");
     // A launch that holds one instance whose node tables of rho and dt rho_xi
     // fit the LDS stages them whole (1024-thread workgroups); any other
     // launch stages windows of them, job by job; the waves then keep their
@@ -882,8 +893,6 @@ int run_fp32_launch(mesh_sdd_ctx *ctx, std::vector<InstView> &views, const std::
         return fail(MESH_SDD_E_NOMEM, "device allocation of the end-state buffer failed");
     if (level == 2)
         views[0].static_rounds = static_rounds(n_items, end_waves, (int)ranges[0].chunk_paths, views[0].K);
-    HIP_TRY(hipMemcpyAsync(views_b.p, views.data(), views.size() * sizeof(InstView), hipMemcpyHostToDevice, st));
-    HIP_TRY(hipMemcpyAsync(ranges_b.p, ranges.data(), ranges.size() * sizeof(WorkRange), hipMemcpyHostToDevice, st));
     // windowed launch: one job per (range, grid block), split so that no job
     // holds more than 1/job_split of a workgroup's share of the items, in
     // block order, cut into per-XCD queues of equal nominal work
@@ -925,37 +934,52 @@ int run_fp32_launch(mesh_sdd_ctx *ctx, std::vector<InstView> &views, const std::
             const WorkRange &w = ranges[j.range];
             return (double)j.count * w.chunk_paths * views[w.inst].K;
         }, qs);
-        if (jobs_b.reserve(std::max<size_t>(1, jobs.size()) * sizeof(msdd::WinJob)))
-            return fail(MESH_SDD_E_NOMEM, "device allocation of the job list failed");
-        if (!jobs.empty())
-            HIP_TRY(hipMemcpyAsync(jobs_b.p, jobs.data(), jobs.size() * sizeof(msdd::WinJob),
-                                   hipMemcpyHostToDevice, st));
     }
-    TimerEvents ev;
-    HIP_TRY(ev.create());
-    HIP_TRY(hipEventRecord(ev.e0, st));
+    // views, ranges and jobs in one copy
+    const size_t at_ranges = round_up(views.size() * sizeof(InstView), 16);
+    const size_t at_jobs = at_ranges + round_up(ranges.size() * sizeof(WorkRange), 16);
+    ctx->plan_host.resize(at_jobs + jobs.size() * sizeof(msdd::WinJob));
+    std::memcpy(ctx->plan_host.data(), views.data(), views.size() * sizeof(InstView));
+    std::memcpy(ctx->plan_host.data() + at_ranges, ranges.data(), ranges.size() * sizeof(WorkRange));
+    if (!jobs.empty())
+        std::memcpy(ctx->plan_host.data() + at_jobs, jobs.data(), jobs.size() * sizeof(msdd::WinJob));
+    if (plan_b.reserve(ctx->plan_host.size()))
+        return fail(MESH_SDD_E_NOMEM, "device allocation for the work queue failed");
+    HIP_TRY(hipMemcpyAsync(plan_b.p, ctx->plan_host.data(), ctx->plan_host.size(), hipMemcpyHostToDevice, st));
+    const InstView *const d_views = plan_b.as<InstView>();
+    const WorkRange *const d_ranges = reinterpret_cast<const WorkRange *>(plan_b.as<char>() + at_ranges);
+    const msdd::WinJob *const d_jobs = reinterpret_cast<const msdd::WinJob *>(plan_b.as<char>() + at_jobs);
+    HIP_TRY(ctx->ev.create());
+    HIP_TRY(hipEventRecord(ctx->ev.e0, st));
     hipError_t le =
-        level == 3 ? msdd::launch_paths_fp32_window(views_b.as<InstView>(), ranges_b.as<WorkRange>(),
-                                                    jobs_b.as<msdd::WinJob>(), qs, head_b.as<uint32_t>(),
-                                                    cap, kind, win_lds, table_grid,
+        level == 3 ? msdd::launch_paths_fp32_window(d_views, d_ranges, d_jobs, qs, head_b.as<uint32_t>(), cap, kind,
+                                                    win_lds, table_grid, ends_b.as<float>(), end_waves,
+                                                    (uint32_t)l.refill_lanes, (uint32_t)l.max_quarters, st)
+        : level > 0 ? msdd::launch_paths_fp32_table(d_views, d_ranges, (uint32_t)n_items, head_b.as<uint32_t>(), cap,
+                                                    level, msdd::path_kind(views[0]), n_nodes, table_grid,
                                                     ends_b.as<float>(), end_waves, (uint32_t)l.refill_lanes,
                                                     (uint32_t)l.max_quarters, st)
-        : level > 0 ? msdd::launch_paths_fp32_table(views_b.as<InstView>(), ranges_b.as<WorkRange>(),
-                                                    (uint32_t)n_items, head_b.as<uint32_t>(), cap, level,
-                                                    msdd::path_kind(views[0]), n_nodes, table_grid,
-                                                    ends_b.as<float>(), end_waves, (uint32_t)l.refill_lanes,
-                                                    (uint32_t)l.max_quarters, st)
-                    : msdd::launch_paths_fp32(views_b.as<InstView>(), ranges_b.as<WorkRange>(),
-                                                      (uint32_t)ranges.size(), (uint32_t)n_items,
-                                                      head_b.as<uint32_t>(), cap, grid_for(ctx, l, cap), l.block,
-                                                      st);
-    HIP_TRY(hipEventRecord(ev.e1, st));
-    hipError_t se = hipEventSynchronize(ev.e1);
-    float t = 0.0f;
-    (void)hipEventElapsedTime(&t, ev.e0, ev.e1);
+                    : msdd::launch_paths_fp32(d_views, d_ranges, (uint32_t)ranges.size(), (uint32_t)n_items,
+                                              head_b.as<uint32_t>(), cap, grid_for(ctx, l, cap), l.block, st);
+    HIP_TRY(hipEventRecord(ctx->ev.e1, st));
+    ctx->launched = true;
     if (le != hipSuccess) return fail(MESH_SDD_E_DEVICE, "path kernel launch failed: %s", hipGetErrorString(le));
-    if (se != hipSuccess) return fail(MESH_SDD_E_DEVICE, "path kernel failed: %s", hipGetErrorString(se));
+    return MESH_SDD_OK;
+}
+
+// Waits for the launch of run_fp32_launch or run_fp64_launch and for what
+// was enqueued behind it; its device time in ms via *ms (0 without a launch).
+// Called on every way out of a call that has enqueued work, also after an
+// error (`rc`, which is returned if it is one).  Caller holds gpu_mu.
+int wait_launch(mesh_sdd_ctx *ctx, int rc, double *ms)
+{
+    const hipError_t se = hipStreamSynchronize(ctx->stream);
+    float t = 0.0f;
+    if (ctx->launched) (void)hipEventElapsedTime(&t, ctx->ev.e0, ctx->ev.e1);
+    ctx->launched = false;
     *ms = t;
+    if (rc != MESH_SDD_OK) return rc;
+    if (se != hipSuccess) return fail(MESH_SDD_E_DEVICE, "path kernel failed: %s", hipGetErrorString(se));
     return MESH_SDD_OK;
 }
 
@@ -974,13 +998,15 @@ WorkRange range_of(const Request &r, uint32_t slot, size_t base, size_t first, s
     return w;
 }
 
-// FP64 launch of one request.  Caller holds gpu_mu.
-int run_fp64_launch(mesh_sdd_ctx *ctx, Request &r, double *ms, Arena *arena = nullptr)
+// FP64 launch of one request, enqueued only: wait_launch waits for it.
+// Caller holds gpu_mu.
+int run_fp64_launch(mesh_sdd_ctx *ctx, Request &r, Arena *arena = nullptr)
 {
     hipStream_t st = ctx->stream;
+    ctx->launched = false;
     DevBuf a_jobs;
     a_jobs.arena = arena;
-    DevBuf &jobs_b = arena ? a_jobs : ctx->jobs;
+    DevBuf &jobs_b = arena ? a_jobs : ctx->plan;
     msdd::Fp64View v{};
     static_cast<InstView &>(v) = r.v;
     const uint32_t waves = (uint32_t)ctx->cu_count * (uint32_t)(msdd::kTableBlock / 64);
@@ -1009,38 +1035,44 @@ int run_fp64_launch(mesh_sdd_ctx *ctx, Request &r, double *ms, Arena *arena = nu
             if (!arena) return fail(MESH_SDD_E_NOMEM, "device allocation of the job list failed");
             v.mode = 0;   // no room in the scratch: the table is read from global memory (the same values)
         } else if (!jobs.empty()) {
-            HIP_TRY(hipMemcpyAsync(jobs_b.p, jobs.data(), jobs.size() * sizeof(msdd::WinJob), hipMemcpyHostToDevice,
-                                   st));
+            ctx->plan_host.resize(jobs.size() * sizeof(msdd::WinJob));
+            std::memcpy(ctx->plan_host.data(), jobs.data(), ctx->plan_host.size());
+            HIP_TRY(hipMemcpyAsync(jobs_b.p, ctx->plan_host.data(), ctx->plan_host.size(), hipMemcpyHostToDevice, st));
             v.jobs = jobs_b.as<msdd::WinJob>();
         }
     }
-    TimerEvents ev;
-    HIP_TRY(ev.create());
-    HIP_TRY(hipEventRecord(ev.e0, st));
+    HIP_TRY(ctx->ev.create());
+    HIP_TRY(hipEventRecord(ctx->ev.e0, st));
     hipError_t le = msdd::launch_paths_fp64(&v, (uint32_t)r.Ms, (uint32_t)r.N, r.chunks_per_node,
                                             r.partials.as<Partial>(), st);
-    HIP_TRY(hipEventRecord(ev.e1, st));
-    hipError_t se = hipEventSynchronize(ev.e1);
-    float t = 0.0f;
-    (void)hipEventElapsedTime(&t, ev.e0, ev.e1);
+    HIP_TRY(hipEventRecord(ctx->ev.e1, st));
+    ctx->launched = true;
     if (le != hipSuccess) return fail(MESH_SDD_E_DEVICE, "FP64 path kernel launch failed: %s", hipGetErrorString(le));
-    if (se != hipSuccess) return fail(MESH_SDD_E_DEVICE, "FP64 path kernel failed: %s", hipGetErrorString(se));
-    *ms = t;
     return MESH_SDD_OK;
 }
 
-// Finalize (a9) into the request's output buffer, interpolate the nodes
-// that ran no paths (a10), and copy the results to the host -- or, when
-// `dev_out` is given, straight into its device arrays.
+// Finalize (a9), interpolate the nodes that ran no paths (a10) and fetch the
+// executed-step total, enqueued behind the launch: results go straight to
+// the caller's device arrays when `dev_out` is given, else through the
+// request's output buffer to the host.  They are there once the stream has
+// been waited for.  Caller holds gpu_mu.
 int finalize_request(mesh_sdd_ctx *ctx, Request &r, const mesh_sdd_result *dev_out = nullptr)
 {
     hipStream_t st = ctx->stream;
     const mesh_sdd &inst = *r.inst;
     const int M = inst.M;
-    double *o = r.out.as<double>();
-    HIP_TRY(msdd::launch_finalize(r.partials.as<Partial>(), r.spans.as<NodeSpan>(), r.view.as<InstView>(),
-                                  (uint32_t)r.Ms, (uint64_t)r.N, o, o + M, o + 2 * (size_t)M, o + 3 * (size_t)M,
-                                  o + 4 * (size_t)M, r.steps_total.as<unsigned long long>(), st));
+    double *const buf = r.out.as<double>();
+    double *o[5];
+    for (int k = 0; k < 5; ++k) o[k] = buf + (size_t)k * M;
+    if (dev_out) {
+        double *dst[5] = {dev_out->mean_x, dev_out->mean_y, dev_out->se_x, dev_out->se_y, dev_out->exit_frac};
+        for (int k = 0; k < 5; ++k)
+            if (dst[k]) o[k] = dst[k];
+        r.direct = true;
+    }
+    const NodeSpan span{0u, r.chunks_per_node};
+    HIP_TRY(msdd::launch_finalize(r.partials.as<Partial>(), &span, &r.v, (uint32_t)r.Ms, (uint64_t)r.N, o[0], o[1],
+                                  o[2], o[3], o[4], r.steps_total.as<unsigned long long>(), st));
     if (r.Ms < M) {
         msdd::InterpArgs a{};
         a.n_xi = inst.d.n_xi;
@@ -1056,29 +1088,62 @@ int finalize_request(mesh_sdd_ctx *ctx, Request &r, const mesh_sdd_result *dev_o
         a.node_i = inst.node_ij.as<int32_t>();   // rank order (the node lists are in block order)
         a.node_j = inst.node_ij.as<int32_t>() + M;
         a.rank_of = inst.node_rank.as<int32_t>();
-        a.bnd1 = r.b1.as<double>();
-        a.mean_x = o;
-        a.mean_y = o + M;
-        a.se_x = o + 2 * (size_t)M;
-        a.se_y = o + 3 * (size_t)M;
-        a.exit_frac = o + 4 * (size_t)M;
+        a.bnd1 = r.v.bnd1;
+        a.mean_x = o[0];
+        a.mean_y = o[1];
+        a.se_x = o[2];
+        a.se_y = o[3];
+        a.exit_frac = o[4];
         HIP_TRY(msdd::launch_interpolate(a, st));
     }
-    unsigned long long steps = 0;
-    if (dev_out) {
-        double *dst[5] = {dev_out->mean_x, dev_out->mean_y, dev_out->se_x, dev_out->se_y, dev_out->exit_frac};
-        for (int k = 0; k < 5; ++k)
-            if (dst[k] && M)
-                HIP_TRY(hipMemcpyAsync(dst[k], o + (size_t)k * M, (size_t)M * sizeof(double), hipMemcpyDeviceToDevice,
-                                       st));
-    } else {
+    if (!dev_out) {
         r.host_out.resize((size_t)5 * M);
-        if (M) HIP_TRY(hipMemcpyAsync(r.host_out.data(), o, r.host_out.size() * sizeof(double), hipMemcpyDeviceToHost, st));
+        if (M)
+            HIP_TRY(hipMemcpyAsync(r.host_out.data(), buf, r.host_out.size() * sizeof(double), hipMemcpyDeviceToHost, st));
     }
-    HIP_TRY(hipMemcpyAsync(&steps, r.steps_total.p, sizeof steps, hipMemcpyDeviceToHost, st));
-    HIP_TRY(hipStreamSynchronize(st));
-    r.executed_steps = steps;
+    static_assert(sizeof r.executed_steps == sizeof(unsigned long long), "step total");
+    HIP_TRY(hipMemcpyAsync(&r.executed_steps, r.steps_total.p, sizeof r.executed_steps, hipMemcpyDeviceToHost, st));
     return MESH_SDD_OK;
+}
+
+// The result arrays of a call that may be written while its inputs are still
+// read: those on the device, unless any result array of the call overlaps an
+// input or another result array (results then go through the host and are
+// copied out in the order of the requests, as they are for host arrays).
+std::vector<const mesh_sdd_result *> direct_results(const std::vector<const mesh_sdd_result *> &results,
+                                                    const std::vector<std::shared_ptr<Request>> &reqs,
+                                                    const std::vector<const mesh_sdd_step *> &dev_steps)
+{
+    struct Span {
+        const char *b, *e;
+        bool out;
+    };
+    std::vector<Span> spans;
+    std::vector<const mesh_sdd_result *> direct(results.size(), nullptr);
+    auto add = [&](const double *p, size_t n, bool out) {
+        const char *c = reinterpret_cast<const char *>(p);
+        if (p && n) spans.push_back(Span{c, c + n * sizeof(double), out});
+    };
+    for (size_t q = 0; q < results.size(); ++q) {
+        const mesh_sdd_desc &d = reqs[q]->inst->d;
+        const size_t n = (size_t)d.n_xi * d.n_eta, nb = 4 * (size_t)d.n_eta + 4 * (size_t)d.n_xi;
+        if (const mesh_sdd_step *s = dev_steps[q]) {
+            for (const double *p : {s->x_cur, s->y_cur}) add(p, n, false);
+            for (const double *p : {s->bnd_t0, s->bnd_t1}) add(p, nb, false);
+        }
+        const mesh_sdd_result *r = results[q];
+        if (!r || !r->outputs_on_device) continue;
+        direct[q] = r;
+        for (const double *p : {r->mean_x, r->mean_y, r->se_x, r->se_y, r->exit_frac}) add(p, (size_t)reqs[q]->M, true);
+    }
+    std::sort(spans.begin(), spans.end(), [](const Span &a, const Span &b) { return a.b < b.b; });
+    const char *end_all = nullptr, *end_out = nullptr;
+    for (const Span &s : spans) {
+        if (s.b < (s.out ? end_all : end_out)) return std::vector<const mesh_sdd_result *>(results.size(), nullptr);
+        end_all = std::max(end_all, s.e);
+        if (s.out) end_out = std::max(end_out, s.e);
+    }
+    return direct;
 }
 
 int copy_result(mesh_sdd_ctx *ctx, const Request &r, mesh_sdd_result *res)
@@ -1088,7 +1153,7 @@ int copy_result(mesh_sdd_ctx *ctx, const Request &r, mesh_sdd_result *res)
         return fail(MESH_SDD_E_INVAL, "result.struct_size %u != %zu", res->struct_size, sizeof(mesh_sdd_result));
     const int M = r.M;   // the instance may already be destroyed
     double *dst[5] = {res->mean_x, res->mean_y, res->se_x, res->se_y, res->exit_frac};
-    for (int k = 0; k < 5; ++k) {
+    for (int k = 0; k < 5 && !r.direct; ++k) {
         if (!dst[k]) continue;
         const double *src = r.host_out.data() + (size_t)k * M;
         if (res->outputs_on_device) {
@@ -1105,8 +1170,11 @@ int copy_result(mesh_sdd_ctx *ctx, const Request &r, mesh_sdd_result *res)
 }
 
 // Blocking path of one or several requests: FP32 ones share ONE launch.
+// `results` (may be empty): where the results go, for those that can be
+// written directly.
 int run_blocking(mesh_sdd_ctx *ctx, std::vector<std::shared_ptr<Request>> &reqs,
-                 const std::vector<const mesh_sdd_step *> &dev_steps, std::vector<int> &status)
+                 const std::vector<const mesh_sdd_step *> &dev_steps, std::vector<int> &status,
+                 const std::vector<const mesh_sdd_result *> &results = {})
 {
     std::lock_guard<std::mutex> g(ctx->gpu_mu);
     status.assign(reqs.size(), MESH_SDD_OK);
@@ -1115,6 +1183,10 @@ int run_blocking(mesh_sdd_ctx *ctx, std::vector<std::shared_ptr<Request>> &reqs,
     std::vector<const SampleSet *> sets;
     std::vector<size_t> fp32_reqs;
     size_t base = 0, limit = 0;   // items gathered, and in chunks of the tuned size
+    SyncOnFail guard{ctx->stream};   // an exception on the way leaves nothing in flight
+    const std::vector<const mesh_sdd_result *> direct =
+        results.empty() ? results : direct_results(results, reqs, dev_steps);
+    auto out_of = [&](size_t q) { return direct.empty() ? nullptr : direct[q]; };
     // one persistent launch over the FP32 requests gathered so far: the
     // bucket's shape for a launch of one instance, the multi-instance shape
     // otherwise
@@ -1122,14 +1194,19 @@ int run_blocking(mesh_sdd_ctx *ctx, std::vector<std::shared_ptr<Request>> &reqs,
         if (fp32_reqs.empty()) return;
         double ms = 0.0;
         const mesh_sdd_launch l = launch_for_group(ctx, fp32_reqs.size() == 1 ? &reqs[fp32_reqs[0]]->inst->d : nullptr);
-        int rc = run_fp32_launch(ctx, views, ranges, sets, l, &ms);
+        int rc = run_fp32_launch(ctx, views, ranges, sets, l);
         for (size_t q : fp32_reqs) {
             Request &r = *reqs[q];
-            int rq = rc;
-            if (rq == MESH_SDD_OK) rq = finalize_request(ctx, r);
-            r.device_ms = ms;
-            status[q] = rq;
-            if (rq != MESH_SDD_OK) r.error = g_last_error;
+            status[q] = rc == MESH_SDD_OK ? finalize_request(ctx, r, out_of(q)) : rc;
+            if (status[q] != MESH_SDD_OK) r.error = g_last_error;
+        }
+        rc = wait_launch(ctx, rc, &ms);
+        for (size_t q : fp32_reqs) {
+            reqs[q]->device_ms = ms;
+            if (rc != MESH_SDD_OK && status[q] == MESH_SDD_OK) {
+                status[q] = rc;
+                reqs[q]->error = g_last_error;
+            }
         }
         views.clear();
         ranges.clear();
@@ -1147,8 +1224,9 @@ int run_blocking(mesh_sdd_ctx *ctx, std::vector<std::shared_ptr<Request>> &reqs,
         }
         if (r.inst->d.precision == MESH_SDD_FP64) {
             double ms = 0.0;
-            rc = run_fp64_launch(ctx, r, &ms);
-            if (rc == MESH_SDD_OK) rc = finalize_request(ctx, r);
+            rc = run_fp64_launch(ctx, r);
+            if (rc == MESH_SDD_OK) rc = finalize_request(ctx, r, out_of(q));
+            rc = wait_launch(ctx, rc, &ms);
             r.device_ms = ms;
             status[q] = rc;
             if (rc != MESH_SDD_OK) r.error = g_last_error;
@@ -1169,6 +1247,7 @@ int run_blocking(mesh_sdd_ctx *ctx, std::vector<std::shared_ptr<Request>> &reqs,
         }
     }
     launch_group();
+    guard.armed = false;
     for (auto &r : reqs) release_request_buffers(*r);
     for (int s : status)
         if (s != MESH_SDD_OK) return s;
@@ -1360,8 +1439,9 @@ void scheduler_loop(mesh_sdd_ctx *ctx)
                     std::lock_guard<std::mutex> g(ctx->gpu_mu);
                     rc = stage_request(*r, nullptr);
                     if (rc == MESH_SDD_OK && r->inst->d.precision == MESH_SDD_FP64) {
-                        rc = run_fp64_launch(ctx, *r, &ms);
+                        rc = run_fp64_launch(ctx, *r);
                         if (rc == MESH_SDD_OK) rc = finalize_request(ctx, *r);
+                        rc = wait_launch(ctx, rc, &ms);
                         r->device_ms = ms;
                         release_request_buffers(*r);
                     }
@@ -1371,6 +1451,7 @@ void scheduler_loop(mesh_sdd_ctx *ctx)
                 if (empty_fp32) {
                     std::lock_guard<std::mutex> g(ctx->gpu_mu);
                     rc = finalize_request(ctx, *r);
+                    rc = wait_launch(ctx, rc, &ms);
                     release_request_buffers(*r);
                 }
                 std::lock_guard<std::mutex> lk(ctx->mu);
@@ -1415,37 +1496,47 @@ void scheduler_loop(mesh_sdd_ctx *ctx)
             // a tick of one request takes its bucket's shape, else the
             // multi-instance shape (launch_for_group takes ctx->mu itself)
             l = launch_for_group(ctx, taken.size() == 1 ? &taken.front().first->inst->d : nullptr);
+            // the requests whose last items this tick holds end with it (on an
+            // error all of them): their finalize kernels follow the launch, and
+            // one wait serves all
             double ms = 0.0;
             int rc;
+            std::vector<std::pair<std::shared_ptr<Request>, int>> ending;
+            std::vector<std::string> errors(taken.size());
+            ending.reserve(taken.size());
+            std::string err;
             {
                 std::lock_guard<std::mutex> g(ctx->gpu_mu);
-                rc = run_fp32_launch(ctx, views, ranges, sets, l, &ms);
+                SyncOnFail guard{ctx->stream};
+                rc = run_fp32_launch(ctx, views, ranges, sets, l);
+                for (auto &t : taken)
+                    if (rc != MESH_SDD_OK || t.first->done_items + t.second == t.first->n_items) {
+                        const int fr = rc == MESH_SDD_OK ? finalize_request(ctx, *t.first) : rc;
+                        if (fr != MESH_SDD_OK) errors[ending.size()] = g_last_error;
+                        ending.emplace_back(t.first, fr);
+                    }
+                const int wr = wait_launch(ctx, rc, &ms);
+                guard.armed = false;
+                if (rc == MESH_SDD_OK && wr != MESH_SDD_OK) {   // the launch failed: every request of the tick ends
+                    rc = wr;
+                    err = g_last_error;
+                    ending.clear();
+                    for (auto &t : taken) ending.emplace_back(t.first, rc);
+                    errors.assign(taken.size(), err);
+                }
+                for (auto &t : taken) drop_snapshots(*t.first);
+                for (auto &e : ending) release_request_buffers(*e.first);
             }
-            std::string err = rc == MESH_SDD_OK ? std::string() : g_last_error;
-            std::vector<std::shared_ptr<Request>> complete;
-            {
-                std::lock_guard<std::mutex> lk(ctx->mu);
-                ctx->busy_ms += ms;
-                for (auto &t : taken) {
-                    t.first->done_items += t.second;
-                    t.first->device_ms += ms;
-                    if (rc != MESH_SDD_OK || t.first->done_items == t.first->n_items) complete.push_back(t.first);
-                }
+            std::lock_guard<std::mutex> lk(ctx->mu);
+            ctx->busy_ms += ms;
+            for (auto &t : taken) {
+                t.first->done_items += t.second;
+                t.first->device_ms += ms;
             }
-            for (auto &r : complete) {
-                int fr = rc;
-                if (fr == MESH_SDD_OK) {
-                    std::lock_guard<std::mutex> g(ctx->gpu_mu);
-                    fr = finalize_request(ctx, *r);
-                }
-                std::string e2 = fr == MESH_SDD_OK ? std::string() : (rc != MESH_SDD_OK ? err : g_last_error);
-                {
-                    std::lock_guard<std::mutex> g(ctx->gpu_mu);
-                    release_request_buffers(*r);
-                }
-                std::lock_guard<std::mutex> lk(ctx->mu);
+            for (size_t k = 0; k < ending.size(); ++k) {
+                const std::shared_ptr<Request> &r = ending[k].first;
                 ctx->running.erase(std::find(ctx->running.begin(), ctx->running.end(), r));
-                finish_request(ctx, r, fr, e2);
+                finish_request(ctx, r, ending[k].second, errors[k]);
             }
         } catch (...) {
             // a host resource ran out inside the tick: the requests that were
@@ -1459,6 +1550,8 @@ void scheduler_loop(mesh_sdd_ctx *ctx)
             }
             {
                 std::lock_guard<std::mutex> g(ctx->gpu_mu);
+                (void)hipStreamSynchronize(ctx->stream);   // staged copies may still read the snapshots
+                ctx->launched = false;
                 for (auto &r : left) release_request_buffers(*r);
             }
             std::lock_guard<std::mutex> lk(ctx->mu);
@@ -1475,6 +1568,7 @@ void scheduler_loop(mesh_sdd_ctx *ctx)
     }
     {
         std::lock_guard<std::mutex> g(ctx->gpu_mu);
+        if (!left.empty()) (void)hipStreamSynchronize(ctx->stream);
         for (auto &r : left) release_request_buffers(*r);
     }
     std::lock_guard<std::mutex> lk(ctx->mu);
@@ -1546,9 +1640,7 @@ try {
     if (ctx->worker.joinable()) ctx->worker.join();
     (void)hipSetDevice(ctx->device);
     ctx->head.release();
-    ctx->views.release();
-    ctx->ranges.release();
-    ctx->jobs.release();
+    ctx->plan.release();
     ctx->ends.release();
     if (ctx->own_stream) (void)hipStreamDestroy(ctx->stream);
     delete ctx;
@@ -1836,7 +1928,9 @@ try {
         idx.push_back(q);
     }
     std::vector<int> rst;
-    int rc = reqs.empty() ? MESH_SDD_OK : run_blocking(ctx, reqs, dev_steps, rst);
+    std::vector<const mesh_sdd_result *> outs;
+    for (int q : idx) outs.push_back(&results[q]);
+    int rc = reqs.empty() ? MESH_SDD_OK : run_blocking(ctx, reqs, dev_steps, rst, outs);
     if (rc != MESH_SDD_OK && first_err == MESH_SDD_OK) {
         first_err = rc;
         first_msg = g_last_error;
@@ -1936,20 +2030,33 @@ try {
     arena.size = msdd_rt::scratch_capacity();
     InflightHold hold;
     hold.add(inst);
+    const std::vector<const mesh_sdd_result *> direct = direct_results({result}, {r}, {step});
+    SyncOnFail guard{ctx->stream};
     rc = stage_request(*r, step, &arena);
     double ms = 0.0;
     if (rc == MESH_SDD_OK) {
         if (fp64) {
-            rc = run_fp64_launch(ctx, *r, &ms, &arena);
+            rc = run_fp64_launch(ctx, *r, &arena);
         } else {
             std::vector<InstView> views{r->v};
             std::vector<WorkRange> ranges;
             std::vector<const SampleSet *> sets{r->ss};
             if (r->n_items) ranges.push_back(range_of(*r, 0, 0, 0, r->n_items));
-            rc = run_fp32_launch(ctx, views, ranges, sets, launch_for(ctx, d), &ms, &arena);
+            rc = run_fp32_launch(ctx, views, ranges, sets, launch_for(ctx, d), &arena);
         }
     }
-    if (rc == MESH_SDD_OK) rc = finalize_request(ctx, *r, result);
+    if (rc == MESH_SDD_OK) rc = finalize_request(ctx, *r, direct[0]);
+    rc = wait_launch(ctx, rc, &ms);
+    guard.armed = false;
+    if (rc == MESH_SDD_OK) {
+        r->device_ms = ms;
+        // result arrays that overlap an input or each other: copied out in turn
+        double *dst[5] = {result->mean_x, result->mean_y, result->se_x, result->se_y, result->exit_frac};
+        for (int k = 0; k < 5 && !r->direct; ++k)
+            if (dst[k] && inst->M)
+                HIP_TRY(hipMemcpy(dst[k], r->host_out.data() + (size_t)k * inst->M, (size_t)inst->M * sizeof(double),
+                                  hipMemcpyHostToDevice));
+    }
     release_request_buffers(*r);   // frees nothing: every piece is the arena's
     if (rc != MESH_SDD_OK) return rc;
     result->executed_path_steps = r->executed_steps;
@@ -2318,8 +2425,12 @@ try {
     std::lock_guard<std::mutex> g(ctx->gpu_mu);
     InflightHold hold;
     hold.add(inst);
+    SyncOnFail guard{ctx->stream};   // every way out waits for the copies and kernels below
     rc = stage_request(*r, step->inputs_on_device ? step : nullptr);
-    DevBuf dvx, dvy, dex, dsd, dst, dtr;
+    DevBuf dvx, dvy, dex, dsd, dst, dtr, view;
+    if (rc == MESH_SDD_OK && (view.alloc(sizeof(InstView)) ||
+                              hipMemcpy(view.p, &r->v, sizeof r->v, hipMemcpyHostToDevice) != hipSuccess))
+        rc = fail(MESH_SDD_E_NOMEM, "device allocation failed");
     if (rc == MESH_SDD_OK && count) {
         const size_t trace_n = trace ? (size_t)count * 4 * inst->d.K : 0;
         if (dvx.alloc(count * 8) || dvy.alloc(count * 8) || dex.alloc(count * 4) || dsd.alloc(count * 4) ||
@@ -2330,7 +2441,7 @@ try {
             hipError_t e = hipSuccess;
             if (trace) e = hipMemcpyAsync(dtr.p, trace, trace_n * 8, hipMemcpyHostToDevice, s);
             if (e == hipSuccess)
-                e = msdd::launch_debug_paths(r->view.as<InstView>(), inst->d.precision == MESH_SDD_FP64,
+                e = msdd::launch_debug_paths(view.as<InstView>(), inst->d.precision == MESH_SDD_FP64,
                                              (uint32_t)r->ss->pos_of_rank[(size_t)node_rank], (uint32_t)p_begin,
                                              count, dvx.as<double>(),
                                              dvy.as<double>(), dex.as<int32_t>(), dsd.as<int32_t>(),
@@ -2345,6 +2456,7 @@ try {
             if (e != hipSuccess) rc = fail(MESH_SDD_E_DEVICE, "debug path kernel failed: %s", hipGetErrorString(e));
         }
     }
+    (void)hipStreamSynchronize(ctx->stream);
     release_request_buffers(*r);
     return rc;
 } catch (...) {

@@ -185,9 +185,10 @@ struct TimerEvents {
     TimerEvents() = default;
     TimerEvents(const TimerEvents &) = delete;
     TimerEvents &operator=(const TimerEvents &) = delete;
-    hipError_t create()
+    hipError_t create()   // once; later calls keep the events
     {
-        hipError_t e = hipEventCreate(&e0);
+        if (e0 && e1) return hipSuccess;
+        hipError_t e = e0 ? hipSuccess : hipEventCreate(&e0);
         if (e != hipSuccess) {
             e0 = nullptr;
             return e;
@@ -280,9 +281,10 @@ struct Request {
     int tuned_chunk = 0;           // the launch shape's; chunk_paths is smaller in small requests
     // host snapshots of host inputs
     std::vector<double> hx, hy, hb0, hb1;
-    // device buffers owned by the request
+    // device buffers owned by the request (x64 .. b1: copies of host inputs;
+    // a blocking call reads device inputs where they are)
     DevBuf x64, y64, b0, b1, xpad, ypad, xpad_f, ypad_f, b0f, b1f;
-    DevBuf view, partials, spans, out, steps_total;
+    DevBuf partials, out, steps_total;
     InstView v{};
     size_t n_items = 0;            // FP32 work items (node-major, see WorkRange)
     size_t limit_items = 0;        // the same in chunks of the tuned size (what the launch limits count)
@@ -294,6 +296,7 @@ struct Request {
     int status = MESH_SDD_PENDING;
     std::string error;
     std::vector<double> host_out;  // 5 * M
+    bool direct = false;           // the results were written to the caller's device arrays
     uint64_t executed_steps = 0;
     double device_ms = 0.0;
     Clock::time_point t_submit, t_done;
@@ -335,8 +338,10 @@ struct mesh_sdd_ctx {
 
     DevPool pool;        // recycled request buffers (declared before users)
     std::mutex gpu_mu;   // serialises use of the stream and the launch scratch below
-    DevBuf head, views, ranges;
-    DevBuf jobs;         // job list of windowed launches (grow-only)
+    DevBuf head, plan;   // work counters; views, ranges and jobs of a launch (grow-only)
+    std::vector<char> plan_host;   // what is being copied to `plan`: kept until the launch is waited for
+    msdd_rt::TimerEvents ev;       // timing of the launch in flight,
+    bool launched = false;         // if there is one
     DevBuf ends;         // item end states of the LDS table and window launches (grow-only)
 
     std::mutex mu;       // guards everything below
