@@ -1113,12 +1113,12 @@ struct Src64Job {
 // (path_fp64.hpp): 1, the whole table in LDS, taken where it fits; 2, windows
 // of it per job, as in paths_fp32_win; 0, global memory, for a launch that has
 // no room for its job list (the no-allocation solve).
-// Bound: VALU issue (217 vector instructions per path-step, 90 % of the issue
-// slots).  The form before it -- one thread per path, the library's log,
+// Bound: VALU issue (about 200 vector instructions per path-step, 90 % of the
+// issue slots).  The form before it -- one thread per path, the library's log,
 // sincospi, sqrt and exp, twelve 8-byte gathers per substep, no lane refill --
 // took about 680 slots and filled the texture path as well: 129^2 bump,
-// 753 nodes, N = 10^4, K = 500: 54.4 -> 22.2 ms; 33^2, 31 nodes, N = 10^4:
-// 2.67 -> 1.6 ms (4844 items on 4096 waves: the second round is mostly empty).
+// 753 nodes, N = 10^4, K = 500: 54.4 -> 20.8 ms; 33^2, 31 nodes, N = 10^4:
+// 2.5 -> 1.35 ms (4844 items on 4096 waves: the second round is mostly empty).
 template <int PER, int MODE>
 __global__ __launch_bounds__(kTableBlock) void paths_fp64(Fp64View V, uint32_t n_paths, uint32_t chunks)
 {
