@@ -206,7 +206,9 @@ struct Win {
 // record; 2: the LDS node table (rho, dt rho_xi interleaved); 3: the LDS
 // window when the cell lies inside it, else the cell record; 4: as 3, with
 // dt rho_eta at the corners of the cells inside the window from LDS too; 5:
-// as 4, for a square window of kWin3Side nodes.
+// as 4, for a square window of kWin3Side nodes; 6: the LDS node table of all
+// three fields, each with its difference to the next node along xi (as
+// bilerp rounds it), in small grids.
 // The values are the same in every case, so the results are identical.
 template <int TAB>
 __device__ __forceinline__ int substep_f32(PathF &P, const ConstF &C, uint32_t wa, uint32_t wb, uint32_t wc,
@@ -251,6 +253,15 @@ __device__ __forceinline__ int substep_f32(PathF &P, const ConstF &C, uint32_t w
         const float2 c00 = t2[0], c10 = t2[1], c01 = t2[C.n_xi], c11 = t2[C.n_xi + 1];
         r00 = c00.x, r10 = c10.x, r01 = c01.x, r11 = c11.x;
         g00 = c00.y, g10 = c10.y, g01 = c01.y, g11 = c11.y;
+    } else if (TAB == 6) {
+        // three pairs (value, difference) per node; row cy + 1 is n_xi nodes on
+        const uint32_t off = __umul24((uint32_t)cy, (uint32_t)C.n_xi * 24u) + __umul24((uint32_t)cx, 24u);
+        const float2 *t2 = (const float2 *)((const char *)tab + off);
+        const float2 *u2 = t2 + 3 * C.n_xi;
+        const float2 ra = t2[0], rb = u2[0], ga = t2[1], gb = u2[1], ea = t2[2], eb = u2[2];
+        r00 = ra.x, r10 = ra.y, r01 = rb.x, r11 = rb.y;
+        g00 = ga.x, g10 = ga.y, g01 = gb.x, g11 = gb.y;
+        G.x = ea.x, G.y = ea.y, G.z = eb.x, G.w = eb.y;
     } else if (TAB >= 3) {
         // Lanes outside the window read the cell record, which keeps its corner
         // values in the window's order (rho, dt rho_xi per node, row by row):
@@ -304,9 +315,10 @@ __device__ __forceinline__ int substep_f32(PathF &P, const ConstF &C, uint32_t w
     // plane holds it in the difference form of bilerp_d, the record (and the
     // three-field window) as corner values
     if (TAB < 3) G = TAB == 2 ? *coef : cell[2];
-    const float rho = bilerp(tx, ty, r00, r10, r01, r11);
-    const float gx = bilerp(tx, ty, g00, g10, g01, g11);
-    const float gy = TAB == 2 || TAB == 3 ? bilerp_d(tx, ty, G.x, G.y, G.z, G.w) : bilerp(tx, ty, G.x, G.y, G.z, G.w);
+    const float rho = TAB == 6 ? bilerp_d(tx, ty, r00, r10, r01, r11) : bilerp(tx, ty, r00, r10, r01, r11);
+    const float gx = TAB == 6 ? bilerp_d(tx, ty, g00, g10, g01, g11) : bilerp(tx, ty, g00, g10, g01, g11);
+    const float gy = TAB == 2 || TAB == 3 || TAB == 6 ? bilerp_d(tx, ty, G.x, G.y, G.z, G.w)
+                                                      : bilerp(tx, ty, G.x, G.y, G.z, G.w);
     const float inv_rho = __builtin_amdgcn_rcpf(rho);
 
     // a5: Euler-Maruyama, x + (grad rho / rho) dt + sqrt(2 dt) N.
@@ -477,7 +489,7 @@ struct Refill {
 
 // Advances one path by quarters of four substeps: each quarter draws its
 // three Philox blocks at once (words 3s..3s+2 for substep s of the quarter,
-// block 3 (k / 4) onwards).  The LDS table and window kernels (TAB 2, 3, 4)
+// block 3 (k / 4) onwards).  The LDS table and window kernels (TAB > 0)
 // run up to rf.quarters quarters and leave after a quarter once fewer than
 // rf.lanes of the wave's 64 lanes still have a path in flight, so the
 // caller's refill and item bookkeeping runs only when lanes are idle.  The
@@ -887,7 +899,13 @@ __device__ __forceinline__ void item_loop_kind(int kind, Src &src, uint32_t n_it
 // interleaved; the bilinear interpolation then reads those corner values
 // there instead of from the cell record (the same values, so the results are
 // identical), which takes two of the three L1 gathers of a substep off the
-// texture path.  The table fills the LDS, so the waves keep the
+// texture path.  TAB 6, for grids of at most kDiffNodes nodes: all three
+// fields, each with its difference to the next node along xi, 24 B per node.
+// A substep then gathers nothing from memory, which shortens the chain that a
+// wave of a small launch waits for, and interpolates in six VALU
+// instructions fewer (33^2, kernel time at N = 10^4, 2 10^4, 3 10^4: 0.494,
+// 0.904, 1.156 ms with TAB 2, 0.480, 0.863, 1.124 with TAB 6; 65^2, N = 3700:
+// 1.644 and 1.560).  The table fills the LDS, so the waves keep the
 // end states of their items in `ends` (global memory, 6 * cap words per
 // wave, room for `end_waves` waves; read back by the same wave only).
 // PER >= 0 (single-instance launches): the instance's path kind as
@@ -913,7 +931,18 @@ __global__ __launch_bounds__(BLOCK) void paths_fp32(const InstView *__restrict__
         const GLOBAL float *src = gptr(insts[0].rho_f);
         const GLOBAL float *srx = gptr(insts[0].rhox_f);
         float2 *t2 = (float2 *)tab;
-        for (int q = threadIdx.x; q < n; q += BLOCK) t2[q] = make_float2(src[q], srx[q]);
+        if (TAB == 6) {
+            const GLOBAL float *sry = gptr(insts[0].rhoy_f);
+            for (int q = threadIdx.x; q < n; q += BLOCK) {
+                const int e = q + 1 < n ? q + 1 : q;   // a row's last node starts no cell: its difference is not read
+                const float r = src[q], gx = srx[q], gy = sry[q];
+                t2[3 * q] = make_float2(r, src[e] - r);
+                t2[3 * q + 1] = make_float2(gx, srx[e] - gx);
+                t2[3 * q + 2] = make_float2(gy, sry[e] - gy);
+            }
+        } else {
+            for (int q = threadIdx.x; q < n; q += BLOCK) t2[q] = make_float2(src[q], srx[q]);
+        }
         __syncthreads();
     }
 
@@ -1647,6 +1676,22 @@ static void launch_table(int grid, size_t lds, hipStream_t s, const InstView *in
                        n_items, head, cap, ends, end_waves, rf);
 }
 
+template <int TAB>
+static void launch_table_kind(int kind, int grid, size_t lds, hipStream_t s, const InstView *insts,
+                              const WorkRange *ranges, uint32_t n_items, uint32_t *head, uint32_t cap, float *ends,
+                              uint32_t end_waves, Refill rf)
+{
+    switch (kind) {
+    case 0: launch_table<TAB, 0>(grid, lds, s, insts, ranges, n_items, head, cap, ends, end_waves, rf); break;
+    case 1: launch_table<TAB, 1>(grid, lds, s, insts, ranges, n_items, head, cap, ends, end_waves, rf); break;
+    case 2: launch_table<TAB, 2>(grid, lds, s, insts, ranges, n_items, head, cap, ends, end_waves, rf); break;
+    case 4: launch_table<TAB, 4>(grid, lds, s, insts, ranges, n_items, head, cap, ends, end_waves, rf); break;
+    case 5: launch_table<TAB, 5>(grid, lds, s, insts, ranges, n_items, head, cap, ends, end_waves, rf); break;
+    case 6: launch_table<TAB, 6>(grid, lds, s, insts, ranges, n_items, head, cap, ends, end_waves, rf); break;
+    default: launch_table<TAB, 3>(grid, lds, s, insts, ranges, n_items, head, cap, ends, end_waves, rf); break;
+    }
+}
+
 hipError_t launch_paths_fp32_table(const InstView *insts, const WorkRange *ranges, uint32_t n_items, uint32_t *head,
                                    uint32_t cap, int level, int kind, int n_nodes, int grid, float *ends,
                                    uint32_t end_waves, uint32_t refill_lanes, uint32_t max_quarters, hipStream_t s)
@@ -1657,17 +1702,12 @@ hipError_t launch_paths_fp32_table(const InstView *insts, const WorkRange *range
     if ((size_t)grid * (kTableBlock / 64) > end_waves || level != 2 || kind < 0 || kind > 6 ||
         refill_lanes < 1 || refill_lanes > 64 || max_quarters < 1 || max_quarters > 64)
         return hipErrorInvalidValue;
-    const size_t lds = paths_fp32_table_lds_bytes(level, n_nodes);
     const Refill rf{refill_lanes, max_quarters};
-    switch (kind) {
-    case 0: launch_table<2, 0>(grid, lds, s, insts, ranges, n_items, head, cap, ends, end_waves, rf); break;
-    case 1: launch_table<2, 1>(grid, lds, s, insts, ranges, n_items, head, cap, ends, end_waves, rf); break;
-    case 2: launch_table<2, 2>(grid, lds, s, insts, ranges, n_items, head, cap, ends, end_waves, rf); break;
-    case 4: launch_table<2, 4>(grid, lds, s, insts, ranges, n_items, head, cap, ends, end_waves, rf); break;
-    case 5: launch_table<2, 5>(grid, lds, s, insts, ranges, n_items, head, cap, ends, end_waves, rf); break;
-    case 6: launch_table<2, 6>(grid, lds, s, insts, ranges, n_items, head, cap, ends, end_waves, rf); break;
-    default: launch_table<2, 3>(grid, lds, s, insts, ranges, n_items, head, cap, ends, end_waves, rf); break;
-    }
+    if (n_nodes <= kDiffNodes)
+        launch_table_kind<6>(kind, grid, (size_t)n_nodes * 24u, s, insts, ranges, n_items, head, cap, ends, end_waves, rf);
+    else
+        launch_table_kind<2>(kind, grid, paths_fp32_table_lds_bytes(level, n_nodes), s, insts, ranges, n_items, head,
+                             cap, ends, end_waves, rf);
     return hipGetLastError();
 }
 
@@ -1677,8 +1717,11 @@ int paths_fp32_table_blocks_per_cu(int level, int n_nodes)
     int n = 0;
     const size_t lds = paths_fp32_table_lds_bytes(level, n_nodes);
     if (level != 2) return 0;
-    const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, paths_fp32<kTableBlock, 2, 0>, kTableBlock,
-                                                                      lds);
+    const hipError_t e =
+        n_nodes <= kDiffNodes
+            ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, paths_fp32<kTableBlock, 6, 0>, kTableBlock,
+                                                           (size_t)n_nodes * 24u)
+            : hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, paths_fp32<kTableBlock, 2, 0>, kTableBlock, lds);
     return e == hipSuccess ? n : 0;
 }
 

@@ -46,10 +46,12 @@ size_t paths_fp32_lds_bytes(int block, uint32_t cap);
 // 1024-thread workgroup (16 waves, 4 per SIMD) copies that instance's FP32
 // node tables of rho and dt rho_xi into LDS, interleaved (level 2, the only
 // level; n_nodes * 8 bytes), and reads those corner values there instead of
-// from the cell records; `ends` holds the waves' item end
+// from the cell records; up to kDiffNodes nodes, all three fields with their
+// differences along xi (n_nodes * 24 bytes); `ends` holds the waves' item end
 // states (6 * cap floats per wave, room for `end_waves` >= grid * 16 waves).
 // Results are identical to launch_paths_fp32's.
 constexpr int kTableBlock = 1024;
+constexpr int kDiffNodes = 160 * 1024 / 24;   // grids whose three fields fit the LDS with their differences along xi
 size_t paths_fp32_table_lds_bytes(int level, int n_nodes);
 // `kind` = path_kind of the instance, 0..6 (compiled in).
 // refill_lanes, max_quarters (1..64): a wave leaves its stepping loop for the
