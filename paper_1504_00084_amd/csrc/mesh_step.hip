@@ -887,6 +887,8 @@ static void launch_sub(const MeshStepArgs &a, const SubShape &h, double *x_new, 
         hipLaunchKernelGGL((subdomain_lds_kernel<P2, 8>), grid, block, lds, s, a, h.first_bnd, x_new, y_new);
     else if (h.rows == 4)
         hipLaunchKernelGGL((subdomain_lds_kernel<P2, 4>), grid, block, lds, s, a, h.first_bnd, x_new, y_new);
+    else if (h.rows == 2)
+        hipLaunchKernelGGL((subdomain_lds_kernel<P2, 2>), grid, block, lds, s, a, h.first_bnd, x_new, y_new);
     else
         hipLaunchKernelGGL((subdomain_lds_kernel<P2, 1>), grid, block, lds, s, a, h.first_bnd, x_new, y_new);
 }

@@ -65,7 +65,8 @@ def test_single_domain_equals_oracle(M, ctx, case):
 
 # nx, ny, sub_xi, sub_eta, per_xi, per_eta, substeps
 BOXES = [(9, 9, 8, 2, 0, 0, 5), (9, 25, 2, 8, 0, 0, 9), (33, 33, 4, 4, 1, 1, 11), (37, 25, 4, 3, 0, 1, 8),
-         (129, 65, 2, 1, 0, 0, 10), (73, 145, 1, 2, 0, 0, 9), (67, 23, 2, 2, 1, 0, 17), (97, 97, 1, 1, 0, 0, 3)]
+         (129, 65, 2, 1, 0, 0, 10), (73, 145, 1, 2, 0, 0, 9), (67, 23, 2, 2, 1, 0, 17), (97, 97, 1, 1, 0, 0, 3),
+         (69, 31, 2, 2, 1, 1, 9), (21, 73, 2, 2, 1, 1, 9)]   # two rows of a column per thread
 
 
 @pytest.mark.parametrize("solver", [0, 2], ids=["auto", "sweep"])
