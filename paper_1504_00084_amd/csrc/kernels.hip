@@ -535,10 +535,39 @@ __device__ __forceinline__ int group_f32(PathF &P, const ConstF &C, uint32_t pat
     return side;
 }
 
+// The value of another lane, by a data-parallel move inside a row of 16 lanes.
+template <int CTRL>
+__device__ __forceinline__ double dpp_f64(double v)
+{
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xF, 0xF, true);
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xF, 0xF, true);
+    return __hiloint2double(hi, lo);
+}
+
+// Sum over the wave, in every lane: the butterfly over lane distances 32, 16,
+// 8, 4, 2, 1.  The halves and rows of 16 lanes are added by the swap
+// instructions, the rest by moves within a row: rotations by 8 and 4 (after
+// distance 8 every lane holds the sum of its class modulo 8, so a rotation
+// by 4 brings the value of distance 4) and quad permutations.  No LDS
+// permutation: 24 of them and their waits per reduction of four sums of an item,
+// twice as many 32-bit ones.
 __device__ __forceinline__ double wave_sum(double v)
 {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
+    typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+    {
+        const u32x2 lo = __builtin_amdgcn_permlane32_swap((unsigned)__double2loint(v), (unsigned)__double2loint(v), false, false);
+        const u32x2 hi = __builtin_amdgcn_permlane32_swap((unsigned)__double2hiint(v), (unsigned)__double2hiint(v), false, false);
+        v = __hiloint2double((int)hi.x, (int)lo.x) + __hiloint2double((int)hi.y, (int)lo.y);
+    }
+    {
+        const u32x2 lo = __builtin_amdgcn_permlane16_swap((unsigned)__double2loint(v), (unsigned)__double2loint(v), false, false);
+        const u32x2 hi = __builtin_amdgcn_permlane16_swap((unsigned)__double2hiint(v), (unsigned)__double2hiint(v), false, false);
+        v = __hiloint2double((int)hi.x, (int)lo.x) + __hiloint2double((int)hi.y, (int)lo.y);
+    }
+    v += dpp_f64<0x128>(v);   // row_ror:8
+    v += dpp_f64<0x124>(v);   // row_ror:4
+    v += dpp_f64<0x4E>(v);    // quad_perm [2, 3, 0, 1]
+    v += dpp_f64<0xB1>(v);    // quad_perm [1, 0, 3, 2]
     return v;
 }
 
@@ -654,10 +683,12 @@ __device__ __forceinline__ void stored_value(const float *b, uint32_t cap, uint3
 // Values and fixed-order reduction of one drained item: lane l evaluates
 // the paths l, l + 64, ... from their end states, v - v_ref is rounded to
 // FP32 and summed in FP64, then the lanes' sums and the exit and step counts
-// are combined by butterflies; every lane stores the identical totals.
+// are combined by butterflies; every lane stores the identical totals.  In a
+// sliced request (items of at most 64 paths) the lanes store their v - v_ref
+// instead, and the finalize sums them.
 __device__ __forceinline__ void finish_item(const float *buf, uint32_t cap, uint32_t count, int lane, uint32_t exits,
                                             unsigned long long steps, const InstView &I, const ConstF &C, double rx,
-                                            double ry, GLOBAL Partial *out)
+                                            double ry, uint32_t part)
 {
     double s1x = 0.0, s2x = 0.0, s1y = 0.0, s2y = 0.0;
     for (uint32_t j = (uint32_t)lane; j < count; j += 64u) {
@@ -669,12 +700,21 @@ __device__ __forceinline__ void finish_item(const float *buf, uint32_t cap, uint
         s1y += dy;
         s2y = fma(dy, dy, s2y);
     }
+    const unsigned long long ex = wave_sum_u64((unsigned long long)exits);
+    const unsigned long long st = wave_sum_u64(steps);
+    if (I.slices) {
+        GLOBAL SliceRec *rec = (GLOBAL SliceRec *)gptr_rw(I.partials) + part;
+        rec->dx[lane] = (float)s1x;   // the path's value, or 0
+        rec->dy[lane] = (float)s1y;
+        rec->exits = ex;
+        rec->steps = st;
+        return;
+    }
+    GLOBAL Partial *out = gptr_rw(I.partials) + part;
     s1x = wave_sum(s1x);
     s2x = wave_sum(s2x);
     s1y = wave_sum(s1y);
     s2y = wave_sum(s2y);
-    const unsigned long long ex = wave_sum_u64((unsigned long long)exits);
-    const unsigned long long st = wave_sum_u64(steps);
     out->s1x = s1x;
     out->s2x = s2x;
     out->s1y = s1y;
@@ -862,13 +902,13 @@ __device__ __forceinline__ void item_loop(Src &src, uint32_t n_items, const Inst
         rem1 -= (uint32_t)__popcll(end_mask & in1);
         // reduce and write the items whose paths have all ended
         if (act0 && rem0 == 0u && !(issuing && cur == 0u)) {
-            finish_item(buf, cap, cnt0, lane, ex0, st0, *Ip, C, rx0, ry0, gptr_rw(Ip->partials) + part0);
+            finish_item(buf, cap, cnt0, lane, ex0, st0, *Ip, C, rx0, ry0, part0);
             ex0 = 0;
             st0 = 0;
             act0 = 0u;
         }
         if (act1 && rem1 == 0u && !(issuing && cur == 1u)) {
-            finish_item(buf + 3u * cap, cap, cnt1, lane, ex1, st1, *Ip, C, rx1, ry1, gptr_rw(Ip->partials) + part1);
+            finish_item(buf + 3u * cap, cap, cnt1, lane, ex1, st1, *Ip, C, rx1, ry1, part1);
             ex1 = 0;
             st1 = 0;
             act1 = 0u;
@@ -1219,45 +1259,98 @@ __global__ __launch_bounds__(kTableBlock) void paths_fp64(Fp64View V, uint32_t n
 // ---------------------------------------------------------------------------
 // Finalize (a9)
 // ---------------------------------------------------------------------------
-// One wave per node: lane l takes the partials l, l + 64, ... in that order,
-// the lanes are combined by butterflies, so the order of the sums is fixed by
-// the chunk count.  (With one thread per node the 79 dependent 48-byte loads
-// of a node at N = 10^4 took 41 us on the 129^2 bump, 30 us on the five-ring
-// mesh; now 6 and 4.)  The step total takes one atomic per workgroup, of
-// which there are at most kFinalBlocks: each costs about 10 ns on its one
-// address.
-constexpr int kFinalWaves = 4, kFinalBlocks = 512;
+// W waves per node (final_waves), 16 / W nodes per workgroup.  The partials are
+// brought to LDS 64 chunks at a time and added chunk by chunk, one lane per
+// sum: the order of one thread that walks the chunks, without its 48-byte
+// loads one after the other (129^2 bump at N = 10^4, 79 chunks: 41 us).  In a
+// sliced request a wave first makes each chunk's partial as finish_item does
+// for a whole chunk: lane l takes the paths l, l + 64, ... of the chunk (0 where
+// the last slice has none, which changes no sum), then the butterflies.  The
+// step total takes one atomic per workgroup, of which there are at most
+// kFinalBlocks: each costs about 10 ns on its one address.
+constexpr int kFinalWaves = 16, kFinalBlocks = 512, kFinalTile = 64;
 __global__ __launch_bounds__(64 * kFinalWaves) void finalize_kernel(
-    const Partial *__restrict__ partials, uint32_t chunks, InstView I, uint32_t M, uint64_t n_paths, double *mean_x,
-    double *mean_y, double *se_x, double *se_y, double *exit_frac, unsigned long long *steps_total)
+    const Partial *__restrict__ partials, uint32_t items, int W, InstView I, uint32_t M, uint64_t n_paths,
+    double *mean_x, double *mean_y, double *se_x, double *se_y, double *exit_frac, unsigned long long *steps_total)
 {
-    __shared__ unsigned long long wave_steps[kFinalWaves];
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    __shared__ double tiles[kFinalWaves][kFinalTile][4], total[kFinalWaves][4];
+    __shared__ unsigned long long wave_ex[kFinalWaves], wave_st[kFinalWaves];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int g = wave / W, w = wave % W;              // node of the workgroup, wave of the node
+    const int t = w * 64 + lane, nt = W * 64;          // thread of the node
+    const uint32_t per_block = (uint32_t)(kFinalWaves / W);
+    double(*tile)[4] = tiles[g];
     const double N = (double)n_paths;
-    unsigned long long my_steps = 0;
-    for (uint32_t node = blockIdx.x * kFinalWaves + w; node < M; node += gridDim.x * kFinalWaves) {
-        double s1x = 0.0, s2x = 0.0, s1y = 0.0, s2y = 0.0;
-        unsigned long long ex = 0;
-        for (uint32_t c = (uint32_t)lane; c < chunks; c += 64u) {
-            const Partial &p = partials[(size_t)node * chunks + c];
-            s1x += p.s1x;
-            s2x += p.s2x;
-            s1y += p.s1y;
-            s2y += p.s2y;
-            ex += p.exits;
-            my_steps += p.steps;
+    const uint32_t chunks = I.slices ? (items + I.slices - 1) / I.slices : items;
+    unsigned long long all_steps = 0;
+    for (uint32_t base = blockIdx.x * per_block; base < M; base += gridDim.x * per_block) {
+        const uint32_t node = base + (uint32_t)g;
+        const bool mine = node < M;
+        double s = 0.0;   // threads 0..3 of the node: s1x, s2x, s1y, s2y
+        unsigned long long ex = 0, st = 0;
+        for (uint32_t c0 = 0; c0 < chunks; c0 += kFinalTile) {
+            const uint32_t nc = mine ? min((uint32_t)kFinalTile, chunks - c0) : 0u;
+            if (I.slices) {
+                const SliceRec *recs = (const SliceRec *)partials + (size_t)node * items;
+                for (uint32_t c = (uint32_t)w; c < nc; c += (uint32_t)W) {
+                    double s1x = 0.0, s2x = 0.0, s1y = 0.0, s2y = 0.0;
+                    const uint32_t q0 = (c0 + c) * I.slices, q1 = min(items, q0 + I.slices);
+#pragma unroll 2
+                    for (uint32_t q = q0; q < q1; ++q) {
+                        const SliceRec &r = recs[q];
+                        const double dx = (double)r.dx[lane], dy = (double)r.dy[lane];
+                        s1x += dx;
+                        s2x = fma(dx, dx, s2x);
+                        s1y += dy;
+                        s2y = fma(dy, dy, s2y);
+                        if (lane == 0) {
+                            ex += r.exits;
+                            st += r.steps;
+                        }
+                    }
+                    s1x = wave_sum(s1x);
+                    s2x = wave_sum(s2x);
+                    s1y = wave_sum(s1y);
+                    s2y = wave_sum(s2y);
+                    if (lane == 0) {
+                        tile[c][0] = s1x;
+                        tile[c][1] = s2x;
+                        tile[c][2] = s1y;
+                        tile[c][3] = s2y;
+                    }
+                }
+            } else {
+                const Partial *p = partials + (size_t)node * items + c0;
+                for (uint32_t k = (uint32_t)t; k < 4u * nc; k += (uint32_t)nt) tile[k >> 2][k & 3u] = (&p[k >> 2].s1x)[k & 3u];
+                for (uint32_t c = (uint32_t)t; c < nc; c += (uint32_t)nt) {
+                    ex += p[c].exits;
+                    st += p[c].steps;
+                }
+            }
+            __syncthreads();
+            if (t < 4) {
+#pragma unroll 8
+                for (uint32_t c = 0; c < nc; ++c) s += tile[c][t];
+            }
+            __syncthreads();
         }
-        s1x = wave_sum(s1x);
-        s2x = wave_sum(s2x);
-        s1y = wave_sum(s1y);
-        s2y = wave_sum(s2y);
         ex = wave_sum_u64(ex);
+        st = wave_sum_u64(st);
+        if (t < 4) total[g][t] = s;
         if (lane == 0) {
+            wave_ex[wave] = ex;
+            wave_st[wave] = st;
+        }
+        __syncthreads();
+        if (t == 0 && mine) {
+            const double s1x = total[g][0], s2x = total[g][1], s1y = total[g][2], s2y = total[g][3];
+            ex = 0;
+            for (int k = wave; k < wave + W; ++k) ex += wave_ex[k];
             const int i0 = I.node_i[node], j0 = I.node_j[node];
             const uint32_t r = I.node_r[node];
-            const size_t g = (size_t)j0 * (I.n_xi + 2) + i0;
-            mean_x[r] = I.x64[g] + s1x / N;
-            mean_y[r] = I.y64[g] + s1y / N;
+            const size_t at = (size_t)j0 * (I.n_xi + 2) + i0;
+            mean_x[r] = I.x64[at] + s1x / N;
+            mean_y[r] = I.y64[at] + s1y / N;
             if (n_paths > 1) {
                 const double vx = (s2x - s1x * s1x / N) / (N - 1.0);
                 const double vy = (s2y - s1y * s1y / N) / (N - 1.0);
@@ -1269,14 +1362,19 @@ __global__ __launch_bounds__(64 * kFinalWaves) void finalize_kernel(
             }
             exit_frac[r] = (double)ex / N;
         }
+        if (threadIdx.x == 0)
+            for (int k = 0; k < kFinalWaves; ++k) all_steps += wave_st[k];
+        __syncthreads();   // total and the wave counts are read
     }
-    my_steps = wave_sum_u64(my_steps);
-    if (lane == 0) wave_steps[w] = my_steps;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int k = 1; k < kFinalWaves; ++k) my_steps += wave_steps[k];
-        if (my_steps) atomicAdd(steps_total, my_steps);
-    }
+    if (threadIdx.x == 0 && all_steps) atomicAdd(steps_total, all_steps);
+}
+
+// Waves per node of the finalize: one where a wave brings the partials of all
+// chunks in two loads; four bring those of a tile in one; four or sixteen share
+// the chunks of a sliced node.
+static int final_waves(uint32_t chunks, bool sliced)
+{
+    return sliced ? (chunks > 16u ? 16 : chunks > 4u ? 4 : 1) : chunks > 32u ? 4 : 1;
 }
 
 // ---------------------------------------------------------------------------
@@ -1812,9 +1910,11 @@ hipError_t launch_finalize(const Partial *partials, const NodeSpan *spans, const
                            double *exit_frac, unsigned long long *steps_total, hipStream_t s)
 {
     if (M == 0) return hipSuccess;
-    const unsigned blocks = blocks_for(M, kFinalWaves);
-    hipLaunchKernelGGL(finalize_kernel, dim3(blocks < kFinalBlocks ? blocks : kFinalBlocks), dim3(64 * kFinalWaves), 0, s, partials, spans->count, *inst, M, n_paths,
-                       mean_x, mean_y, se_x, se_y, exit_frac, steps_total);
+    const uint32_t items = spans->count;
+    const int W = final_waves(inst->slices ? (items + inst->slices - 1) / inst->slices : items, inst->slices != 0);
+    const unsigned blocks = blocks_for(M, kFinalWaves / W);
+    hipLaunchKernelGGL(finalize_kernel, dim3(blocks < kFinalBlocks ? blocks : kFinalBlocks), dim3(64 * kFinalWaves), 0, s,
+                       partials, items, W, *inst, M, n_paths, mean_x, mean_y, se_x, se_y, exit_frac, steps_total);
     return hipGetLastError();
 }
 

@@ -57,6 +57,16 @@ struct Partial {
     unsigned long long steps;
 };
 
+// What an item of a sliced request writes instead: v - v_ref of its up to 64
+// paths, one per lane (FP32, as the sums take them).  The finalize sums the
+// slices of a chunk as one item of the whole chunk would, so the results do
+// not depend on how a request is cut into items.
+struct SliceRec {
+    float dx[64], dy[64];
+    unsigned long long exits;
+    unsigned long long steps;
+};
+
 // One problem instance as the kernels see it.  All pointers are device
 // addresses owned by the instance.  Grids are row-major [n_eta][n_xi].
 struct InstView {
@@ -70,6 +80,7 @@ struct InstView {
     uint32_t key0, key1;          // Philox key (seed low / high word)
     uint32_t ctr3;                // instance_id << 16 | mesh_step & 0xffff
     uint32_t rec0;                // byte offset of `cells` from `coef_y` (one allocation)
+    uint32_t slices;              // sliced request: slices (items of 64 paths) per chunk, else 0
     double Lx, Ly, tau, dt;       // extents, mesh step, substep
     float Lx_f, Ly_f, dt_f, sq2dt_f, inv_dt_f, inv_tau_f;
     float c_rad_f;                // -4 ln2 dt
@@ -109,7 +120,8 @@ struct InstView {
     // (0, 0) of the padded mesh, row stride n_xi + 2; read at interface nodes.
     const double *x64, *y64;
 
-    // Partial sums of this request's work items.
+    // Partial sums of this request's work items (SliceRec of each in a
+    // sliced request).
     Partial *partials;
 };
 

@@ -394,20 +394,30 @@ size_t request_bytes(const mesh_sdd &inst, int64_t N, int chunk, int32_t Ms)
            (size_t)inst.M * 5 * sizeof(double) + sizeof(InstView) + 64;
 }
 
-// Paths per item of an FP32 request: the launch shape's chunk, halved (down to
-// 64, one path per lane) while the request has fewer than 8 items for every
-// wave of the device, so that its paths spread over all waves and the last
-// items are short: 33^2 bump, N = 10^4 (1240 items of 256 on 4096 waves) 1.22 ->
-// 0.54 ms; above 8 items per wave the larger chunk is as fast.  Counted over
-// all M interface nodes, whatever the sampling stride: a function of the
-// instance, its bucket's shape and N, so alone, batched, served and subsampled
-// results have the same sums.  The partials grow by 3 MB at most (the end
-// states of a launch shrink by more).
-int small_chunk(const mesh_sdd_ctx *ctx, int32_t M, int64_t N, int chunk)
+// Slices per chunk of an FP32 request: its items are slices of 64 paths, one
+// per lane, instead of whole chunks while the request has fewer than 8 chunks
+// for every wave of the device, so that its paths spread over all waves and
+// the last items are short (33^2 bump, N = 10^4: 1240 items of 256 on 4096
+// waves 1.22 ms, 4867 slices 0.48); above 8 chunks per wave whole chunks are as
+// fast.  Not for paths of fewer than 64 substeps, whose items are short
+// anyway and whose records cost more than that gains.  0: whole chunks.  The
+// results are the same either way.
+int slices_per_chunk(const mesh_sdd_ctx *ctx, int32_t Ms, int64_t N, int K, int chunk)
 {
     const int64_t waves = (int64_t)ctx->cu_count * (msdd::kTableBlock / 64);
-    while (chunk > 64 && (int64_t)M * ((N + chunk - 1) / chunk) < 8 * waves) chunk = std::max(64, chunk / 128 * 64);
-    return chunk;
+    return chunk > 64 && K >= 64 && (int64_t)Ms * ((N + chunk - 1) / chunk) < 8 * waves ? chunk / 64 : 0;
+}
+
+// Cut the request into whole chunks or slices; the slices' records (528 bytes
+// each) must fit `room` bytes and kMaxSliceBytes.  Returns their bytes.
+constexpr size_t kMaxSliceBytes = (size_t)48 << 20;
+size_t set_items(Request &r, size_t room)
+{
+    const size_t bytes = (size_t)r.Ms * (size_t)((r.N + 63) / 64) * sizeof(msdd::SliceRec);
+    r.slices = slices_per_chunk(r.inst->ctx, r.Ms, r.N, r.inst->d.K, r.tuned_chunk);
+    if (r.inst->d.precision == MESH_SDD_FP64 || bytes > kMaxSliceBytes || bytes > room) r.slices = 0;
+    r.chunk_paths = r.slices ? 64 : r.tuned_chunk;
+    return r.slices ? bytes : 0;
 }
 
 // Snapshot host inputs (the caller may free them once submit returns).
@@ -421,8 +431,9 @@ std::shared_ptr<Request> make_request(mesh_sdd *inst, const mesh_sdd_step &s, in
     r->N = N;
     r->mesh_step = s.mesh_step;
     r->tuned_chunk = std::max(64, launch_for(inst->ctx, inst->d).chunk_paths / 64 * 64);
-    r->chunk_paths = small_chunk(inst->ctx, inst->M, N, r->tuned_chunk);
     r->cost_bytes = request_bytes(*inst, N, r->tuned_chunk, r->Ms);
+    const size_t budget = inst->ctx->budget;
+    r->cost_bytes += set_items(*r, budget > r->cost_bytes ? budget - r->cost_bytes : 0);
     const size_t n = (size_t)inst->d.n_xi * inst->d.n_eta;
     const size_t nb = 4 * (size_t)inst->d.n_eta + 4 * (size_t)inst->d.n_xi;
     if (!s.inputs_on_device) {
@@ -690,7 +701,7 @@ int stage_request(Request &r, const mesh_sdd_step *dev_step, Arena *arena = null
     if ((!dev_step && (r.x64.alloc(n * 8) || r.y64.alloc(n * 8) || r.b0.alloc(nb * 8) || r.b1.alloc(nb * 8))) ||
         r.xpad.alloc(np * 8) || r.ypad.alloc(np * 8) ||
         (!fp64 && (r.xpad_f.alloc(np * 4) || r.ypad_f.alloc(np * 4) || r.b0f.alloc(nb * 4) || r.b1f.alloc(nb * 4))) ||
-        r.partials.alloc(n_part * sizeof(Partial)) || r.out.alloc((size_t)5 * M * sizeof(double)) ||
+        r.partials.alloc(n_part * (r.slices ? sizeof(msdd::SliceRec) : sizeof(Partial))) || r.out.alloc((size_t)5 * M * sizeof(double)) ||
         r.steps_total.alloc(kTotalsBytes))
         return fail(MESH_SDD_E_NOMEM, "device allocation for a request failed");
 
@@ -770,6 +781,7 @@ int stage_request(Request &r, const mesh_sdd_step *dev_step, Arena *arena = null
     v.x64 = r.xpad.as<double>() + (d.n_xi + 2) + 1;
     v.y64 = r.ypad.as<double>() + (d.n_xi + 2) + 1;
     v.partials = r.partials.as<Partial>();
+    v.slices = (uint32_t)r.slices;
     HIP_TRY(msdd::launch_fill_u32(r.steps_total.as<uint32_t>(), 0u, 2, st));
 
     // FP32 work: every (node, chunk), numbered node-major, so that the waves
@@ -848,13 +860,15 @@ void cut_queues(const std::vector<msdd::WinJob> &jobs, Weight weight, msdd::JobQ
 // than 16 substeps of the wave: the counter, one address for all XCDs, gives
 // out an item every 10 ns or so, which 4096 waves with such items outrun (five
 // rings, 41^2, one substep, N = 10^4: 200 us from the counter, 80 by number).
-// In between, all but the last two rounds.
+// All but the last two rounds up to 64 substeps.  Longer items keep the
+// counter below its rate, and it keeps the waves level: 129 x 85, items of 230
+// substeps, 109 rounds: 19.7 ms with 107 rounds by number, 16.1 from the counter.
 uint32_t static_rounds(size_t n_items, uint32_t waves, int chunk_paths, int K)
 {
     const size_t rounds = (n_items + waves - 1) / waves;
     const int64_t substeps = (int64_t)(chunk_paths / 64) * K;
     if (substeps <= 16) return (uint32_t)rounds;
-    if (substeps <= 256) return (uint32_t)std::max<size_t>(1, rounds > 2 ? rounds - 2 : 1);
+    if (substeps <= 64) return (uint32_t)std::max<size_t>(1, rounds > 2 ? rounds - 2 : 1);
     return 1u;
 }
 
@@ -2020,6 +2034,14 @@ try {
         for (auto s = inst->samples.begin(); s != inst->samples.end(); ++s)
             if (std::get<0>(s->first) == r->stride) nb_max = std::max(nb_max, s->second->blocks.size());
         if (level == 3) need += piece((n_items / 64 + nb_max + 1) * sizeof(msdd::WinJob));
+    }
+    // slices take more (their records, and up to one job per 32 of them):
+    // whole chunks, with the same results, where that does not fit
+    if (r->slices) {
+        const size_t items = (size_t)r->Ms * (size_t)((N + 63) / 64);
+        const size_t more = items / 32 * sizeof(msdd::WinJob) + 1024;
+        const size_t room = msdd_rt::scratch_capacity();
+        set_items(*r, room > need + more ? room - need - more : 0);
     }
     if (need > msdd_rt::scratch_capacity())
         return fail(MESH_SDD_E_INVAL, "the solve needs %zu bytes of scratch, more than the %zu of the no-allocation "

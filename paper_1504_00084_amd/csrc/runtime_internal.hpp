@@ -278,7 +278,8 @@ struct Request {
     int64_t N = 0;
     uint32_t mesh_step = 0;
     int chunk_paths = 0;           // paths per item
-    int tuned_chunk = 0;           // the launch shape's; chunk_paths is smaller in small requests
+    int tuned_chunk = 0;           // the launch shape's: paths per chunk
+    int slices = 0;                // items of 64 paths per chunk in a sliced request, else 0: items are chunks
     // host snapshots of host inputs
     std::vector<double> hx, hy, hb0, hb1;
     // device buffers owned by the request (x64 .. b1: copies of host inputs;
