@@ -817,14 +817,19 @@ void release_request_buffers(Request &r)
 // of an XCD end together.  513^2 bump, N = 10^4: 204.5 -> 194.0 ms (its jobs of
 // 1/8 of a workgroup's share are 580 items, 17 ms); half or a sixth of the
 // share: 199.6, 196; 16 items at least: the batched mix at small path counts
-// 1 to 2 % slower.  The no-allocation solve, whose scratch holds jobs of 64
+// 1 to 2 % slower.  A launch of one instance with long paths (64 substeps or
+// more) and fewer than 32 items per workgroup gives every workgroup a job, of 8
+// items at least (FP64, 153 x 142, N = 101, 2800 items: 2135 -> 1243 us; with
+// short paths the windows cost more than that gains).  The no-allocation solve, whose scratch holds jobs of 64
 // items, takes every job at its full size.
 struct JobSizer {
     double queue, done = 0.0;   // work of one queue; work of the jobs so far
     double groups;              // workgroups per queue
     bool full;
-    JobSizer(double total, size_t share, bool full_size)
-        : queue(total / msdd::kJobQueues), groups((double)share / msdd::kJobQueues), full(full_size)
+    size_t least;               // items of the smallest job
+    JobSizer(double total, size_t items, size_t share, bool full_size)
+        : queue(total / msdd::kJobQueues), groups((double)share / msdd::kJobQueues), full(full_size),
+          least(std::min<size_t>(32, std::max<size_t>(8, (items + share - 1) / share)))
     {
     }
     // items of the next job: at most jmax and `left`, each of `item` work
@@ -834,7 +839,7 @@ struct JobSizer {
         if (!full && queue > 0.0) {
             const double at = done / queue;
             const double rest = (1.0 - (at - std::floor(at))) * queue / (3.0 * groups * item);
-            if ((double)n > rest) n = std::min(left, std::max<size_t>(32, (size_t)rest));
+            if ((double)n > rest) n = std::min(left, std::max(least, (size_t)rest));
         }
         done += (double)n * item;
         return n;
@@ -924,7 +929,8 @@ int run_fp32_launch(mesh_sdd_ctx *ctx, std::vector<InstView> &views, const std::
         const size_t jmax0 = std::max<size_t>(64, (n_items + share * split0 - 1) / (share * split0));
         double total = 0.0;
         for (const WorkRange &w : ranges) total += (double)w.count * w.chunk_paths * views[w.inst].K;
-        JobSizer sizer(total, share, arena != nullptr);
+        const bool one_long = ranges.size() == 1 && views[ranges[0].inst].K >= 64;
+        JobSizer sizer(total, one_long ? n_items : 32 * share, share, arena != nullptr);
         for (size_t ri = 0; ri < ranges.size(); ++ri) {
             const WorkRange &w = ranges[ri];
             const InstView &v = views[w.inst];
@@ -1035,7 +1041,8 @@ int run_fp64_launch(mesh_sdd_ctx *ctx, Request &r, Arena *arena = nullptr)
         // about 32 of them (at least two items for each of its waves)
         std::vector<msdd::WinJob> jobs;
         const size_t jmax = std::max<size_t>(64, v.n_items / ((size_t)ctx->cu_count * 32) + 1);
-        JobSizer sizer((double)v.n_items, (size_t)ctx->cu_count, false);
+        JobSizer sizer((double)v.n_items, r.v.K >= 64 ? v.n_items : 32 * (size_t)ctx->cu_count,
+                       (size_t)ctx->cu_count, false);
         for (const BlockRun &b : r.ss->blocks) {
             const size_t qa = (size_t)b.pos_begin * r.chunks_per_node, qb = (size_t)b.pos_end * r.chunks_per_node;
             for (size_t q = qa, n; q < qb; q += n) {
