@@ -1131,6 +1131,9 @@ int finalize_request(mesh_sdd_ctx *ctx, Request &r, const mesh_sdd_result *dev_o
 // read: those on the device, unless any result array of the call overlaps an
 // input or another result array (results then go through the host and are
 // copied out in the order of the requests, as they are for host arrays).
+// Writing them from the context's stream needs no more ordering than that:
+// its own stream waits for the default stream, on which the copies out run,
+// but a stream of the caller's need not, so its blocking solves copy out.
 std::vector<const mesh_sdd_result *> direct_results(const std::vector<const mesh_sdd_result *> &results,
                                                     const std::vector<std::shared_ptr<Request>> &reqs,
                                                     const std::vector<const mesh_sdd_step *> &dev_steps)
@@ -1205,8 +1208,8 @@ int run_blocking(mesh_sdd_ctx *ctx, std::vector<std::shared_ptr<Request>> &reqs,
     std::vector<size_t> fp32_reqs;
     size_t base = 0, limit = 0;   // items gathered, and in chunks of the tuned size
     SyncOnFail guard{ctx->stream};   // an exception on the way leaves nothing in flight
-    const std::vector<const mesh_sdd_result *> direct =
-        results.empty() ? results : direct_results(results, reqs, dev_steps);
+    std::vector<const mesh_sdd_result *> direct;
+    if (ctx->own_stream && !results.empty()) direct = direct_results(results, reqs, dev_steps);
     auto out_of = [&](size_t q) { return direct.empty() ? nullptr : direct[q]; };
     // one persistent launch over the FP32 requests gathered so far: the
     // bucket's shape for a launch of one instance, the multi-instance shape
