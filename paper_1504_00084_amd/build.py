@@ -32,6 +32,7 @@ SOURCES = [
     ("noalloc.hip", ["--offload-arch=" + ARCH] + DEVICE_FLAGS),
     ("runtime.cpp", []),
     ("mesh_step.cpp", []),
+    ("device_memory.cpp", []),
 ]
 
 

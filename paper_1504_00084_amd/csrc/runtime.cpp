@@ -644,6 +644,12 @@ struct SyncOnFail {
     }
 };
 
+// Whether kernels may use the caller's array of n doubles where it lies.
+bool in_place(const mesh_sdd_ctx *ctx, const double *p, size_t n)
+{
+    return !msdd_rt::device_holds || msdd_rt::device_holds(ctx->device, p, n * sizeof(double));
+}
+
 // Allocate the request's device buffers, stage its inputs and run the prep
 // kernels; builds the work items.  Nothing is waited for: the host snapshots
 // stay until the launch that follows has been.  With an arena the buffers are carved from
@@ -698,7 +704,9 @@ int stage_request(Request &r, const mesh_sdd_step *dev_step, Arena *arena = null
         b->pool = &ctx->pool;
         b->arena = arena;
     }
-    if ((!dev_step && (r.x64.alloc(n * 8) || r.y64.alloc(n * 8) || r.b0.alloc(nb * 8) || r.b1.alloc(nb * 8))) ||
+    const bool direct = dev_step && in_place(ctx, dev_step->x_cur, n) && in_place(ctx, dev_step->y_cur, n) &&
+                        in_place(ctx, dev_step->bnd_t0, nb) && in_place(ctx, dev_step->bnd_t1, nb);
+    if ((!direct && (r.x64.alloc(n * 8) || r.y64.alloc(n * 8) || r.b0.alloc(nb * 8) || r.b1.alloc(nb * 8))) ||
         r.xpad.alloc(np * 8) || r.ypad.alloc(np * 8) ||
         (!fp64 && (r.xpad_f.alloc(np * 4) || r.ypad_f.alloc(np * 4) || r.b0f.alloc(nb * 4) || r.b1f.alloc(nb * 4))) ||
         r.partials.alloc(n_part * (r.slices ? sizeof(msdd::SliceRec) : sizeof(Partial))) || r.out.alloc((size_t)5 * M * sizeof(double)) ||
@@ -706,7 +714,7 @@ int stage_request(Request &r, const mesh_sdd_step *dev_step, Arena *arena = null
         return fail(MESH_SDD_E_NOMEM, "device allocation for a request failed");
 
     const double *x = nullptr, *y = nullptr, *b0 = nullptr, *b1 = nullptr;   // device inputs
-    if (dev_step) {
+    if (direct) {
         // a blocking call: its kernels read the caller's arrays, which no
         // result array of the call overlaps when results are written directly
         x = dev_step->x_cur;
@@ -714,10 +722,11 @@ int stage_request(Request &r, const mesh_sdd_step *dev_step, Arena *arena = null
         b0 = dev_step->bnd_t0;
         b1 = dev_step->bnd_t1;
     } else {
-        HIP_TRY(hipMemcpyAsync(r.x64.p, r.hx.data(), n * 8, hipMemcpyHostToDevice, st));
-        HIP_TRY(hipMemcpyAsync(r.y64.p, r.hy.data(), n * 8, hipMemcpyHostToDevice, st));
-        HIP_TRY(hipMemcpyAsync(r.b0.p, r.hb0.data(), nb * 8, hipMemcpyHostToDevice, st));
-        HIP_TRY(hipMemcpyAsync(r.b1.p, r.hb1.data(), nb * 8, hipMemcpyHostToDevice, st));
+        const hipMemcpyKind kind = dev_step ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice;
+        HIP_TRY(hipMemcpyAsync(r.x64.p, dev_step ? dev_step->x_cur : r.hx.data(), n * 8, kind, st));
+        HIP_TRY(hipMemcpyAsync(r.y64.p, dev_step ? dev_step->y_cur : r.hy.data(), n * 8, kind, st));
+        HIP_TRY(hipMemcpyAsync(r.b0.p, dev_step ? dev_step->bnd_t0 : r.hb0.data(), nb * 8, kind, st));
+        HIP_TRY(hipMemcpyAsync(r.b1.p, dev_step ? dev_step->bnd_t1 : r.hb1.data(), nb * 8, kind, st));
         x = r.x64.as<double>();
         y = r.y64.as<double>();
         b0 = r.b0.as<double>();
@@ -1128,7 +1137,7 @@ int finalize_request(mesh_sdd_ctx *ctx, Request &r, const mesh_sdd_result *dev_o
 }
 
 // The result arrays of a call that may be written while its inputs are still
-// read: those on the device, unless any result array of the call overlaps an
+// read: those in the device's memory, unless any result array of the call overlaps an
 // input or another result array (results then go through the host and are
 // copied out in the order of the requests, as they are for host arrays).
 // Writing them from the context's stream needs no more ordering than that:
@@ -1158,7 +1167,10 @@ std::vector<const mesh_sdd_result *> direct_results(const std::vector<const mesh
         const mesh_sdd_result *r = results[q];
         if (!r || !r->outputs_on_device) continue;
         direct[q] = r;
-        for (const double *p : {r->mean_x, r->mean_y, r->se_x, r->se_y, r->exit_frac}) add(p, (size_t)reqs[q]->M, true);
+        for (const double *p : {r->mean_x, r->mean_y, r->se_x, r->se_y, r->exit_frac}) {
+            add(p, (size_t)reqs[q]->M, true);
+            if (p && reqs[q]->M && !in_place(reqs[q]->inst->ctx, p, (size_t)reqs[q]->M)) direct[q] = nullptr;
+        }
     }
     std::sort(spans.begin(), spans.end(), [](const Span &a, const Span &b) { return a.b < b.b; });
     const char *end_all = nullptr, *end_out = nullptr;

@@ -283,7 +283,7 @@ struct Request {
     // host snapshots of host inputs
     std::vector<double> hx, hy, hb0, hb1;
     // device buffers owned by the request (x64 .. b1: copies of host inputs;
-    // a blocking call reads device inputs where they are)
+    // a blocking call reads inputs in the device's memory where they are)
     DevBuf x64, y64, b0, b1, xpad, ypad, xpad_f, ypad_f, b0f, b1f;
     DevBuf partials, out, steps_total;
     InstView v{};
@@ -380,6 +380,13 @@ int install_monitor(mesh_sdd *inst, hipStream_t st);
 size_t scratch_capacity();
 hipError_t scratch_resolve(int device);
 int scratch_region(int device, void **base, std::mutex **use);
+
+// Whether `bytes` bytes at p lie in one allocation of `device`: only then do
+// kernels read or write a caller's array where it lies.  Any other array
+// given as a device array (another device's, host memory, one that is too
+// short) goes through hipMemcpy, which copies it or refuses it.  Weak: a build
+// of the host sources without device_memory.cpp takes every array as it is.
+bool device_holds(int device, const void *p, size_t bytes) __attribute__((weak));
 
 // Ranks of the interface nodes that run paths under `stride` (0 or 1: all),
 // in rank order.  The stride must have passed the step validation.

@@ -1,0 +1,222 @@
+// Host-only checks of what the library's calls hand to its kernels and of
+// what they charge to the memory budget (built with g++ against the CPU
+// stand-in HIP header; no GPU).  The stub launchers of stub_kernels.cpp, some
+// of them recording their arguments.  TEST INFRASTRUCTURE ONLY.  Scenarios
+// (argv[1]):
+//   arrays   device arrays that kernels may not address are staged
+// Exit status 0 when every check holds; a message names the first failure.
+#define launch_prep_mesh stub_launch_prep_mesh
+#define launch_finalize stub_launch_finalize
+#include "stub_kernels.cpp"
+#undef launch_prep_mesh
+#undef launch_finalize
+
+#include <cstdarg>
+#include <cstdio>
+#include <string>
+#include <utility>
+#include <vector>
+
+#include "mesh_sdd.h"
+
+static int g_failures = 0;
+static void check(bool ok, const char *fmt, ...)
+{
+    if (ok) return;
+    va_list ap;
+    va_start(ap, fmt);
+    std::vfprintf(stderr, fmt, ap);
+    va_end(ap);
+    std::fprintf(stderr, " (last error: %s)\n", mesh_sdd_last_error());
+    ++g_failures;
+}
+
+// ---- recording launchers ---------------------------------------------------
+static const double *g_prep_x = nullptr;         // mesh that the last launch_prep_mesh read
+static double g_prep_first = 0.0;                // and its first value
+static std::vector<const double *> g_final;      // result arrays of the last launch_finalize
+
+namespace msdd {
+hipError_t launch_prep_mesh(const double *x, const double *y, int n_xi, int n_eta, int per_xi, int per_eta, double Lx,
+                            double Ly, double *xpad, double *ypad, float *xpad_f, float *ypad_f, hipStream_t s)
+{
+    g_prep_x = x;
+    g_prep_first = x[0];
+    return stub_launch_prep_mesh(x, y, n_xi, n_eta, per_xi, per_eta, Lx, Ly, xpad, ypad, xpad_f, ypad_f, s);
+}
+hipError_t launch_finalize(const Partial *p, const NodeSpan *sp, const InstView *v, uint32_t M, uint64_t n, double *mx,
+                           double *my, double *sx, double *sy, double *ef, unsigned long long *t, hipStream_t s)
+{
+    g_final = {mx, my, sx, sy, ef};
+    return stub_launch_finalize(p, sp, v, M, n, mx, my, sx, sy, ef, t, s);
+}
+}  // namespace msdd
+
+// ---- which memory the device holds -----------------------------------------
+static std::vector<std::pair<const void *, size_t>> g_foreign;   // arrays that are not the device's, and their bytes
+static std::vector<std::pair<const void *, size_t>> g_asked;
+namespace msdd_rt {
+bool device_holds(int device, const void *p, size_t bytes)
+{
+    g_asked.emplace_back(p, bytes);
+    for (auto &f : g_foreign)
+        if (f.first == p) return false;
+    return device == 0;
+}
+}  // namespace msdd_rt
+
+// ---- a small problem --------------------------------------------------------
+struct Problem {
+    int n;
+    std::vector<double> rho, x, y, b;
+    explicit Problem(int n_) : n(n_), rho((size_t)n_ * n_, 1.0), x(rho.size()), y(rho.size())
+    {
+        for (int j = 0; j < n; ++j)
+            for (int i = 0; i < n; ++i) {
+                x[(size_t)j * n + i] = i / (n - 1.0);
+                y[(size_t)j * n + i] = j / (n - 1.0);
+            }
+        for (int s = 0; s < 4; ++s)
+            for (int c = 0; c < 2; ++c)
+                for (int k = 0; k < n; ++k) {
+                    const double t = k / (n - 1.0), at[2] = {s < 2 ? (double)s : t, s < 2 ? t : s - 2.0};
+                    b.push_back(at[c]);
+                }
+        x[0] = 0.0;
+    }
+};
+
+static mesh_sdd_desc make_desc(int n, int sub, int precision, int K, uint32_t id = 0)
+{
+    mesh_sdd_desc d;
+    std::memset(&d, 0, sizeof d);
+    d.struct_size = sizeof d;
+    d.n_xi = d.n_eta = n;
+    d.sub_xi = d.sub_eta = sub;
+    d.K = K;
+    d.Lx = d.Ly = 1.0;
+    d.tau = 0.01;
+    d.precision = precision;
+    d.bridge = 1;
+    d.instance_id = id;
+    return d;
+}
+
+static mesh_sdd_step make_step(const Problem &p, int64_t N, int on_device)
+{
+    mesh_sdd_step s;
+    std::memset(&s, 0, sizeof s);
+    s.struct_size = sizeof s;
+    s.inputs_on_device = on_device;
+    s.x_cur = p.x.data();
+    s.y_cur = p.y.data();
+    s.bnd_t0 = s.bnd_t1 = p.b.data();
+    s.paths_per_node = N;
+    return s;
+}
+
+struct Out {
+    std::vector<double> a[5];
+    mesh_sdd_result r;
+    explicit Out(int m, int on_device)
+    {
+        std::memset(&r, 0, sizeof r);
+        r.struct_size = sizeof r;
+        r.outputs_on_device = on_device;
+        for (auto &v : a) v.assign((size_t)m, -1.0);
+        double **p[5] = {&r.mean_x, &r.mean_y, &r.se_x, &r.se_y, &r.exit_frac};
+        for (int k = 0; k < 5; ++k) *p[k] = a[k].data();
+    }
+};
+
+struct Fixture {
+    mesh_sdd_ctx *ctx = nullptr;
+    std::vector<mesh_sdd *> h;
+    Fixture(size_t budget = 0) { check(mesh_sdd_ctx_create(0, budget, nullptr, &ctx) == MESH_SDD_OK, "ctx_create"); }
+    ~Fixture()
+    {
+        for (mesh_sdd *i : h) check(mesh_sdd_destroy(i) == MESH_SDD_OK, "destroy");
+        check(mesh_sdd_ctx_destroy(ctx) == MESH_SDD_OK, "ctx_destroy");
+    }
+    mesh_sdd *add(const Problem &p, const mesh_sdd_desc &d)
+    {
+        mesh_sdd *i = nullptr;
+        check(mesh_sdd_create(ctx, &d, &i) == MESH_SDD_OK, "create");
+        check(mesh_sdd_set_monitor(i, p.rho.data(), 0) == MESH_SDD_OK, "set_monitor");
+        h.push_back(i);
+        return i;
+    }
+};
+
+// ---------------------------------------------------------------------------
+static void scenario_arrays()
+{
+    Problem p(17);
+    p.x[0] = 0.25;   // recognised in the staged copy
+    for (int precision : {MESH_SDD_FP32, MESH_SDD_FP64}) {
+        Fixture f;
+        mesh_sdd *h = f.add(p, make_desc(17, 2, precision, 20));
+        const int m = mesh_sdd_num_interface_nodes(h);
+        const size_t n = p.x.size() * 8, nb = p.b.size() * 8;
+        for (bool noalloc : {false, true}) {
+            auto solve = noalloc ? mesh_sdd_solve_interfaces_noalloc : mesh_sdd_solve_interfaces;
+            mesh_sdd_step st = make_step(p, 300, 1);
+            Out o(m, 1);
+            // the device's own arrays: used where they are, each asked for its whole length
+            g_foreign.clear();
+            g_asked.clear();
+            check(solve(h, &st, &o.r) == MESH_SDD_OK, "solve");
+            check(g_prep_x == p.x.data(), "the mesh is read in place");
+            check(g_final[0] == o.a[0].data(), "the results are written in place");
+            for (auto &want : {std::make_pair((const void *)p.x.data(), n), std::make_pair((const void *)p.y.data(), n),
+                               std::make_pair((const void *)p.b.data(), nb),
+                               std::make_pair((const void *)o.a[4].data(), (size_t)m * 8)}) {
+                bool found = false;
+                for (auto &a : g_asked) found = found || a == want;
+                check(found, "an array of %zu bytes was not looked up", want.second);
+            }
+            // each input in turn not the device's: a staged copy of the same values
+            for (const double *bad : {p.x.data(), p.y.data(), p.b.data()}) {
+                g_foreign.assign(1, {bad, 0});
+                check(solve(h, &st, &o.r) == MESH_SDD_OK, "solve with a foreign input");
+                check(g_prep_x != p.x.data() && g_prep_first == 0.25, "a foreign input is read in place");
+                check(g_final[0] == o.a[0].data(), "the results are written in place");
+            }
+            // each result in turn not the device's: copied out
+            for (int k = 0; k < 5; ++k) {
+                Out q(m, 1);
+                g_foreign.assign(1, {q.a[k].data(), 0});
+                check(solve(h, &st, &q.r) == MESH_SDD_OK, "solve with a foreign result");
+                check(g_prep_x == p.x.data(), "the mesh is read in place");
+                check(g_final[k] != q.a[k].data() && q.a[k][0] == 0.0 && q.a[k][m - 1] == 0.0,
+                      "foreign result %d: written in place, or not at all", k);
+            }
+        }
+        // a batch: the other request still writes in place
+        mesh_sdd *both[2] = {h, h};
+        mesh_sdd_step st[2] = {make_step(p, 300, 1), make_step(p, 300, 1)};
+        Out a(m, 1), b(m, 1);
+        mesh_sdd_result res[2] = {a.r, b.r};
+        g_foreign.assign(1, {a.a[2].data(), 0});
+        check(mesh_sdd_solve_batch(both, st, res, 2, nullptr) == MESH_SDD_OK, "batch");
+        check(g_final[0] == b.a[0].data() && a.a[0][0] == 0.0, "batch with a foreign result");
+        g_foreign.clear();
+    }
+}
+
+int main(int argc, char **argv)
+{
+    const std::string what = argc > 1 ? argv[1] : "";
+    if (what == "arrays")
+        scenario_arrays();
+    else {
+        std::fprintf(stderr, "unknown scenario %s\n", what.c_str());
+        return 2;
+    }
+    if (g_failures) {
+        std::fprintf(stderr, "%d check(s) failed\n", g_failures);
+        return 1;
+    }
+    std::printf("%s: all checks passed\n", what.c_str());
+    return 0;
+}
