@@ -156,8 +156,8 @@ int solve_dev(mesh_sdd *inst, const MpOpts &o, const double *x0, const double *y
     int rc = fe_substeps(d, o, &L);
     if (rc != MESH_SDD_OK) return rc;
     const size_t n = grid_size(d);
-    DevBuf tx1, ty1, mask, ax, ay, bx, by;
-    tx1.pool = ty1.pool = mask.pool = ax.pool = ay.pool = bx.pool = by.pool = &ctx->pool;
+    DevBuf tx1, ty1, mask, ax, ay, bx, by, sx, sy;
+    tx1.pool = ty1.pool = mask.pool = ax.pool = ay.pool = bx.pool = by.pool = sx.pool = sy.pool = &ctx->pool;
     SyncOnExit sync{st};
     if (tx1.alloc(n * 8) || ty1.alloc(n * 8) || mask.alloc(n))
         return fail(MESH_SDD_E_NOMEM, "device allocation for the mesh step failed");
@@ -201,6 +201,16 @@ int solve_dev(mesh_sdd *inst, const MpOpts &o, const double *x0, const double *y
     // (from then on they are node 0 plus the period).
     if (ax.alloc(n * 8) || ay.alloc(n * 8) || bx.alloc(n * 8) || by.alloc(n * 8))
         return fail(MESH_SDD_E_NOMEM, "device allocation for the mesh step failed");
+    auto overlap = [n](const double *p, const double *q) { return p < q + n && q < p + n; };
+    if (overlap(x_new, x0) || overlap(x_new, y0) || overlap(y_new, x0) || overlap(y_new, y0)) {
+        // a mesh step in place: the last launch writes the result while other
+        // tiles read the start mesh, so they read a copy
+        if (sx.alloc(n * 8) || sy.alloc(n * 8)) return fail(MESH_SDD_E_NOMEM, "device allocation for the mesh step failed");
+        HIP_TRY(hipMemcpyAsync(sx.p, x0, n * 8, hipMemcpyDeviceToDevice, st));
+        HIP_TRY(hipMemcpyAsync(sy.p, y0, n * 8, hipMemcpyDeviceToDevice, st));
+        a.x0 = x0 = sx.as<double>();
+        a.y0 = y0 = sy.as<double>();
+    }
     const double *cx = x0, *cy = y0;
     double *nx = ax.as<double>(), *ny = ay.as<double>();
     double *ox = bx.as<double>(), *oy = by.as<double>();
