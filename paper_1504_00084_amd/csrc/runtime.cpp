@@ -409,7 +409,9 @@ int slices_per_chunk(const mesh_sdd_ctx *ctx, int32_t Ms, int64_t N, int K, int 
 }
 
 // Cut the request into whole chunks or slices; the slices' records (528 bytes
-// each) must fit `room` bytes and kMaxSliceBytes.  Returns their bytes.
+// each) must fit `room` bytes and kMaxSliceBytes.  Returns their bytes.  Who
+// runs a request decides when it is about to be staged: until then it is
+// charged, and staged by default, as whole chunks.
 constexpr size_t kMaxSliceBytes = (size_t)48 << 20;
 size_t set_items(Request &r, size_t room)
 {
@@ -431,9 +433,8 @@ std::shared_ptr<Request> make_request(mesh_sdd *inst, const mesh_sdd_step &s, in
     r->N = N;
     r->mesh_step = s.mesh_step;
     r->tuned_chunk = std::max(64, launch_for(inst->ctx, inst->d).chunk_paths / 64 * 64);
+    r->chunk_paths = r->tuned_chunk;
     r->cost_bytes = request_bytes(*inst, N, r->tuned_chunk, r->Ms);
-    const size_t budget = inst->ctx->budget;
-    r->cost_bytes += set_items(*r, budget > r->cost_bytes ? budget - r->cost_bytes : 0);
     const size_t n = (size_t)inst->d.n_xi * inst->d.n_eta;
     const size_t nb = 4 * (size_t)inst->d.n_eta + 4 * (size_t)inst->d.n_xi;
     if (!s.inputs_on_device) {
@@ -1219,6 +1220,15 @@ int run_blocking(mesh_sdd_ctx *ctx, std::vector<std::shared_ptr<Request>> &reqs,
     std::vector<const SampleSet *> sets;
     std::vector<size_t> fp32_reqs;
     size_t base = 0, limit = 0;   // items gathered, and in chunks of the tuned size
+    {
+        // slices where their records fit the budget beside what is in use, the
+        // rest of the batch and the records granted before them
+        size_t used = 0;
+        for (auto &r : reqs) used += r->cost_bytes;
+        std::lock_guard<std::mutex> lk(ctx->mu);
+        used += ctx->in_use;
+        for (auto &r : reqs) used += set_items(*r, used < ctx->budget ? ctx->budget - used : 0);
+    }
     SyncOnFail guard{ctx->stream};   // an exception on the way leaves nothing in flight
     std::vector<const mesh_sdd_result *> direct;
     if (ctx->own_stream && !results.empty()) direct = direct_results(results, reqs, dev_steps);
@@ -1426,7 +1436,10 @@ void finish_request(mesh_sdd_ctx *ctx, const std::shared_ptr<Request> &r, int st
     }
     r->finished = true;
     r->t_done = Clock::now();
-    if (r->admitted) ctx->in_use -= std::min(ctx->in_use, r->cost_bytes);
+    if (r->admitted) {
+        ctx->in_use -= std::min(ctx->in_use, r->cost_bytes);
+        ctx->slices_in_use -= r->slice_bytes;
+    }
     r->inst->inflight.fetch_sub(1);
     if (status == MESH_SDD_OK) {
         ++ctx->completed;
@@ -1453,12 +1466,25 @@ void scheduler_loop(mesh_sdd_ctx *ctx)
                 std::unique_lock<std::mutex> lk(ctx->mu);
                 ctx->cv.wait(lk, [&] { return ctx->stop || !ctx->queue.empty() || !ctx->running.empty(); });
                 if (ctx->stop) break;
-                // admission in arrival order while the budget allows
+                // admission in arrival order while the budget allows, by the
+                // requests' cost in whole chunks.  A request runs in slices
+                // where their records fit beside everything in use and every
+                // request that waits, and while all records together hold no
+                // more than a sixteenth of the budget: what arrives later is
+                // to find the room that it would find without them
+                size_t waiting = 0;
+                for (auto &r : ctx->queue) waiting += r->cost_bytes;
                 while (!ctx->queue.empty()) {
-                    auto &r = ctx->queue.front();
+                    auto r = ctx->queue.front();
                     if (ctx->in_use + r->cost_bytes > ctx->budget && !ctx->running.empty()) break;
                     to_admit.reserve(to_admit.size() + 1);   // the only allocations, before any state changes
                     ctx->running.reserve(ctx->running.size() + 1);
+                    const size_t used = ctx->in_use + waiting, most = ctx->budget / 16;
+                    waiting -= r->cost_bytes;
+                    r->slice_bytes = set_items(*r, std::min(used < ctx->budget ? ctx->budget - used : 0,
+                                                            most - std::min(most, ctx->slices_in_use)));
+                    r->cost_bytes += r->slice_bytes;
+                    ctx->slices_in_use += r->slice_bytes;
                     ctx->in_use += r->cost_bytes;
                     r->admitted = true;
                     to_admit.push_back(r);
@@ -2059,7 +2085,7 @@ try {
     }
     // slices take more (their records, and up to one job per 32 of them):
     // whole chunks, with the same results, where that does not fit
-    if (r->slices) {
+    if (!fp64) {
         const size_t items = (size_t)r->Ms * (size_t)((N + 63) / 64);
         const size_t more = items / 32 * sizeof(msdd::WinJob) + 1024;
         const size_t room = msdd_rt::scratch_capacity();

@@ -292,7 +292,8 @@ struct Request {
     size_t next_item = 0;          // first item not yet handed to a tick
     size_t done_items = 0;
     uint32_t chunks_per_node = 0;
-    size_t cost_bytes = 0;
+    size_t cost_bytes = 0;         // device memory: in whole chunks; once admitted, with slice_bytes
+    size_t slice_bytes = 0;        // admitted in slices: the bytes of their records
     // completion
     int status = MESH_SDD_PENDING;
     std::string error;
@@ -348,6 +349,7 @@ struct mesh_sdd_ctx {
     std::mutex mu;       // guards everything below
     std::condition_variable cv, done_cv;
     size_t in_use = 0;
+    size_t slices_in_use = 0;      // of which records of slices
     int n_instances = 0;
     std::deque<std::shared_ptr<Request>> queue;    // submitted, not admitted
     std::vector<std::shared_ptr<Request>> running; // admitted, not finished

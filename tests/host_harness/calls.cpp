@@ -4,6 +4,8 @@
 // of them recording their arguments.  TEST INFRASTRUCTURE ONLY.  Scenarios
 // (argv[1]):
 //   arrays   device arrays that kernels may not address are staged
+//   budget   requests in slices of 64 paths claim memory only where the budget
+//            has room for it beside everything else
 // Exit status 0 when every check holds; a message names the first failure.
 #define launch_prep_mesh stub_launch_prep_mesh
 #define launch_finalize stub_launch_finalize
@@ -11,6 +13,7 @@
 #undef launch_prep_mesh
 #undef launch_finalize
 
+#include <algorithm>
 #include <cstdarg>
 #include <cstdio>
 #include <string>
@@ -35,6 +38,10 @@ static void check(bool ok, const char *fmt, ...)
 static const double *g_prep_x = nullptr;         // mesh that the last launch_prep_mesh read
 static double g_prep_first = 0.0;                // and its first value
 static std::vector<const double *> g_final;      // result arrays of the last launch_finalize
+static std::vector<uint32_t> g_slices;           // slices per chunk of each request finalized
+static mesh_sdd_ctx *g_watched = nullptr;        // its memory in use at every staging, the most
+static std::atomic<uint64_t> g_most_in_use{0}, g_most_running{0};
+static std::mutex g_gate;                        // held: staging waits
 
 namespace msdd {
 hipError_t launch_prep_mesh(const double *x, const double *y, int n_xi, int n_eta, int per_xi, int per_eta, double Lx,
@@ -42,12 +49,22 @@ hipError_t launch_prep_mesh(const double *x, const double *y, int n_xi, int n_et
 {
     g_prep_x = x;
     g_prep_first = x[0];
+    if (g_watched) {
+        std::lock_guard<std::mutex> hold(g_gate);
+        mesh_sdd_stats st;
+        std::memset(&st, 0, sizeof st);
+        st.struct_size = sizeof st;
+        mesh_sdd_ctx_stats(g_watched, &st);
+        g_most_in_use = std::max<uint64_t>(g_most_in_use, st.hbm_in_use);
+        g_most_running = std::max<uint64_t>(g_most_running, st.running);
+    }
     return stub_launch_prep_mesh(x, y, n_xi, n_eta, per_xi, per_eta, Lx, Ly, xpad, ypad, xpad_f, ypad_f, s);
 }
 hipError_t launch_finalize(const Partial *p, const NodeSpan *sp, const InstView *v, uint32_t M, uint64_t n, double *mx,
                            double *my, double *sx, double *sy, double *ef, unsigned long long *t, hipStream_t s)
 {
     g_final = {mx, my, sx, sy, ef};
+    g_slices.push_back(v->slices);
     return stub_launch_finalize(p, sp, v, M, n, mx, my, sx, sy, ef, t, s);
 }
 }  // namespace msdd
@@ -204,11 +221,129 @@ static void scenario_arrays()
     }
 }
 
+// ---------------------------------------------------------------------------
+// Requests of 29 nodes at N = 1280 on 8 CUs: 10 chunks of 128 paths per node,
+// or 20 slices whose records take 29 * 20 * 528 bytes.
+static const int64_t kN = 1280;
+static const size_t kRecords = 29 * 20 * sizeof(msdd::SliceRec);
+
+static uint64_t in_use(mesh_sdd_ctx *ctx)
+{
+    mesh_sdd_stats st;
+    std::memset(&st, 0, sizeof st);
+    st.struct_size = sizeof st;
+    check(mesh_sdd_ctx_stats(ctx, &st) == MESH_SDD_OK, "stats");
+    return st.hbm_in_use;
+}
+
+// Submits one request per instance, all of them queued before the first is
+// staged, and waits for all; the most memory in use and requests running.
+static void serve(Fixture &f, const Problem &p, size_t count, uint64_t *most, uint64_t *running)
+{
+    g_slices.clear();
+    g_most_in_use = g_most_running = 0;
+    g_watched = f.ctx;
+    std::vector<mesh_sdd_ticket> t(count);
+    mesh_sdd_step st = make_step(p, kN, 0);
+    {
+        std::lock_guard<std::mutex> hold(g_gate);
+        for (size_t k = 0; k < count; ++k) check(mesh_sdd_submit(f.h[k], &st, &t[k]) == MESH_SDD_OK, "submit");
+    }
+    Out o(29, 0);
+    for (size_t k = 0; k < count; ++k) check(mesh_sdd_wait(f.ctx, t[k], &o.r, -1) == MESH_SDD_OK, "wait");
+    g_watched = nullptr;
+    if (most) *most = g_most_in_use;
+    if (running) *running = g_most_running;
+}
+
+static size_t sliced()
+{
+    size_t n = 0;
+    for (uint32_t s : g_slices) n += s != 0;
+    return n;
+}
+
+static void scenario_budget()
+{
+    Problem p(17), big(65);
+    size_t tables, tables65, base;
+    uint64_t most = 0, running = 0;
+    {
+        // the cost of an instance's tables and of a request in whole chunks
+        // (paths of fewer than 64 substeps never run in slices)
+        Fixture f;
+        f.add(p, make_desc(17, 2, MESH_SDD_FP32, 20));
+        tables = in_use(f.ctx);
+        serve(f, p, 1, &most, nullptr);
+        base = most - tables;
+        check(in_use(f.ctx) == tables, "a finished request leaves nothing in use");
+        f.add(big, make_desc(65, 2, MESH_SDD_FP32, 20));
+        tables65 = in_use(f.ctx) - tables;
+        check(base > 10000 && base < kRecords / 2, "base %zu", base);
+    }
+    {
+        // room for everything: slices, alone, in a batch and served
+        Fixture f;
+        for (int k = 0; k < 5; ++k) f.add(p, make_desc(17, 2, MESH_SDD_FP32, 100, k));
+        serve(f, p, 5, &most, &running);
+        check(g_slices.size() == 5 && sliced() == 5, "%zu of 5 requests in slices", sliced());
+        check(running >= 4, "%d requests ran together", (int)running);
+        check(most == 5 * tables + running * (base + kRecords), "%zu bytes in use", (size_t)most);
+        check(in_use(f.ctx) == 5 * tables, "finished requests leave nothing in use");
+    }
+    {
+        // room for the requests in whole chunks beside each other and for
+        // the records of one: they run together, as whole chunks
+        Fixture f(5 * tables + 5 * base + kRecords);
+        for (int k = 0; k < 5; ++k) f.add(p, make_desc(17, 2, MESH_SDD_FP32, 100, k));
+        serve(f, p, 5, &most, &running);
+        check(running >= 4, "%d requests ran together", (int)running);
+        check(most <= 5 * tables + 5 * base + kRecords, "%zu bytes in use of %zu", (size_t)most,
+              5 * tables + 5 * base + kRecords);
+    }
+    {
+        // resident tables leave room for one request in whole chunks only
+        const size_t budget = tables + 4 * tables65 + base + kRecords / 2;
+        check(budget > base + kRecords, "the records alone would fit the budget");
+        Fixture f(budget);
+        f.add(p, make_desc(17, 2, MESH_SDD_FP32, 100));
+        for (int k = 0; k < 4; ++k) f.add(big, make_desc(65, 2, MESH_SDD_FP32, 100, 1 + k));
+        serve(f, p, 1, &most, &running);
+        check(most <= budget && sliced() == 0, "%zu bytes in use of %zu", (size_t)most, budget);
+        g_slices.clear();
+        mesh_sdd_step st = make_step(p, kN, 0);
+        Out o(29, 0);
+        check(mesh_sdd_solve_interfaces(f.h[0], &st, &o.r) == MESH_SDD_OK && sliced() == 0, "a blocking solve");
+    }
+    {
+        // a batch: slices for as many of its requests as the budget has room for
+        Fixture f(5 * tables + 5 * base + 2 * kRecords + kRecords / 2);
+        std::vector<mesh_sdd_step> st(5, make_step(p, kN, 0));
+        std::vector<Out> o(5, Out(29, 0));
+        std::vector<mesh_sdd_result> r;
+        for (int k = 0; k < 5; ++k) {
+            f.add(p, make_desc(17, 2, MESH_SDD_FP32, 100, k));
+            o[k] = Out(29, 0);
+            r.push_back(o[k].r);
+        }
+        g_slices.clear();
+        check(mesh_sdd_solve_batch(f.h.data(), st.data(), r.data(), 5, nullptr) == MESH_SDD_OK, "batch");
+        check(g_slices.size() == 5 && sliced() == 2, "%zu of 5 requests in slices", sliced());
+        g_slices.clear();
+        mesh_sdd_step dev = make_step(p, kN, 1);
+        Out d(29, 1);
+        check(mesh_sdd_solve_interfaces_noalloc(f.h[0], &dev, &d.r) == MESH_SDD_OK && sliced() == 1,
+              "the no-allocation solve's records lie in its own scratch");
+    }
+}
+
 int main(int argc, char **argv)
 {
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "arrays")
         scenario_arrays();
+    else if (what == "budget")
+        scenario_budget();
     else {
         std::fprintf(stderr, "unknown scenario %s\n", what.c_str());
         return 2;
