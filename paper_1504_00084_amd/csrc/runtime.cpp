@@ -379,19 +379,34 @@ int grid_for(mesh_sdd_ctx *ctx, const mesh_sdd_launch &l, uint32_t cap)
 // ---------------------------------------------------------------------------
 // Requests
 // ---------------------------------------------------------------------------
+// Device memory of a request whose Ms nodes run N paths in chunks of `chunk`.
 size_t request_bytes(const mesh_sdd &inst, int64_t N, int chunk, int32_t Ms)
 {
     const mesh_sdd_desc &d = inst.d;
     const size_t n = (size_t)d.n_xi * d.n_eta;
     const size_t np = (size_t)(d.n_xi + 2) * (d.n_eta + 2);
     const size_t nb = 4 * (size_t)d.n_eta + 4 * (size_t)d.n_xi;
-    size_t chunks;
-    if (d.precision == MESH_SDD_FP64)
-        chunks = (size_t)((N + msdd::kFp64Block - 1) / msdd::kFp64Block);
-    else
-        chunks = (size_t)((N + chunk - 1) / chunk);
+    const size_t chunks = (size_t)((N + chunk - 1) / chunk);
     return 2 * n * 8 + 2 * np * 12 + 2 * nb * 12 + (size_t)Ms * (chunks * sizeof(Partial) + sizeof(NodeSpan)) +
            (size_t)inst.M * 5 * sizeof(double) + sizeof(InstView) + 64;
+}
+
+// Paths per item of an FP64 request.  256; requests below 32 items of 64 paths
+// for every wave of the device take 64, so that the last items of a launch
+// are short and a launch with few items still gives every wave some (5 MB
+// more of partials at most; on the 129^2 bump at N = 10^4 items of 256 leave the
+// last of 7.4 rounds half empty).  Not where those partials would take more
+// than a sixteenth of the memory budget, or the request past it.  Counted over
+// all M interface nodes, so alone, batched, served and subsampled results of
+// a context have the same sums.
+int fp64_chunk(const mesh_sdd &inst, int64_t N)
+{
+    const mesh_sdd_ctx *ctx = inst.ctx;
+    const int64_t waves = (int64_t)ctx->cu_count * (msdd::kTableBlock / 64);
+    if ((int64_t)inst.M * ((N + 63) / 64) > 32 * waves) return msdd::kFp64Block;
+    const size_t small = request_bytes(inst, N, 64, inst.M);
+    const size_t more = small - request_bytes(inst, N, msdd::kFp64Block, inst.M);
+    return more <= ctx->budget / 16 && small <= ctx->budget ? 64 : msdd::kFp64Block;
 }
 
 // Slices per chunk of an FP32 request: its items are slices of 64 paths, one
@@ -416,8 +431,9 @@ constexpr size_t kMaxSliceBytes = (size_t)48 << 20;
 size_t set_items(Request &r, size_t room)
 {
     const size_t bytes = (size_t)r.Ms * (size_t)((r.N + 63) / 64) * sizeof(msdd::SliceRec);
+    if (r.inst->d.precision == MESH_SDD_FP64) return 0;
     r.slices = slices_per_chunk(r.inst->ctx, r.Ms, r.N, r.inst->d.K, r.tuned_chunk);
-    if (r.inst->d.precision == MESH_SDD_FP64 || bytes > kMaxSliceBytes || bytes > room) r.slices = 0;
+    if (bytes > kMaxSliceBytes || bytes > room) r.slices = 0;
     r.chunk_paths = r.slices ? 64 : r.tuned_chunk;
     return r.slices ? bytes : 0;
 }
@@ -433,8 +449,8 @@ std::shared_ptr<Request> make_request(mesh_sdd *inst, const mesh_sdd_step &s, in
     r->N = N;
     r->mesh_step = s.mesh_step;
     r->tuned_chunk = std::max(64, launch_for(inst->ctx, inst->d).chunk_paths / 64 * 64);
-    r->chunk_paths = r->tuned_chunk;
-    r->cost_bytes = request_bytes(*inst, N, r->tuned_chunk, r->Ms);
+    r->chunk_paths = inst->d.precision == MESH_SDD_FP64 ? fp64_chunk(*inst, N) : r->tuned_chunk;
+    r->cost_bytes = request_bytes(*inst, N, r->chunk_paths, r->Ms);
     const size_t n = (size_t)inst->d.n_xi * inst->d.n_eta;
     const size_t nb = 4 * (size_t)inst->d.n_eta + 4 * (size_t)inst->d.n_xi;
     if (!s.inputs_on_device) {
@@ -623,18 +639,6 @@ constexpr uint32_t kMaxLaunchItems = MESH_SDD_MAX_LAUNCH_ITEMS;
 // counters of an FP64 launch.
 constexpr size_t kTotalsBytes = 128;
 
-// Paths per item of an FP64 request.  256; requests below 32 items of 64 paths
-// for every wave of the device take 64, so that the last items of a launch
-// are short and a launch with few items still gives every wave some (6 MB
-// of partials at most; on the 129^2 bump at N = 10^4 items of 256 leave the
-// last of 7.4 rounds half empty).  Counted over all M interface nodes, so
-// alone, batched, served and subsampled results have the same sums.
-int fp64_chunk(const mesh_sdd_ctx *ctx, int32_t M, int64_t N)
-{
-    const int64_t waves = (int64_t)ctx->cu_count * (msdd::kTableBlock / 64);
-    return (int64_t)M * ((N + 63) / 64) <= 32 * waves ? 64 : msdd::kFp64Block;
-}
-
 // Waits for the stream when it goes out of scope armed.
 struct SyncOnFail {
     hipStream_t s;
@@ -686,7 +690,6 @@ int stage_request(Request &r, const mesh_sdd_step *dev_step, Arena *arena = null
     }
     const int Ms = r.ss->Ms;
 
-    if (fp64) r.chunk_paths = fp64_chunk(ctx, M, r.N);
     const uint32_t chunks = (uint32_t)((r.N + r.chunk_paths - 1) / r.chunk_paths);
     r.chunks_per_node = chunks;
     const size_t n_part = (size_t)Ms * chunks;

@@ -6,6 +6,7 @@
 //   arrays   device arrays that kernels may not address are staged
 //   budget   requests in slices of 64 paths claim memory only where the budget
 //            has room for it beside everything else
+//   fp64     FP64 requests are charged for the partial sums that they allocate
 // Exit status 0 when every check holds; a message names the first failure.
 #define launch_prep_mesh stub_launch_prep_mesh
 #define launch_finalize stub_launch_finalize
@@ -39,6 +40,7 @@ static const double *g_prep_x = nullptr;         // mesh that the last launch_pr
 static double g_prep_first = 0.0;                // and its first value
 static std::vector<const double *> g_final;      // result arrays of the last launch_finalize
 static std::vector<uint32_t> g_slices;           // slices per chunk of each request finalized
+static uint32_t g_items = 0;                     // items per node of the last one
 static mesh_sdd_ctx *g_watched = nullptr;        // its memory in use at every staging, the most
 static std::atomic<uint64_t> g_most_in_use{0}, g_most_running{0};
 static std::mutex g_gate;                        // held: staging waits
@@ -65,6 +67,7 @@ hipError_t launch_finalize(const Partial *p, const NodeSpan *sp, const InstView 
 {
     g_final = {mx, my, sx, sy, ef};
     g_slices.push_back(v->slices);
+    g_items = sp->count;
     return stub_launch_finalize(p, sp, v, M, n, mx, my, sx, sy, ef, t, s);
 }
 }  // namespace msdd
@@ -337,6 +340,47 @@ static void scenario_budget()
     }
 }
 
+// ---------------------------------------------------------------------------
+static void scenario_fp64()
+{
+    // 29 nodes at N = 6400: 100 items of 64 paths per node, or 25 of 256
+    Problem p(17);
+    const size_t n = 17 * 17, np = 19 * 19, nb = 8 * 17;
+    const size_t large = 2 * n * 8 + 2 * np * 12 + 2 * nb * 12 + 29 * (25 * sizeof(msdd::Partial) + sizeof(msdd::NodeSpan)) +
+                         29 * 5 * 8 + sizeof(msdd::InstView) + 64;
+    const size_t small = large + 29 * 75 * sizeof(msdd::Partial);
+    size_t tables = 0;
+    auto run = [&](size_t budget, uint32_t items, size_t bytes) {
+        Fixture f(budget);
+        f.add(p, make_desc(17, 2, MESH_SDD_FP64, 20));
+        tables = in_use(f.ctx);
+        g_most_in_use = 0;
+        g_watched = f.ctx;
+        mesh_sdd_step st = make_step(p, 6400, 0);
+        mesh_sdd_ticket t = 0;
+        Out o(29, 0);
+        check(mesh_sdd_submit(f.h[0], &st, &t) == MESH_SDD_OK, "submit within a budget of %zu", budget);
+        check(mesh_sdd_wait(f.ctx, t, &o.r, -1) == MESH_SDD_OK, "wait");
+        check(g_items == items, "%u items per node", g_items);
+        check(g_most_in_use == tables + bytes, "%zu bytes charged, %zu allocated", (size_t)g_most_in_use - tables, bytes);
+        g_watched = nullptr;
+        // the blocking and the no-allocation solve have the same sums
+        check(mesh_sdd_solve_interfaces(f.h[0], &st, &o.r) == MESH_SDD_OK && g_items == items, "solve");
+        mesh_sdd_step dev = make_step(p, 6400, 1);
+        Out d(29, 1);
+        check(mesh_sdd_solve_interfaces_noalloc(f.h[0], &dev, &d.r) == MESH_SDD_OK && g_items == items, "noalloc");
+    };
+    run(0, 100, small);
+    run(16 * (small - large), 100, small);
+    run(16 * (small - large) - 16, 25, large);
+    run(large, 25, large);   // what a request of 256-path items always fitted
+    Fixture f(large - 1);
+    f.add(p, make_desc(17, 2, MESH_SDD_FP64, 20));
+    mesh_sdd_step st = make_step(p, 6400, 0);
+    mesh_sdd_ticket t = 0;
+    check(mesh_sdd_submit(f.h[0], &st, &t) == MESH_SDD_E_BUDGET, "a request past the budget");
+}
+
 int main(int argc, char **argv)
 {
     const std::string what = argc > 1 ? argv[1] : "";
@@ -344,6 +388,8 @@ int main(int argc, char **argv)
         scenario_arrays();
     else if (what == "budget")
         scenario_budget();
+    else if (what == "fp64")
+        scenario_fp64();
     else {
         std::fprintf(stderr, "unknown scenario %s\n", what.c_str());
         return 2;
