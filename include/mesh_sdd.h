@@ -432,8 +432,8 @@ typedef struct {
                                         0 = taken from step->bnd_t1                    */
     int32_t solver;                  /* subdomain solves: 0 automatic, 1 each subdomain
                                         resident in LDS (E_INVAL if one does not fit:
-                                        at most 4096 interior nodes), 2 whole-grid
-                                        sweeps in global memory                        */
+                                        at most 4096 interior and 1024 boundary
+                                        nodes), 2 the whole grid, in tiles             */
     int32_t reserved;                /* must be 0                                      */
     double fe_cfl;                   /* fraction of the stability limit, (0, 1];
                                         0 means 0.9                                    */

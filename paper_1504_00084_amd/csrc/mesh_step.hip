@@ -232,7 +232,8 @@ __device__ __forceinline__ double fe_update(const FeCoef &k, double bx, double b
 // LDS, one barrier per substep.  A thread owns R nodes of a column (its north
 // and south neighbours then are its own registers but for two), the last
 // segment of a column overlapping the one before it; the threads from
-// `first_bnd` on own a boundary node each.  Bound: LDS reads and FP64 issue of
+// `first_bnd` on own a boundary node each (beside their segment where the
+// workgroup is full).  Bound: LDS reads and FP64 issue of
 // one CU (33x33 box: 5 + 2 LDS values and 28 operations per node and
 // substep, about 420 clocks of each), then the barrier.  16 boxes of 33x33,
 // 729 substeps: 1.10 ms with a node per thread, four divisions per update and
@@ -257,7 +258,7 @@ __global__ __launch_bounds__(kSubBlock) void subdomain_lds_kernel(MeshStepArgs a
     const FeCoef k = fe_coef<P2>(a);
     const int segs = (Px - 1) * ((Py - 1 + R - 1) / R);
     const bool inner = tid < segs;
-    int q0 = 0;   // first node of the segment, or the boundary node
+    int q0 = 0, qb = 0;   // first node of the segment, the boundary node
     double bx[R], by[R], x[R], y[R];
     if (inner) {
         const int ca = 1 + tid % (Px - 1), grp = tid / (Px - 1);
@@ -292,7 +293,7 @@ __global__ __launch_bounds__(kSubBlock) void subdomain_lds_kernel(MeshStepArgs a
             cc = 1 + tb - 2 * Bx - (By - 2);
         }
         const int g = (j0 + cc) * a.n_xi + i0 + ca;
-        q0 = cc * Bx + ca;
+        qb = cc * Bx + ca;
         bx0 = a.x0[g];
         by0 = a.y0[g];
         bx1 = a.tx1[g];
@@ -337,8 +338,8 @@ __global__ __launch_bounds__(kSubBlock) void subdomain_lds_kernel(MeshStepArgs a
         }
         if (edge) {
             const double th1 = (double)(l + 1) / (double)a.L;
-            nxt[q0] = (1.0 - th1) * bx0 + th1 * bx1;
-            nxt[n + q0] = (1.0 - th1) * by0 + th1 * by1;
+            nxt[qb] = (1.0 - th1) * bx0 + th1 * bx1;
+            nxt[n + qb] = (1.0 - th1) * by0 + th1 * by1;
         }
         __syncthreads();
         double *t = cur;

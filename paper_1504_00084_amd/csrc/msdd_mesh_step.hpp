@@ -21,30 +21,34 @@ constexpr int kTileRim = 8;                     // the rim around them = substep
 constexpr int kTileSide = kTileCore + 2 * kTileRim;
 constexpr int kTileRows = 2;                    // and nodes per thread
 
-// Workgroup of the LDS solve of one (P_xi + 1) x (P_eta + 1) subdomain: rows
-// of a column per thread, the first thread that owns a boundary node, the
-// block.  block = 0 where two time levels do not fit the LDS or the threads do
-// not suffice: the tiles take such subdomains.  The rows are those with the
+// Workgroup of the LDS solve of one (P_xi + 1) x (P_eta + 1) subdomain that
+// subdomain_fits_lds admits: rows of a column per thread, the first thread
+// that owns a boundary node, the block.  Where the workgroup has too few
+// threads for a segment or a boundary node each, its last threads own both.
+// block = 0 for other subdomains.  The rows are those with the
 // fewest updates in a row on a SIMD, and of these the most, which read the
 // least LDS: 33 x 33 boxes take 4; 10 x 36 boxes (161 x 145 grid, 16 x 4) 632 us
 // with 4 rows, where 2 waves of the CU work, 352 with 2.
 struct SubShape {
     int rows, first_bnd, block;
+    bool shared;   // some threads own a segment and a boundary node
 };
 inline SubShape subdomain_shape(int P_xi, int P_eta)
 {
-    const long nb = 2L * (P_xi + 1) + 2L * (P_eta - 1);
-    if (P_xi < 2 || P_eta < 2 || (size_t)4 * (P_xi + 1) * (P_eta + 1) * sizeof(double) > kSubLdsMax)
-        return SubShape{0, 0, 0};
-    SubShape best{0, 0, 0};
+    const long nb = 2L * (P_xi + 1) + 2L * (P_eta - 1), bnd = (nb + 63) / 64 * 64;
+    SubShape best{0, 0, 0, false};
+    if (P_xi < 2 || P_eta < 2 || nb > kSubBlock || (size_t)4 * (P_xi + 1) * (P_eta + 1) * sizeof(double) > kSubLdsMax)
+        return best;
     long best_cost = 0;
     for (int rows : {8, 4, 2, 1}) {
         if (P_eta - 1 < rows) continue;
-        const long segs = (long)(P_xi - 1) * ((P_eta - 1 + rows - 1) / rows);
-        const long first = (segs + 63) / 64 * 64, block = first + (nb + 63) / 64 * 64;
+        const long segs = (long)(P_xi - 1) * ((P_eta - 1 + rows - 1) / rows), inner = (segs + 63) / 64 * 64;
         const long cost = (segs + 255) / 256 * rows;   // node updates one after the other on a SIMD
-        if (block > kSubBlock || (best.block && cost >= best_cost)) continue;
-        best = SubShape{rows, (int)first, (int)block};
+        const bool shared = inner + bnd > kSubBlock;
+        if (inner > kSubBlock || (best.block && (shared > best.shared || (shared == best.shared && cost >= best_cost))))
+            continue;
+        const long first = shared ? kSubBlock - bnd : inner;
+        best = SubShape{rows, (int)first, (int)(shared ? kSubBlock : first + bnd), shared};
         best_cost = cost;
     }
     return best;
