@@ -191,8 +191,10 @@ int solve_dev(mesh_sdd *inst, const MpOpts &o, const double *x0, const double *y
     const bool fits = msdd::subdomain_fits_lds(a.P_xi, a.P_eta);
     if (with_interfaces && o.solver == 1 && !fits)
         return fail(MESH_SDD_E_INVAL, "a %dx%d subdomain does not fit in LDS", a.P_xi + 1, a.P_eta + 1);
-    // (left alone, tiles where threads would own a segment and a boundary node)
-    if (with_interfaces && fits && o.solver != 2 && (o.solver == 1 || !msdd::subdomain_shape(a.P_xi, a.P_eta).shared)) {
+    const bool exact = msdd::exact_scaling(d.n_xi, d.n_eta);
+    if (with_interfaces && fits && o.solver != 2 &&
+        (o.solver == 1 || !msdd::subdomain_tiles(a.P_xi, a.P_eta, (long)a.sub_xi * a.sub_eta, ctx->cu_count,
+                                                 msdd::subdomain_shape(a.P_xi, a.P_eta, exact), exact))) {
         HIP_TRY(msdd::launch_subdomain_lds(a, x_new, y_new, st));
         return MESH_SDD_OK;
     }

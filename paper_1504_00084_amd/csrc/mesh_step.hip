@@ -229,17 +229,18 @@ __device__ __forceinline__ double fe_update(const FeCoef &k, double bx, double b
 // Subdomain solves with the subdomain resident in LDS
 // ---------------------------------------------------------------------------
 // One workgroup per subdomain, all substeps in one launch, two time levels in
-// LDS, one barrier per substep.  A thread owns R nodes of a column (its north
-// and south neighbours then are its own registers but for two), the last
-// segment of a column overlapping the one before it; the threads from
-// `first_bnd` on own a boundary node each (beside their segment where the
-// workgroup is full).  Bound: LDS reads and FP64 issue of
-// one CU (33x33 box: 5 + 2 LDS values and 28 operations per node and
+// LDS, one barrier per substep.  Without divisions (P2) a thread owns R nodes
+// of a column (its north and south neighbours then are its own registers but
+// for two), the last segment of a column overlapping the one before it; with
+// them it owns the nodes t, t + inner, ... of the box.  The threads from
+// `first_bnd` on own a boundary node each (beside their other nodes where the
+// workgroup is full).  Bound: LDS reads and FP64 issue of one CU (33x33 box
+// without divisions: 5 + 2 LDS values and 28 operations per node and
 // substep, about 420 clocks of each), then the barrier.  16 boxes of 33x33,
 // 729 substeps: 1.10 ms with a node per thread, four divisions per update and
-// two barriers, 0.43 ms now.
+// two barriers, 0.34 ms now.
 template <bool P2, int R>
-__global__ __launch_bounds__(kSubBlock) void subdomain_lds_kernel(MeshStepArgs a, int first_bnd,
+__global__ __launch_bounds__(kSubBlock) void subdomain_lds_kernel(MeshStepArgs a, int inner, int first_bnd,
                                                                   double *__restrict__ x_new,
                                                                   double *__restrict__ y_new)
 {
@@ -256,17 +257,21 @@ __global__ __launch_bounds__(kSubBlock) void subdomain_lds_kernel(MeshStepArgs a
         cur[n + q] = a.y0[g];
     }
     const FeCoef k = fe_coef<P2>(a);
-    const int segs = (Px - 1) * ((Py - 1 + R - 1) / R);
-    const bool inner = tid < segs;
-    int q0 = 0, qb = 0;   // first node of the segment, the boundary node
+    // own interior nodes, -1: none; q[r] = q[0] + r Bx in a segment (and one
+    // node is a segment of one)
+    constexpr bool kSegment = P2 || R == 1;
+    const int segs = (Px - 1) * ((Py - 1 + R - 1) / R), nin = (Px - 1) * (Py - 1);
+    int q[R], qb = 0;   // and the boundary node
     double bx[R], by[R], x[R], y[R];
-    if (inner) {
-        const int ca = 1 + tid % (Px - 1), grp = tid / (Px - 1);
-        const int cc = min(1 + grp * R, Py - R);
-        q0 = cc * Bx + ca;
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const int g = (j0 + cc + r) * a.n_xi + i0 + ca;
+    for (int r = 0; r < R; ++r) {
+        const int k1 = kSegment ? tid : tid + r * inner;
+        q[r] = -1;
+        if (tid < inner && k1 < (kSegment ? segs : nin)) {
+            const int ca = 1 + k1 % (Px - 1), row = k1 / (Px - 1);
+            const int cc = kSegment ? min(1 + row * R, Py - R) + r : 1 + row;
+            const int g = (j0 + cc) * a.n_xi + i0 + ca;
+            q[r] = cc * Bx + ca;
             bx[r] = a.tx1[g] * k.sx;
             by[r] = a.ty1[g] * k.sy;
             x[r] = a.x0[g];
@@ -301,8 +306,8 @@ __global__ __launch_bounds__(kSubBlock) void subdomain_lds_kernel(MeshStepArgs a
     }
     __syncthreads();
     for (int l = 0; l < a.L; ++l) {
-        if (inner) {
-            const double *px = cur + q0, *py = px + n;
+        if (kSegment && q[0] >= 0) {
+            const double *px = cur + q[0], *py = px + n;
             double e[R], w[R];
 #pragma unroll
             for (int r = 0; r < R; ++r) {
@@ -319,7 +324,7 @@ __global__ __launch_bounds__(kSubBlock) void subdomain_lds_kernel(MeshStepArgs a
             }
             double below2 = py[-Bx];
             const double above2 = py[R * Bx];
-            double *ox = nxt + q0, *oy = ox + n;
+            double *ox = nxt + q[0], *oy = ox + n;
 #pragma unroll
             for (int r = 0; r < R; ++r) {
                 const double v = fe_update<P2>(k, bx[r], by[r], x[r], e[r], w[r], r + 1 < R ? x[r + 1] : above, below);
@@ -336,6 +341,17 @@ __global__ __launch_bounds__(kSubBlock) void subdomain_lds_kernel(MeshStepArgs a
                 oy[r * Bx] = v;
             }
         }
+        if (!kSegment) {
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+                if (q[r] >= 0) {
+                    const double *px = cur + q[r], *py = px + n;
+                    x[r] = fe_update<P2>(k, bx[r], by[r], x[r], px[1], px[-1], px[Bx], px[-Bx]);
+                    y[r] = fe_update<P2>(k, bx[r], by[r], y[r], py[1], py[-1], py[Bx], py[-Bx]);
+                    nxt[q[r]] = x[r];
+                    nxt[n + q[r]] = y[r];
+                }
+        }
         if (edge) {
             const double th1 = (double)(l + 1) / (double)a.L;
             nxt[qb] = (1.0 - th1) * bx0 + th1 * bx1;
@@ -346,15 +362,13 @@ __global__ __launch_bounds__(kSubBlock) void subdomain_lds_kernel(MeshStepArgs a
         cur = nxt;
         nxt = t;
     }
-    if (inner) {
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const int q = q0 + r * Bx;
-            const int g = (j0 + q / Bx) * a.n_xi + i0 + q % Bx;
+    for (int r = 0; r < R; ++r)
+        if (q[r] >= 0) {
+            const int g = (j0 + q[r] / Bx) * a.n_xi + i0 + q[r] % Bx;
             x_new[g] = x[r];
             y_new[g] = y[r];
         }
-    }
 }
 
 // ---------------------------------------------------------------------------
@@ -840,8 +854,6 @@ __global__ void transfer_p1_kernel(TransferArgs a)
 // ---------------------------------------------------------------------------
 // Launchers
 // ---------------------------------------------------------------------------
-static bool power_of_two(int n) { return n > 0 && (n & (n - 1)) == 0; }
-
 size_t edge_gen_lds_bytes(int n_max) { return (size_t)3 * (size_t)n_max * sizeof(double); }
 
 hipError_t launch_edge_gen(const double *rho, const double *rho_xi, const double *rho_eta, int n_xi, int n_eta,
@@ -884,21 +896,23 @@ static void launch_sub(const MeshStepArgs &a, const SubShape &h, double *x_new, 
 {
     const dim3 grid(a.sub_xi * a.sub_eta), block(h.block);
     const size_t lds = 2 * subdomain_lds_bytes(a.P_xi, a.P_eta);
-    if (h.rows == 8)
-        hipLaunchKernelGGL((subdomain_lds_kernel<P2, 8>), grid, block, lds, s, a, h.first_bnd, x_new, y_new);
-    else if (h.rows == 4)
-        hipLaunchKernelGGL((subdomain_lds_kernel<P2, 4>), grid, block, lds, s, a, h.first_bnd, x_new, y_new);
-    else if (h.rows == 2)
-        hipLaunchKernelGGL((subdomain_lds_kernel<P2, 2>), grid, block, lds, s, a, h.first_bnd, x_new, y_new);
+    auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, lds, s, a, h.inner, h.first_bnd, x_new, y_new); };
+    if (h.nodes == 4)
+        launch(subdomain_lds_kernel<P2, 4>);
+    else if (h.nodes == 3)
+        launch(subdomain_lds_kernel<false, 3>);   // (with divisions only)
+    else if (h.nodes == 2)
+        launch(subdomain_lds_kernel<P2, 2>);
     else
-        hipLaunchKernelGGL((subdomain_lds_kernel<P2, 1>), grid, block, lds, s, a, h.first_bnd, x_new, y_new);
+        launch(subdomain_lds_kernel<P2, 1>);
 }
 
 hipError_t launch_subdomain_lds(const MeshStepArgs &a, double *x_new, double *y_new, hipStream_t s)
 {
-    const SubShape h = subdomain_shape(a.P_xi, a.P_eta);
+    const bool exact = exact_scaling(a.n_xi, a.n_eta);
+    const SubShape h = subdomain_shape(a.P_xi, a.P_eta, exact);
     if (!h.block) return hipErrorInvalidValue;
-    if (power_of_two(a.n_xi - 1) && power_of_two(a.n_eta - 1))
+    if (exact)
         launch_sub<true>(a, h, x_new, y_new, s);
     else
         launch_sub<false>(a, h, x_new, y_new, s);
@@ -920,7 +934,7 @@ hipError_t launch_fe_sweep(const MeshStepArgs &a, const double *cx, const double
                          blocks_of((size_t)std::max(niy, 0), kTileCore) * a.sub_xi * a.sub_eta;
     if (tiles == 0) return hipSuccess;   // boxes of one cell: every node is Dirichlet
     if (tiles > 0x7FFFFFFFu) return hipErrorInvalidValue;
-    const bool p2 = power_of_two(a.n_xi - 1) && power_of_two(a.n_eta - 1);
+    const bool p2 = exact_scaling(a.n_xi, a.n_eta);
     const dim3 grid((unsigned)tiles), block(kTileSide * kTileSide / kTileRows);
     if (p2 && per)
         hipLaunchKernelGGL((fe_tile_kernel<true, true>), grid, block, 0, s, a, cx, cy, nx, ny);

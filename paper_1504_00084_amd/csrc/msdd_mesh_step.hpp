@@ -21,37 +21,66 @@ constexpr int kTileRim = 8;                     // the rim around them = substep
 constexpr int kTileSide = kTileCore + 2 * kTileRim;
 constexpr int kTileRows = 2;                    // and nodes per thread
 
+inline bool power_of_two(int n) { return n > 0 && (n & (n - 1)) == 0; }
+
+// Whether both cell counts are powers of two: the updates then need no
+// divisions (fe_update).
+inline bool exact_scaling(int n_xi, int n_eta) { return power_of_two(n_xi - 1) && power_of_two(n_eta - 1); }
+
 // Workgroup of the LDS solve of one (P_xi + 1) x (P_eta + 1) subdomain that
-// subdomain_fits_lds admits: rows of a column per thread, the first thread
-// that owns a boundary node, the block.  Where the workgroup has too few
-// threads for a segment or a boundary node each, its last threads own both.
-// block = 0 for other subdomains.  The rows are those with the
-// fewest updates in a row on a SIMD, and of these the most, which read the
-// least LDS: 33 x 33 boxes take 4; 10 x 36 boxes (161 x 145 grid, 16 x 4) 632 us
-// with 4 rows, where 2 waves of the CU work, 352 with 2.
+// subdomain_fits_lds admits: nodes per thread, the threads that own interior
+// nodes, the first one that owns a boundary node, the block, and the node
+// updates that follow one another on a SIMD.  Where the workgroup has too few
+// threads for both, its last threads own interior and boundary nodes.
+// block = 0 for other subdomains.
+// Without divisions (`exact`) a thread owns a segment of a column, which saves
+// LDS reads: as many rows as leave the fewest updates in a row, of equal ones
+// two, then one (33 x 33 boxes, 300 substeps: two rows 151 us, one 169, four
+// 181).  With divisions the updates bound the solve, so the nodes are dealt
+// out evenly, one to four to a thread: 48 x 48 cells 9 updates in a row, 12
+// in segments of four.  41 x 41 boxes, 300 substeps: 557 us, in segments of
+// four 699, of eight, which spilled registers, 756.
 struct SubShape {
-    int rows, first_bnd, block;
-    bool shared;   // some threads own a segment and a boundary node
+    int nodes, inner, first_bnd, block, cost;
 };
-inline SubShape subdomain_shape(int P_xi, int P_eta)
+inline SubShape subdomain_shape(int P_xi, int P_eta, bool exact)
 {
-    const long nb = 2L * (P_xi + 1) + 2L * (P_eta - 1), bnd = (nb + 63) / 64 * 64;
-    SubShape best{0, 0, 0, false};
-    if (P_xi < 2 || P_eta < 2 || nb > kSubBlock || (size_t)4 * (P_xi + 1) * (P_eta + 1) * sizeof(double) > kSubLdsMax)
+    const long nin = (long)(P_xi - 1) * (P_eta - 1), nb = 2L * (P_xi + 1) + 2L * (P_eta - 1), bnd = (nb + 63) / 64 * 64;
+    SubShape best{0, 0, 0, 0, 0};
+    if (P_xi < 2 || P_eta < 2 || nb > kSubBlock || nin > (long)kSubBlock * kSubPerThread ||
+        (size_t)4 * (P_xi + 1) * (P_eta + 1) * sizeof(double) > kSubLdsMax)
         return best;
-    long best_cost = 0;
-    for (int rows : {8, 4, 2, 1}) {
-        if (P_eta - 1 < rows) continue;
-        const long segs = (long)(P_xi - 1) * ((P_eta - 1 + rows - 1) / rows), inner = (segs + 63) / 64 * 64;
-        const long cost = (segs + 255) / 256 * rows;   // node updates one after the other on a SIMD
-        const bool shared = inner + bnd > kSubBlock;
-        if (inner > kSubBlock || (best.block && (shared > best.shared || (shared == best.shared && cost >= best_cost))))
-            continue;
-        const long first = shared ? kSubBlock - bnd : inner;
-        best = SubShape{rows, (int)first, (int)(shared ? kSubBlock : first + bnd), shared};
-        best_cost = cost;
+    auto take = [&](int nodes, long threads, long cost) {
+        const long inner = (threads + 63) / 64 * 64, first = inner + bnd > kSubBlock ? kSubBlock - bnd : inner;
+        if (inner > kSubBlock || (best.block && cost >= best.cost)) return;
+        best = SubShape{nodes, (int)inner, (int)first, (int)(first + bnd > inner ? first + bnd : inner), (int)cost};
+    };
+    if (exact) {
+        for (int rows : {2, 1, 4}) {
+            if (P_eta - 1 < rows) continue;
+            const long segs = (long)(P_xi - 1) * ((P_eta - 1 + rows - 1) / rows);
+            take(rows, segs, (segs + 255) / 256 * rows);
+        }
+    } else {
+        const long full = (nin - 1) / kSubBlock;   // nodes that every thread owns
+        take((int)full + 1, full ? kSubBlock : nin, 4 * full + (nin - full * kSubBlock + 255) / 256);
     }
     return best;
+}
+
+// Whether tiles of the whole grid advance subdomains faster than one
+// workgroup for each does, by the time of a substep on `cus` compute units:
+// a workgroup's updates one after the other (80 ns each without divisions,
+// 270 with them; 220 ns for threads that own boundary nodes as well), or an eighth of a launch (630 ns) and the tiles that follow
+// one another on a compute unit.  4 x 4 boxes of 61 x 61, 300 substeps: LDS 1210
+// us, tiles 580; 2 x 2 of 65 x 65 without divisions 429 and 326; 12 x 12 of 42 x
+// 42, 100 substeps: LDS 225 us, tiles 781.
+inline bool subdomain_tiles(int P_xi, int P_eta, long boxes, long cus, const SubShape &h, bool exact)
+{
+    const long tiles = boxes * ((P_xi - 1 + kTileCore - 1) / kTileCore) * ((P_eta - 1 + kTileCore - 1) / kTileCore);
+    const long lds = (boxes + cus - 1) / cus *
+                     ((exact ? 100 + 80 * (long)h.cost : 30 + 270 * (long)h.cost) + (h.first_bnd < h.inner ? 220 : 0));
+    return lds > 630 + (tiles + cus - 1) / cus * (exact ? 420 : 1160);
 }
 
 // Everything the targets / subdomain / sweep kernels read; device pointers.

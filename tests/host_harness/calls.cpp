@@ -404,18 +404,24 @@ static void scenario_boxes()
 {
     // every subdomain of at most 4096 interior and 1024 boundary nodes
     // (subdomain_fits_lds) has a workgroup with a thread for each boundary
-    // node and for each segment of a column
+    // node and threads for all interior ones
     long boxes = 0;
     for (int px = 2; px <= 511; ++px)
         for (int py = 2; py <= 511; ++py) {
             const long nin = (long)(px - 1) * (py - 1), nb = 2L * (px + 1) + 2L * (py - 1);
             if (nin > (long)msdd::kSubBlock * msdd::kSubPerThread || nb > msdd::kSubBlock) continue;
             ++boxes;
-            const msdd::SubShape h = msdd::subdomain_shape(px, py);
-            const long segs = h.rows ? (long)(px - 1) * ((py - 1 + h.rows - 1) / h.rows) : 0;
-            check(h.block >= 64 && h.block <= msdd::kSubBlock && h.block % 64 == 0 && h.rows <= py - 1 && segs <= h.block &&
-                      h.first_bnd >= 0 && h.first_bnd + nb <= h.block && (h.shared || segs <= h.first_bnd),
-                  "%d x %d cells: %d rows, boundary from %d, block %d", px, py, h.rows, h.first_bnd, h.block);
+            for (bool exact : {false, true}) {
+                if (exact && !msdd::power_of_two(px)) continue;   // they divide a power of two
+                if (exact && !msdd::power_of_two(py)) continue;
+                const msdd::SubShape h = msdd::subdomain_shape(px, py, exact);
+                const long per = h.nodes, segs = per ? (long)(px - 1) * ((py - 1 + per - 1) / per) : 0;
+                check(h.block >= 64 && h.block <= msdd::kSubBlock && h.block % 64 == 0 && h.inner <= h.block && per <= 4 &&
+                          (exact ? per <= py - 1 && segs <= h.inner : per * h.inner >= nin) && h.first_bnd >= 0 &&
+                          h.first_bnd + nb <= h.block && (h.first_bnd >= h.inner || h.block == msdd::kSubBlock),
+                      "%d x %d cells: %d nodes on %d threads, boundary from %d, block %d", px, py, h.nodes, h.inner,
+                      h.first_bnd, h.block);
+            }
         }
     check(boxes > 10000, "%ld boxes", boxes);
     // forced on boxes of 3 x 500 cells, by themselves the tiles'
