@@ -1191,8 +1191,9 @@ struct Src64Job {
 // waves per SIMD (at most 128 registers).  PER: the instance's periodic flags
 // (PER & 1: xi, PER >> 1: eta).  MODE: where the padded rho table is read
 // (path_fp64.hpp): 1, the whole table in LDS, taken where it fits; 2, windows
-// of it per job, as in paths_fp32_win; 0, global memory, for a launch that has
-// no room for its job list (the no-allocation solve).
+// of it per job, as in paths_fp32_win; 0, global memory, for launches too short
+// for windows and for one that has no room for its job list (the no-allocation
+// solve).
 // Bound: VALU issue (about 200 vector instructions per path-step, 90 % of the
 // issue slots).  The form before it -- one thread per path, the library's log,
 // sincospi, sqrt and exp, twelve 8-byte gathers per substep, no lane refill --

@@ -1031,6 +1031,15 @@ WorkRange range_of(const Request &r, uint32_t slot, size_t base, size_t first, s
     return w;
 }
 
+// Substeps of a wave up to which an FP64 window does not pay: bringing its 163
+// kB takes a workgroup about as long as 64 substeps of its 16 waves gain, and
+// jobs bind a wave to a workgroup.  Such launches read rho from global memory:
+// 193^2, 8 x 8, N = 1000, K = 1 (64): 291 us in windows, 158 without; 145^2, 4 x 4,
+// N = 50, K = 60 (199): 360 and 160; 513^2, 16 x 16, N = 1000, K = 4 (1024): 832
+// and 737, K = 16 (4096): 2009 and 2218; 257^2, periodic, wide substeps, N =
+// 1000, K = 20 (1280): 932 and 1173.
+constexpr double kWindowWork64 = 1024.0;
+
 // FP64 launch of one request, enqueued only: wait_launch waits for it.
 // Caller holds gpu_mu.
 int run_fp64_launch(mesh_sdd_ctx *ctx, Request &r, Arena *arena = nullptr)
@@ -1049,11 +1058,16 @@ int run_fp64_launch(mesh_sdd_ctx *ctx, Request &r, Arena *arena = nullptr)
     v.grid = (uint32_t)ctx->cu_count;
     v.head = r.steps_total.as<uint32_t>() + 16;
     v.mode = 1;
-    if (window_bytes(2, v.n_xi, v.n_eta) > window_limit(2)) {
-        // windows: one job per grid block, cut so that every workgroup gets
-        // about 32 of them (at least two items for each of its waves)
+    // windows: one job per grid block, cut so that every workgroup gets
+    // about 32 of them (at least two items for each of its waves)
+    const size_t jmax = std::max<size_t>(64, v.n_items / ((size_t)ctx->cu_count * 32) + 1);
+    // substeps of a wave that a window then serves
+    const double per_window = std::min((double)jmax, (double)v.n_items / ctx->cu_count) *
+                              (double)((std::min<int64_t>(r.chunk_paths, r.N) + 63) / 64) * v.K;
+    if (window_bytes(2, v.n_xi, v.n_eta) > window_limit(2) && per_window <= kWindowWork64) {
+        v.mode = 0;
+    } else if (window_bytes(2, v.n_xi, v.n_eta) > window_limit(2)) {
         std::vector<msdd::WinJob> jobs;
-        const size_t jmax = std::max<size_t>(64, v.n_items / ((size_t)ctx->cu_count * 32) + 1);
         JobSizer sizer((double)v.n_items, r.v.K >= 64 ? v.n_items : 32 * (size_t)ctx->cu_count,
                        (size_t)ctx->cu_count, false);
         for (const BlockRun &b : r.ss->blocks) {
