@@ -286,7 +286,7 @@ int mesh_sdd_desc_check(const mesh_sdd_desc *desc);
  * rank order into caller arrays of length M. */
 int mesh_sdd_desc_interface_nodes(const mesh_sdd_desc *desc, int32_t *i, int32_t *j);
 
-/* Work order of the FP32 kernels for a descriptor and an interface stride
+/* Work order of the path kernels for a descriptor and an interface stride
  * (0 or 1: every interface node; else the sampling of section 3.6, with the
  * same validation as mesh_sdd_step.interface_stride).  The nodes that run
  * paths are stepped block by block (blocks in Z order, ranks ascending inside
@@ -297,9 +297,12 @@ int mesh_sdd_desc_interface_nodes(const mesh_sdd_desc *desc, int32_t *i, int32_t
  * windows that also hold dt rho_eta per node, 114 x 114 nodes when square,
  * blocks of 54 nodes, 30 nodes of margin.  Kind 1 where
  * its window holds the whole grid, else kind 0 where that one does, else
- * kind 1 for grids under 400 nodes per axis and kind 0 above.  The order changes no result.  Returns the
- * number of nodes Ms >= 0 or a negative error.  When `ranks` is not NULL,
- * writes the Ms interface ranks in work order (caller array of length Ms).
+ * kind 1 for grids under 400 nodes per axis and kind 0 above.  FP64
+ * descriptors: kind 2, windows of rho alone in double precision with one node
+ * more on each side, (width + 2) (height + 2) <= 143^2, blocks of 51 nodes, 45
+ * nodes of margin (launches too short for windows read the whole table in the
+ * same order).  The order changes no result.  Returns the number of nodes
+ * Ms >= 0 or a negative error.  When `ranks` is not NULL, writes the Ms interface ranks in work order (caller array of length Ms).
  * When `n_blocks` is not NULL, writes the block count there; when `blocks`
  * is not NULL too, writes one record of seven int32 per block -- first
  * position, end position, window i0, j0, width, height, kind -- into caller

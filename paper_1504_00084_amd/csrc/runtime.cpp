@@ -1841,7 +1841,7 @@ try {
     tmp.M = (int32_t)tmp.node_i.size();
     std::vector<int32_t> order = sampled_ranks(tmp, interface_stride > 1 ? (int)interface_stride : 1);
     std::vector<BlockRun> runs;
-    order_by_blocks(tmp, layout_of(*desc, default_launch()), order, runs);
+    order_by_blocks(tmp, set_layout(*desc, default_launch()), order, runs);
     if (ranks && !order.empty()) std::memcpy(ranks, order.data(), order.size() * 4);
     if (n_blocks) *n_blocks = (int32_t)runs.size();
     if (blocks) {

@@ -225,7 +225,7 @@ struct Request;
 struct BlockRun {
     int32_t pos_begin, pos_end;
     int32_t i0, j0, tw, th;
-    int32_t kind;   // 0: (rho, dt rho_xi) per node; 1: also dt rho_eta per node
+    int32_t kind;   // 0: (rho, dt rho_xi) per node; 1: also dt rho_eta per node; 2 (FP64): rho, and one node around
 };
 
 // The nodes that run paths for one interface stride.  They are stored in
