@@ -1765,7 +1765,10 @@ hipError_t launch_paths_fp32(const InstView *insts, const WorkRange *ranges, uin
     return hipGetLastError();
 }
 
-size_t paths_fp32_table_lds_bytes(int level, int n_nodes) { return (size_t)n_nodes * (size_t)level * sizeof(float); }
+size_t paths_fp32_table_lds_bytes(int level, int n_nodes)
+{
+    return (size_t)n_nodes * (n_nodes <= kDiffNodes ? 24u : (size_t)level * sizeof(float));
+}
 
 template <int TAB, int PER>
 static void launch_table(int grid, size_t lds, hipStream_t s, const InstView *insts, const WorkRange *ranges,
@@ -1802,11 +1805,11 @@ hipError_t launch_paths_fp32_table(const InstView *insts, const WorkRange *range
         refill_lanes < 1 || refill_lanes > 64 || max_quarters < 1 || max_quarters > 64)
         return hipErrorInvalidValue;
     const Refill rf{refill_lanes, max_quarters};
+    const size_t lds = paths_fp32_table_lds_bytes(level, n_nodes);
     if (n_nodes <= kDiffNodes)
-        launch_table_kind<6>(kind, grid, (size_t)n_nodes * 24u, s, insts, ranges, n_items, head, cap, ends, end_waves, rf);
+        launch_table_kind<6>(kind, grid, lds, s, insts, ranges, n_items, head, cap, ends, end_waves, rf);
     else
-        launch_table_kind<2>(kind, grid, paths_fp32_table_lds_bytes(level, n_nodes), s, insts, ranges, n_items, head,
-                             cap, ends, end_waves, rf);
+        launch_table_kind<2>(kind, grid, lds, s, insts, ranges, n_items, head, cap, ends, end_waves, rf);
     return hipGetLastError();
 }
 
@@ -1818,8 +1821,7 @@ int paths_fp32_table_blocks_per_cu(int level, int n_nodes)
     if (level != 2) return 0;
     const hipError_t e =
         n_nodes <= kDiffNodes
-            ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, paths_fp32<kTableBlock, 6, 0>, kTableBlock,
-                                                           (size_t)n_nodes * 24u)
+            ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, paths_fp32<kTableBlock, 6, 0>, kTableBlock, lds)
             : hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, paths_fp32<kTableBlock, 2, 0>, kTableBlock, lds);
     return e == hipSuccess ? n : 0;
 }

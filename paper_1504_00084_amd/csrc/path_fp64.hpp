@@ -49,7 +49,8 @@ __device__ __forceinline__ double sqrt64(double a)
 }
 
 // log(u), u = (2 floor(w / 2^9) + 1) 2^-24.  The odd integer is exact in
-// FP32, whose bits give u = 2^e f with f in [sqrt(1/2), sqrt(2)); f - 1 and
+// FP32, whose bits give u = 2^e f with f in [sqrt(1/2), sqrt(2)) (the split of
+// FreeBSD's and musl's logf: add the bits of 1, take off those of sqrt(1/2)); f - 1 and
 // f + 1 are exact, s = (f - 1) / (f + 1), log f = 2 s + s^3 P(s^2) (the atanh
 // series; P of degree 6, error below 4e-16 of a term that is at most 1e-2 of
 // the result).

@@ -1012,7 +1012,7 @@ int wait_launch(mesh_sdd_ctx *ctx, int rc, double *ms)
     ctx->launched = false;
     *ms = t;
     if (rc != MESH_SDD_OK) return rc;
-    if (se != hipSuccess) return fail(MESH_SDD_E_DEVICE, "path kernel failed: %s", hipGetErrorString(se));
+    if (se != hipSuccess) return fail(MESH_SDD_E_DEVICE, "a launch of the solve failed: %s", hipGetErrorString(se));
     return MESH_SDD_OK;
 }
 
