@@ -415,11 +415,15 @@ int fp64_chunk(const mesh_sdd &inst, int64_t N)
 // the last items are short (33^2 bump, N = 10^4: 1240 items of 256 on 4096
 // waves 1.22 ms, 4867 slices 0.48); above 8 chunks per wave whole chunks are as
 // fast.  Not for paths of fewer than 64 substeps, whose items are short
-// anyway and whose records cost more than that gains.  0: whole chunks.  The
-// results are the same either way.
+// anyway and whose records cost more than that gains, nor for more nodes than
+// half the waves with a second and last slice of few paths (129^2, 32 x 32, 7040
+// nodes, N = 85, a slice of 21: 1.14 ms in slices, 0.94 in chunks, whose lanes
+// take the next paths; a third slice of 2, N = 130: 1.35 and 1.56).
+// 0: whole chunks.  The results are the same either way.
 int slices_per_chunk(const mesh_sdd_ctx *ctx, int32_t Ms, int64_t N, int K, int chunk)
 {
     const int64_t waves = (int64_t)ctx->cu_count * (msdd::kTableBlock / 64);
+    if (N > 64 && N < 96 && 2 * (int64_t)Ms > waves) return 0;
     return chunk > 64 && K >= 64 && (int64_t)Ms * ((N + chunk - 1) / chunk) < 8 * waves ? chunk / 64 : 0;
 }
 

@@ -8,6 +8,7 @@
 //            has room for it beside everything else
 //   boxes    a forced LDS solve runs the LDS kernel for every subdomain that
 //            fits it, with threads for all its nodes
+//   slices   no slices of 64 paths where many of their lanes would have no path
 //   fp64     FP64 requests are charged for the partial sums that they allocate
 // Exit status 0 when every check holds; a message names the first failure.
 #define launch_prep_mesh stub_launch_prep_mesh
@@ -450,6 +451,22 @@ static void scenario_boxes()
     }
 }
 
+// ---------------------------------------------------------------------------
+static void scenario_slices()
+{
+    // 381 nodes on 8 CUs: more slices than waves
+    Fixture f;
+    Problem q(193);
+    mesh_sdd *g = f.add(q, make_desc(193, 2, MESH_SDD_FP32, 100, 2));
+    Out o(mesh_sdd_num_interface_nodes(g), 0);
+    for (auto &c : std::vector<std::pair<int64_t, bool>>{{64, true}, {65, false}, {95, false}, {96, true}, {130, true}}) {
+        g_slices.clear();
+        mesh_sdd_step st = make_step(q, c.first, 0);
+        check(mesh_sdd_solve_interfaces(g, &st, &o.r) == MESH_SDD_OK, "solve");
+        check((sliced() == 1) == c.second, "N = %d", (int)c.first);
+    }
+}
+
 int main(int argc, char **argv)
 {
     const std::string what = argc > 1 ? argv[1] : "";
@@ -459,6 +476,8 @@ int main(int argc, char **argv)
         scenario_budget();
     else if (what == "boxes")
         scenario_boxes();
+    else if (what == "slices")
+        scenario_slices();
     else if (what == "fp64")
         scenario_fp64();
     else {
