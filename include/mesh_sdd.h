@@ -206,9 +206,12 @@ typedef struct {
                                         paths inside, at more window refills         */
     int32_t job_split;               /* windowed kernel: a job holds at most 1/job_split
                                         of a workgroup's share of the launch's items
-                                        (1..4096; default 6, and 256 on grids cut
-                                        into several two-field windows); the last
-                                        jobs of a launch are smaller                 */
+                                        (1..4096; default: 6; 32 on grids from 400
+                                        nodes on in three-field windows; 256 on
+                                        grids cut into several two-field windows; in
+                                        launches of several instances jobs of about
+                                        200 items, 6 to 64), and at least 64 items;
+                                        the last jobs of a launch are smaller        */
 } mesh_sdd_launch;
 
 /* ---- context ------------------------------------------------------------ */

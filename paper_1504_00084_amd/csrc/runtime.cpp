@@ -277,10 +277,16 @@ int validate_step(const mesh_sdd &inst, const mesh_sdd_step *s, int64_t *N_out)
 // Default job_split.  Every job ends with its waves waiting for the last of
 // them and starts with a window refill, so jobs are large, and JobSizer makes
 // the last ones small: 1/6 of a workgroup's share (257^2 front, N = 10^5:
-// 403.5 ms; 1/16 404.9, 1/32 409.8; before the last jobs were cut, 1/32 was
-// the best, 411.2).  In a block of a grid cut into two-field windows 1/256:
-// smaller jobs keep the blocks an XCD runs at one time within its L2.
-constexpr int kJobSplit = 6, kJobSplit0 = 256;
+// 403.5 ms; 1/16 404.9, 1/32 409.8).  Smaller jobs keep the blocks that an XCD
+// runs at one time, and their cell records, within its L2, which counts where
+// paths leave their windows for records that the L2 does not hold: 1/256 in a
+// block of a grid cut into two-field windows, 1/32 in three-field windows of
+// grids from kWin1MaxN nodes on (513^2 bump, N = 26481: 1/6 508 ms, 1/32 497, 1/64
+// 503).  A launch of several instances holds such grids among others: jobs of
+// about 200 items, up to 1/64 (path-steps of the launch, 1/6, 1/32, 1/64:
+// 1.5 10^10 36.3, 38.0, 37.9 ms; 6 10^10 183, 168, 174; 2.4 10^11 664, 637, 637;
+// 8.2 10^11 2310, 2256, 2214).
+constexpr int kJobSplit = 6, kJobSplit0 = 256, kJobSplit1 = 32, kJobSplitMost = 64, kJobItems = 200;
 
 mesh_sdd_launch default_launch()
 {
@@ -300,7 +306,7 @@ mesh_sdd_launch default_launch()
     l.max_quarters = 16;
     l.window_kind = 0;     // automatic: see window_kind()
     l.window_margin = 0;   // the kind's default margin
-    l.job_split = 0;       // kJobSplit, and kJobSplit0 in grids cut into several two-field windows
+    l.job_split = 0;       // by the launch (kJobSplit and below)
     return l;
 }
 
@@ -863,6 +869,16 @@ struct JobSizer {
     }
 };
 
+// job_split of the blocks of one kind in a launch of `items` items per
+// workgroup, where `l` sets none.
+size_t job_split(const mesh_sdd_launch &l, bool several, size_t items, int kind, bool blocked, int n_xi, int n_eta)
+{
+    if (l.job_split > 0) return (size_t)l.job_split;
+    if (kind == 0 && blocked) return kJobSplit0;
+    if (several) return std::min<size_t>(kJobSplitMost, std::max<size_t>(kJobSplit, items / kJobItems));
+    return kind == 1 && blocked && std::max(n_xi, n_eta) >= kWin1MaxN ? kJobSplit1 : kJobSplit;
+}
+
 // Cuts a job list, in order, into the per-XCD queues of about equal weight.
 template <class Weight>
 void cut_queues(const std::vector<msdd::WinJob> &jobs, Weight weight, msdd::JobQueues &qs)
@@ -929,8 +945,7 @@ int run_fp32_launch(mesh_sdd_ctx *ctx, std::vector<InstView> &views, const std::
         return fail(MESH_SDD_E_NOMEM, "device allocation of the end-state buffer failed");
     if (level == 2)
         views[0].static_rounds = static_rounds(n_items, end_waves, (int)ranges[0].chunk_paths, views[0].K);
-    // windowed launch: one job per (range, grid block), split so that no job
-    // holds more than 1/job_split of a workgroup's share of the items, in
+    // windowed launch: jobs of the items of one range in one grid block, in
     // block order, cut into per-XCD queues of equal nominal work
     std::vector<msdd::WinJob> jobs;
     msdd::JobQueues qs{};
@@ -938,12 +953,6 @@ int run_fp32_launch(mesh_sdd_ctx *ctx, std::vector<InstView> &views, const std::
     int kind = -2;
     if (level == 3) {
         const size_t share = ((size_t)ctx->cu_count * (size_t)per_cu);
-        const size_t split = l.job_split > 0 ? (size_t)l.job_split : kJobSplit;
-        const size_t split0 = l.job_split > 0 ? (size_t)l.job_split : kJobSplit0;
-        // (at least 64 items, four for each wave, as a workgroup's waves wait
-        // for the last of them at the end of a job)
-        const size_t jmax = std::max<size_t>(64, (n_items + share * split - 1) / (share * split));
-        const size_t jmax0 = std::max<size_t>(64, (n_items + share * split0 - 1) / (share * split0));
         double total = 0.0;
         for (const WorkRange &w : ranges) total += (double)w.count * w.chunk_paths * views[w.inst].K;
         const bool one_long = ranges.size() == 1 && views[ranges[0].inst].K >= 64;
@@ -958,9 +967,13 @@ int run_fp32_launch(mesh_sdd_ctx *ctx, std::vector<InstView> &views, const std::
             for (const BlockRun &b : sets[w.inst]->blocks) {
                 const size_t qa = std::max(lo, (size_t)b.pos_begin * w.chunks);
                 const size_t qb = std::min(hi, (size_t)b.pos_end * w.chunks);
-                const bool blocked0 = b.kind == 0 && (b.tw < v.n_xi || b.th < v.n_eta);
+                const bool blocked = b.tw < v.n_xi || b.th < v.n_eta;
+                // (at least 64 items, four for each wave, as a workgroup's waves
+                // wait for the last of them at the end of a job)
+                const size_t split = job_split(l, ranges.size() > 1, n_items / share, b.kind, blocked, v.n_xi, v.n_eta);
+                const size_t jmax = std::max<size_t>(64, (n_items + share * split - 1) / (share * split));
                 for (size_t q = qa, n; q < qb; q += n) {
-                    n = sizer.next(blocked0 ? jmax0 : jmax, qb - q, item);
+                    n = sizer.next(jmax, qb - q, item);
                     jobs.push_back(msdd::WinJob{(uint32_t)ri, (uint32_t)q, (uint32_t)n, b.i0, b.j0, b.tw, b.th,
                                                 (uint32_t)b.kind});
                 }
@@ -1805,7 +1818,8 @@ try {
     if (out->job_split == 0) {
         int wx = 0, wy = 0;
         window_dims(lay.kind, inst->d.n_xi, inst->d.n_eta, &wx, &wy);
-        out->job_split = lay.kind == 0 && (wx < inst->d.n_xi || wy < inst->d.n_eta) ? kJobSplit0 : kJobSplit;
+        out->job_split = (int32_t)job_split(*out, false, 0, lay.kind, wx < inst->d.n_xi || wy < inst->d.n_eta,
+                                            inst->d.n_xi, inst->d.n_eta);
     }
     return MESH_SDD_OK;
 } catch (...) {
