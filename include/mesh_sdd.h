@@ -211,7 +211,11 @@ typedef struct {
                                         grids cut into several two-field windows; in
                                         launches of several instances jobs of about
                                         200 items, 6 to 64), and at least 64 items;
-                                        the last jobs of a launch are smaller        */
+                                        the last jobs of a launch are smaller.  A
+                                        launch of one instance below 400 nodes per
+                                        axis with fewer than 56 rounds of 64 paths
+                                        per wave takes one to three jobs of equal
+                                        size per workgroup                           */
 } mesh_sdd_launch;
 
 /* ---- context ------------------------------------------------------------ */

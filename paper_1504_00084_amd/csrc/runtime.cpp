@@ -840,11 +840,10 @@ void release_request_buffers(Request &r)
 // of an XCD end together.  513^2 bump, N = 10^4: 204.5 -> 194.0 ms (its jobs of
 // 1/8 of a workgroup's share are 580 items, 17 ms); half or a sixth of the
 // share: 199.6, 196; 16 items at least: the batched mix at small path counts
-// 1 to 2 % slower.  A launch of one instance with long paths (64 substeps or
-// more) and fewer than 32 items per workgroup gives every workgroup a job, of 8
-// items at least (FP64, 153 x 142, N = 101, 2800 items: 2135 -> 1243 us; with
-// short paths the windows cost more than that gains).  The no-allocation solve, whose scratch holds jobs of 64
-// items, takes every job at its full size.
+// 1 to 2 % slower.  A launch of one instance with paths of 64 substeps or more
+// and fewer than 32 items per workgroup gives every workgroup a job, of 8 items
+// at least (FP64, 153 x 142, N = 101, 2800 items: 2135 -> 1243 us; with short
+// paths the windows cost more than that gains).
 struct JobSizer {
     double queue, done = 0.0;   // work of one queue; work of the jobs so far
     double groups;              // workgroups per queue
@@ -868,6 +867,19 @@ struct JobSizer {
         return n;
     }
 };
+
+// An FP32 launch of one instance with fewer rounds of 64 paths per wave than
+// this (and paths of 64 substeps or more) takes jobs of one size, one, two or
+// three for every workgroup: each job costs about a round, in which its waves
+// wait for the last of them, and one more than a multiple of the workgroups a
+// whole job.  Rounds, times with jobs of 64 items, with JobSizer's, with these:
+// 193^2, 8 x 8: 7.7 (N = 761) 2.74, 3.19, 2.56 ms; 15.4 5.14, 5.80, 4.94; 23 7.61,
+// 8.17, 7.37; 257^2 front: 15.4 (N = 1059) 7.09, 5.82, 5.34; 38 12.1, 12.7, 11.7;
+// at 77 and more JobSizer's are as good or better (257^2 front, N = 21186: 94.8,
+// 84.8, 88.0).  Not on grids from kWin1MaxN nodes on, where many paths leave
+// their windows and the blocks' jobs take unequal times (513^2 front, 11 rounds:
+// 6.3 ms with JobSizer's jobs, 10.3 with equal ones).
+constexpr double kEqualRounds = 56.0;
 
 // job_split of the blocks of one kind in a launch of `items` items per
 // workgroup, where `l` sets none.
@@ -946,43 +958,76 @@ int run_fp32_launch(mesh_sdd_ctx *ctx, std::vector<InstView> &views, const std::
     if (level == 2)
         views[0].static_rounds = static_rounds(n_items, end_waves, (int)ranges[0].chunk_paths, views[0].K);
     // windowed launch: jobs of the items of one range in one grid block, in
-    // block order, cut into per-XCD queues of equal nominal work
+    // block order, cut into per-XCD queues of equal nominal work (of as many
+    // jobs where they have one size)
     std::vector<msdd::WinJob> jobs;
     msdd::JobQueues qs{};
     size_t win_lds = 32;
     int kind = -2;
     if (level == 3) {
         const size_t share = ((size_t)ctx->cu_count * (size_t)per_cu);
+        // items of a block in this launch
+        auto part = [&](const WorkRange &w, const BlockRun &b, size_t &qa, size_t &qb) {
+            qa = std::max((size_t)w.first, (size_t)b.pos_begin * w.chunks);
+            qb = std::min((size_t)w.first + w.count, (size_t)b.pos_end * w.chunks);
+            return qa < qb;
+        };
+        // jobs per workgroup where they have one size, else 0 (the no-allocation
+        // solve, whose scratch holds jobs of 64 items, takes every job at its
+        // full size)
+        const WorkRange &w0 = ranges[0];
+        const InstView &v0 = views[w0.inst];
+        const bool one_long = ranges.size() == 1 && v0.K >= 64;
+        const double rounds = (double)n_items * ((std::min(w0.chunk_paths, w0.N) + 63) / 64) / (double)end_waves;
+        size_t equal = 0;
+        if (one_long && !arena && rounds < kEqualRounds && std::max(v0.n_xi, v0.n_eta) < kWin1MaxN)
+            equal = rounds < 8 ? 1 : rounds < 24 ? 2 : 3;
+        size_t piece = n_items;   // items of the largest equal job
+        if (equal) {
+            size_t lo = 1;
+            while (lo < piece) {
+                const size_t mid = (lo + piece) / 2;
+                size_t count = 0, qa, qb;
+                for (const BlockRun &b : sets[w0.inst]->blocks)
+                    if (part(w0, b, qa, qb)) count += (qb - qa + mid - 1) / mid;
+                if (count <= share * equal)
+                    piece = mid;
+                else
+                    lo = mid + 1;
+            }
+        }
         double total = 0.0;
         for (const WorkRange &w : ranges) total += (double)w.count * w.chunk_paths * views[w.inst].K;
-        const bool one_long = ranges.size() == 1 && views[ranges[0].inst].K >= 64;
         JobSizer sizer(total, one_long ? n_items : 32 * share, share, arena != nullptr);
         for (size_t ri = 0; ri < ranges.size(); ++ri) {
             const WorkRange &w = ranges[ri];
             const InstView &v = views[w.inst];
             const int p = msdd::path_kind(v);
             kind = kind == -2 || kind == p ? p : -1;
-            const size_t lo = w.first, hi = (size_t)w.first + w.count;
             const double item = (double)w.chunk_paths * v.K;
             for (const BlockRun &b : sets[w.inst]->blocks) {
-                const size_t qa = std::max(lo, (size_t)b.pos_begin * w.chunks);
-                const size_t qb = std::min(hi, (size_t)b.pos_end * w.chunks);
+                size_t qa, qb;
+                if (!part(w, b, qa, qb)) continue;
                 const bool blocked = b.tw < v.n_xi || b.th < v.n_eta;
                 // (at least 64 items, four for each wave, as a workgroup's waves
                 // wait for the last of them at the end of a job)
                 const size_t split = job_split(l, ranges.size() > 1, n_items / share, b.kind, blocked, v.n_xi, v.n_eta);
                 const size_t jmax = std::max<size_t>(64, (n_items + share * split - 1) / (share * split));
-                for (size_t q = qa, n; q < qb; q += n) {
-                    n = sizer.next(jmax, qb - q, item);
+                const size_t pieces = (qb - qa + piece - 1) / piece;
+                size_t q = qa;
+                for (size_t k = 0; q < qb; ++k) {
+                    const size_t n = equal ? (qb - qa) * (k + 1) / pieces - (qb - qa) * k / pieces
+                                           : sizer.next(jmax, qb - q, item);
                     jobs.push_back(msdd::WinJob{(uint32_t)ri, (uint32_t)q, (uint32_t)n, b.i0, b.j0, b.tw, b.th,
                                                 (uint32_t)b.kind});
+                    q += n;
                 }
-                if (qa < qb) win_lds = std::max(win_lds, window_bytes(b.kind, b.tw, b.th));
+                win_lds = std::max(win_lds, window_bytes(b.kind, b.tw, b.th));
             }
         }
         cut_queues(jobs, [&](const msdd::WinJob &j) {
             const WorkRange &w = ranges[j.range];
-            return (double)j.count * w.chunk_paths * views[w.inst].K;
+            return equal ? 1.0 : (double)j.count * w.chunk_paths * views[w.inst].K;
         }, qs);
     }
     // views, ranges and jobs in one copy

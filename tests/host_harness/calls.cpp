@@ -8,6 +8,9 @@
 //            has room for it beside everything else
 //   boxes    a forced LDS solve runs the LDS kernel for every subdomain that
 //            fits it, with threads for all its nodes
+//   jobs     the jobs of windowed launches hold every item once; those of a
+//            launch with few items are as many as its workgroups, or two or
+//            three times that, and of one size
 //   slices   no slices of 64 paths where many of their lanes would have no path
 //   fp64     FP64 requests are charged for the partial sums that they allocate
 // Exit status 0 when every check holds; a message names the first failure.
@@ -15,9 +18,11 @@
 #define launch_finalize stub_launch_finalize
 #define launch_subdomain_lds stub_launch_subdomain_lds
 #define launch_fe_sweep stub_launch_fe_sweep
+#define launch_paths_fp32_window stub_launch_paths_fp32_window
 #include "stub_kernels.cpp"
 #undef launch_subdomain_lds
 #undef launch_fe_sweep
+#undef launch_paths_fp32_window
 #undef launch_prep_mesh
 #undef launch_finalize
 
@@ -50,6 +55,9 @@ static std::vector<uint32_t> g_slices;           // slices per chunk of each req
 static uint32_t g_items = 0;                     // items per node of the last one
 static mesh_sdd_ctx *g_watched = nullptr;        // its memory in use at every staging, the most
 static std::atomic<uint64_t> g_most_in_use{0}, g_most_running{0};
+static std::vector<msdd::WinJob> g_jobs;         // of the last windowed launch, with its queues and ranges
+static msdd::JobQueues g_queues;
+static std::vector<msdd::WorkRange> g_ranges;
 static int g_lds_solves = 0, g_sweeps = 0;       // launches of the subdomain solves
 static std::mutex g_gate;                        // held: staging waits
 
@@ -77,6 +85,17 @@ hipError_t launch_finalize(const Partial *p, const NodeSpan *sp, const InstView 
     g_slices.push_back(v->slices);
     g_items = sp->count;
     return stub_launch_finalize(p, sp, v, M, n, mx, my, sx, sy, ef, t, s);
+}
+hipError_t launch_paths_fp32_window(const InstView *v, const WorkRange *r, const WinJob *j, const JobQueues &qs,
+                                    uint32_t *head, uint32_t cap, int kind, size_t lds, int grid, float *ends,
+                                    uint32_t waves, uint32_t lanes, uint32_t quarters, hipStream_t s)
+{
+    g_jobs.assign(j, j + qs.b[kJobQueues]);
+    g_queues = qs;
+    uint32_t n = 0;
+    for (const WinJob &job : g_jobs) n = std::max(n, job.range + 1);
+    g_ranges.assign(r, r + n);
+    return stub_launch_paths_fp32_window(v, r, j, qs, head, cap, kind, lds, grid, ends, waves, lanes, quarters, s);
 }
 hipError_t launch_subdomain_lds(const MeshStepArgs &a, double *x, double *y, hipStream_t s)
 {
@@ -452,6 +471,93 @@ static void scenario_boxes()
 }
 
 // ---------------------------------------------------------------------------
+// Every item of every range in exactly one job, no job empty, queues in order.
+static void check_jobs(const char *what)
+{
+    std::vector<std::vector<int>> seen;
+    for (const msdd::WorkRange &w : g_ranges) seen.emplace_back(w.count, 0);
+    for (const msdd::WinJob &j : g_jobs) {
+        check(j.count > 0, "%s: an empty job", what);
+        const msdd::WorkRange &w = g_ranges[j.range];
+        for (uint32_t k = 0; k < j.count; ++k) {
+            const uint32_t q = j.q0 + k - w.first;
+            if (q < w.count) ++seen[j.range][q];
+            else check(false, "%s: item %u outside its range", what, q);
+        }
+    }
+    for (auto &r : seen)
+        for (int c : r)
+            if (c != 1) return check(false, "%s: an item in %d jobs", what, c);
+    check(g_queues.b[0] == 0 && g_queues.b[msdd::kJobQueues] == g_jobs.size(), "%s: queues", what);
+}
+
+static void scenario_jobs()
+{
+    // 8 workgroups of 16 waves; 161^2 in 8 x 8: 2177 nodes in 3 x 3 blocks
+    Fixture f;
+    Problem p(161), q(193);
+    mesh_sdd *h = f.add(p, make_desc(161, 8, MESH_SDD_FP32, 100, 1));
+    mesh_sdd *g = f.add(q, make_desc(193, 2, MESH_SDD_FP32, 100, 2));
+    mesh_sdd *k = f.add(q, make_desc(193, 2, MESH_SDD_FP32, 20, 3));   // short paths
+    auto run = [&](mesh_sdd *i, const Problem &pr, int64_t n, uint32_t stride) {
+        mesh_sdd_step st = make_step(pr, n, 0);
+        st.interface_stride = stride;
+        Out o(mesh_sdd_num_interface_nodes(i), 0);
+        g_jobs.clear();
+        check(mesh_sdd_solve_interfaces(i, &st, &o.r) == MESH_SDD_OK, "solve");
+        return g_jobs.size();
+    };
+    struct {
+        mesh_sdd *i;
+        const Problem *p;
+        int64_t n;
+        uint32_t stride;
+        size_t jobs;   // at most (or one for each block); 0: not of equal size
+    } cases[] = {{g, &q, 64, 0, 8},    {g, &q, 65, 0, 8},   {g, &q, 150, 0, 16}, {g, &q, 640, 0, 24},
+                 {g, &q, 1300, 0, 0},  {h, &p, 64, 0, 16},  {h, &p, 200, 0, 0},  {h, &p, 100, 4, 9},
+                 {h, &p, 1, 0, 16},    {k, &q, 640, 0, 0},  {g, &q, 1, 8, 8}};
+    for (auto &c : cases) {
+        const size_t n = run(c.i, *c.p, c.n, c.stride);
+        check_jobs("alone");
+        if (!c.jobs) continue;
+        check(n <= c.jobs, "N = %d: %zu jobs, at most %zu", (int)c.n, n, c.jobs);
+        for (size_t a = 1; a < g_jobs.size(); ++a)   // the jobs of a block differ by one item at most
+            if (g_jobs[a].i0 == g_jobs[a - 1].i0 && g_jobs[a].j0 == g_jobs[a - 1].j0)
+                check(std::abs((int)g_jobs[a].count - (int)g_jobs[a - 1].count) <= 1, "N = %d: jobs of %u and %u items",
+                      (int)c.n, g_jobs[a].count, g_jobs[a - 1].count);
+    }
+    // several instances, and a job_split that is set
+    std::vector<mesh_sdd *> all{h, g, k};
+    std::vector<mesh_sdd_step> st{make_step(p, 500, 0), make_step(q, 64, 0), make_step(q, 900, 0)};
+    std::vector<Out> o;
+    std::vector<mesh_sdd_result> r;
+    for (mesh_sdd *i : all) o.emplace_back(mesh_sdd_num_interface_nodes(i), 0);
+    for (auto &x : o) r.push_back(x.r);
+    for (int split : {0, 1, 4096}) {
+        mesh_sdd_launch l;
+        std::memset(&l, 0, sizeof l);
+        l.struct_size = sizeof l;
+        l.job_split = split;
+        check(mesh_sdd_set_launch(f.ctx, &l) == MESH_SDD_OK, "set_launch");
+        g_jobs.clear();
+        check(mesh_sdd_solve_batch(all.data(), st.data(), r.data(), 3, nullptr) == MESH_SDD_OK, "batch");
+        check(g_ranges.size() == 3, "three ranges");
+        check_jobs("batch");
+        run(g, q, 1300, 0);
+        check_jobs("split");
+        run(g, q, 150, 0);
+        check_jobs("split, few items");
+    }
+    // the no-allocation solve
+    mesh_sdd_step dev = make_step(q, 640, 1);
+    Out d(mesh_sdd_num_interface_nodes(g), 1);
+    g_jobs.clear();
+    check(mesh_sdd_solve_interfaces_noalloc(g, &dev, &d.r) == MESH_SDD_OK, "noalloc");
+    check_jobs("noalloc");
+    for (const msdd::WinJob &j : g_jobs) check(j.count <= 64 || g_jobs.size() < 64, "noalloc: a job of %u items", j.count);
+}
+
+// ---------------------------------------------------------------------------
 static void scenario_slices()
 {
     // 381 nodes on 8 CUs: more slices than waves
@@ -476,6 +582,8 @@ int main(int argc, char **argv)
         scenario_budget();
     else if (what == "boxes")
         scenario_boxes();
+    else if (what == "jobs")
+        scenario_jobs();
     else if (what == "slices")
         scenario_slices();
     else if (what == "fp64")

@@ -7,6 +7,8 @@ budget: requests that run in slices of 64 paths claim memory for the slices'
 records only beside all else that is in use or waits, so they run together
 wherever whole chunks would, within the budget.
 boxes: a forced LDS solve runs the LDS kernel for every subdomain that fits it.
+jobs: the jobs of windowed launches hold every item once, in as many as the
+workgroups need.
 slices: no slices where many of their lanes would have no path.
 fp64: FP64 requests are charged for the partial sums that they allocate, and
 fit every budget that items of 256 paths fitted."""
@@ -34,7 +36,7 @@ def exe(tmp_path_factory):
     return out
 
 
-@pytest.mark.parametrize("scenario", ["arrays", "budget", "boxes", "slices", "fp64"])
+@pytest.mark.parametrize("scenario", ["arrays", "budget", "boxes", "jobs", "slices", "fp64"])
 def test_calls(exe, scenario):
     res = subprocess.run([exe, scenario], capture_output=True, text=True, timeout=300)
     assert res.returncode == 0 and "all checks passed" in res.stdout, (res.stdout + res.stderr)[-4000:]
