@@ -972,15 +972,16 @@ int run_fp32_launch(mesh_sdd_ctx *ctx, std::vector<InstView> &views, const std::
             qb = std::min((size_t)w.first + w.count, (size_t)b.pos_end * w.chunks);
             return qa < qb;
         };
-        // jobs per workgroup where they have one size, else 0 (the no-allocation
-        // solve, whose scratch holds jobs of 64 items, takes every job at its
-        // full size)
+        // jobs per workgroup where they have one size, else 0.  The scratch of
+        // the no-allocation solve is sized for jobs of 64 items: one size where
+        // it has room for the list, else every job at its full size
         const WorkRange &w0 = ranges[0];
         const InstView &v0 = views[w0.inst];
         const bool one_long = ranges.size() == 1 && v0.K >= 64;
         const double rounds = (double)n_items * ((std::min(w0.chunk_paths, w0.N) + 63) / 64) / (double)end_waves;
         size_t equal = 0;
-        if (one_long && !arena && rounds < kEqualRounds && std::max(v0.n_xi, v0.n_eta) < kWin1MaxN)
+        const size_t list = (3 * share + sets[w0.inst]->blocks.size()) * sizeof(msdd::WinJob) + 4096;   // the longest, and views
+        if (one_long && (!arena || arena->size - arena->used > list) && rounds < kEqualRounds && std::max(v0.n_xi, v0.n_eta) < kWin1MaxN)
             equal = rounds < 8 ? 1 : rounds < 24 ? 2 : 3;
         size_t piece = n_items;   // items of the largest equal job
         if (equal) {

@@ -548,13 +548,15 @@ static void scenario_jobs()
         run(g, q, 150, 0);
         check_jobs("split, few items");
     }
-    // the no-allocation solve
+    // the no-allocation solve: the same jobs where its scratch has room for the list
+    check(mesh_sdd_set_launch(f.ctx, nullptr) == MESH_SDD_OK, "set_launch");
+    const size_t alone = run(g, q, 640, 0);
     mesh_sdd_step dev = make_step(q, 640, 1);
     Out d(mesh_sdd_num_interface_nodes(g), 1);
     g_jobs.clear();
     check(mesh_sdd_solve_interfaces_noalloc(g, &dev, &d.r) == MESH_SDD_OK, "noalloc");
     check_jobs("noalloc");
-    for (const msdd::WinJob &j : g_jobs) check(j.count <= 64 || g_jobs.size() < 64, "noalloc: a job of %u items", j.count);
+    check(g_jobs.size() == alone, "noalloc: %zu jobs, %zu", g_jobs.size(), alone);
 }
 
 // ---------------------------------------------------------------------------
