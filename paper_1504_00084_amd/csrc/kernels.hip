@@ -1194,8 +1194,8 @@ struct Src64Job {
 // of it per job, as in paths_fp32_win; 0, global memory, for launches too short
 // for windows and for one that has no room for its job list (the no-allocation
 // solve).
-// Bound: VALU issue (about 200 vector instructions per path-step, 90 % of the
-// issue slots).  The form before it -- one thread per path, the library's log,
+// Bound: VALU issue (232 vector instructions issued per path-step, 181 with the
+// lanes that take part; 92 to 96 % of the issue slots).  The form before it -- one thread per path, the library's log,
 // sincospi, sqrt and exp, twelve 8-byte gathers per substep, no lane refill --
 // took about 680 slots and filled the texture path as well: 129^2 bump,
 // 753 nodes, N = 10^4, K = 500: 54.4 -> 20.8 ms; 33^2, 31 nodes, N = 10^4:

@@ -71,10 +71,11 @@ inline SubShape subdomain_shape(int P_xi, int P_eta, bool exact)
 // Whether tiles of the whole grid advance subdomains faster than one
 // workgroup for each does, by the time of a substep on `cus` compute units:
 // a workgroup's updates one after the other (80 ns each without divisions,
-// 270 with them; 220 ns for threads that own boundary nodes as well), or an eighth of a launch (630 ns) and the tiles that follow
-// one another on a compute unit.  4 x 4 boxes of 61 x 61, 300 substeps: LDS 1210
-// us, tiles 580; 2 x 2 of 65 x 65 without divisions 429 and 326; 12 x 12 of 42 x
-// 42, 100 substeps: LDS 225 us, tiles 781.
+// 270 with them; 220 ns for threads that own boundary nodes as well), or an
+// eighth of a launch (630 ns) and the tiles that follow one another on a
+// compute unit.  4 x 4 boxes of 61 x 61, 300 substeps: LDS 1210 us, tiles 580;
+// 2 x 2 of 65 x 65 without divisions 429 and 326; 12 x 12 of 42 x 42, 100
+// substeps: LDS 225 us, tiles 781.
 inline bool subdomain_tiles(int P_xi, int P_eta, long boxes, long cus, const SubShape &h, bool exact)
 {
     const long tiles = boxes * ((P_xi - 1 + kTileCore - 1) / kTileCore) * ((P_eta - 1 + kTileCore - 1) / kTileCore);

@@ -365,8 +365,9 @@ __device__ __forceinline__ int group64(PathD &P, const ConstD &C, const Tab64 &T
 // of its own paths in their order, so an item's totals depend neither on
 // the schedule nor on which wave ran it, and no path needs its end state
 // stored.  Two items are in flight per wave; the older one is reduced and
-// written once every lane has left it.  87 % of the lanes are busy on the
-// 129^2 bump (15 % of whose path-steps are saved by exits).  The stepping loop
+// written once every lane has left it.  Over all vector instructions 78 % of
+// the lanes take part on the 129^2 bump (15 % of whose path-steps are saved by
+// exits).  The stepping loop
 // is left once fewer than 48 lanes are busy (56 and 60: 1 and 2 % slower).
 struct Item64 {
     uint32_t node, p_begin, count, partial;

@@ -16,7 +16,7 @@ from collections import defaultdict
 
 
 def short(name: str) -> str:
-    name = name.split("(")[0]
+    name = name.replace("(anonymous namespace)::", "").split("(")[0]
     return name.replace("void ", "")
 
 
