@@ -54,8 +54,8 @@ def w_slots(per_xi: int, per_eta: int) -> float:
 # scaled by what the counter reads for a 1 GiB device copy in the same run.
 # Valid only for the kernel code it was measured on (kernels_sha1: SHA-1 of
 # csrc/kernels.hip without comments) and the workload named; null otherwise.
-TRAFFIC_RECORD = {"workload": "front257_8x8_perx", "kernels_sha1": "be45c705c70c2caeb1190e13bbe1a85e5b0331d0",
-                  "fetch_kib": 83773.9, "write_kib": 3449590.0, "fetch_scale": 2.0, "write_scale": 1.0}
+TRAFFIC_RECORD = {"workload": "front257_8x8_perx", "kernels_sha1": "952761fafd24be641467436b37624b9defb54381",
+                  "fetch_kib": 69379.3, "write_kib": 3151580.0, "fetch_scale": 2.0, "write_scale": 1.0}
 
 
 def kernels_code_sha1():
